@@ -10,13 +10,8 @@ same equations in plain binary64 torch.
 
 Families (`kind`):
   push    gcb_push (or gcb_push_noalloc) in two dimensions, gcb_push_3d in
-          three: `steps` steps of n particles.  A program calls it again and
-          again on the same arrays, so a pass advances the state in place.  In
-          the precision form the pass starts from a kept copy of the state (a
-          sort key near a tile's edge may fall on either side of it after a
-          pass whose binary32 rounding differs).
-  gr      gcb_push_gr, from a kept copy of the state: in this geometry the
-          particles fall in or fly off within some hundred calls.
+          three: `steps` steps of n particles.
+  gr      gcb_push_gr.
   back    gcb_push_backward / gcb_push_backward_3d on one segment.
   train   one step of a program that fits binary32 field parameters: forward
           push (autograd.push / autograd.push3, checkpointed), kinetic-energy
@@ -27,6 +22,13 @@ workloads, made on the GPU from the seed (which also moves the fields): half
 Maxwell-Juttner with theta = 1, half a Gamma^-2 power law to 1e4, isotropic.
 Positions come in the order a running simulation has them, that of an earlier
 cell sort, except where the particles are never sorted.
+
+A push pass starts from a kept copy of the state (one buffer, one copy), as a
+program does that follows the same particles under several parameters; left to
+run on for the tens of thousands of steps of a measurement, the inflow would
+gather all particles in the sheets and the hole swallow them.  Only unsorted
+binary64 pushes in flat space, the calls where every microsecond counts, run
+on in place.
 """
 from __future__ import annotations
 
@@ -303,35 +305,46 @@ def _inputs(case, seed):
     return F, st, qm, g
 
 
+def _packed(arrays):
+    """One buffer that holds the given arrays (wider types first), a copy of
+    it, and the arrays' views into the first."""
+    arrays = [(k, v) for k, v in arrays if v is not None]
+    arrays.sort(key=lambda kv: -kv[1].element_size())
+    start = torch.cat([v.contiguous().view(torch.uint8) for _, v in arrays])
+    buf, views, o = start.clone(), {}, 0
+    for k, v in arrays:
+        m = v.numel() * v.element_size()
+        views[k] = buf[o:o + m].view(v.dtype)
+        o += m
+    return start, buf, views
+
+
 def _prepare_push(case, seed):
     F, st, qm, _ = _inputs(case, seed)
     n, dim = case["n"], case["dim"]
     mixed = case["arith"] == "mixed"
-    t = {k: st[i].clone() for i, k in enumerate(_names(dim))}
-    if mixed:
-        for k in ("ux", "uy", "uz"):
-            t[k] = t[k].float()
-    t["qm"] = qm
-    t["id"] = torch.arange(n, dtype=torch.int32, device="cuda") if case["sort"] else None
-    t["status"] = torch.zeros(n, dtype=torch.uint8, device="cuda")
-    s = dict(case=case, ctx=_context(case, F), prm=_params(case), t=t,
-             trace=(torch.zeros((case["steps"], n), dtype=torch.uint8, device="cuda")
-                    if case["trace"] else None))
-    s["parts"] = (gcb.particles if dim == 2 else gcb.particles3)(t)
-    s["start"] = {k: v.clone() for k, v in t.items() if v is not None} if mixed else None
-    s["call"] = (gcb.gcb_push_3d if dim == 3 else
-                 gcb.gcb_push_noalloc if case["noalloc"] else gcb.gcb_push)
-    return s
+    rows = [(k, st[i].float() if mixed and k[0] == "u" else st[i])
+            for i, k in enumerate(_names(dim))]
+    start, buf, t = _packed(rows + [
+        ("qm", qm),
+        ("id", torch.arange(n, dtype=torch.int32, device="cuda") if case["sort"] else None),
+        ("status", torch.zeros(n, dtype=torch.uint8, device="cuda"))])
+    return dict(case=case, ctx=_context(case, F), prm=_params(case), t=t, buf=buf,
+                start=start if mixed or case["sort"] else None,
+                trace=(torch.zeros((case["steps"], n), dtype=torch.uint8, device="cuda")
+                       if case["trace"] else None),
+                parts=(gcb.particles if dim == 2 else gcb.particles3)(t),
+                call=(gcb.gcb_push_3d if dim == 3 else
+                      gcb.gcb_push_noalloc if case["noalloc"] else gcb.gcb_push))
 
 
 def _run_push(s):
-    case, t = s["case"], s["t"]
+    case = s["case"]
     if s["start"] is not None:
-        for k, v in s["start"].items():
-            t[k].copy_(v)
+        s["buf"].copy_(s["start"])
     st = s["call"](s["ctx"].handle, s["parts"], s["prm"], case["steps"], s_trace=s["trace"],
                    want_stats=case["stats"])
-    out = {k: v for k, v in t.items() if v is not None}
+    out = dict(s["t"])
     if s["trace"] is not None:
         out["trace"] = s["trace"]
     if st is not None:
@@ -430,20 +443,16 @@ def _prepare_gr(case, seed):
         kw["arith"] = gcb.GCB_ARITH_FAST
     prm = gcb.params(dt=GR["dt"], c=1.0, qm=GR["qm"], f_rho=GR["f_rho"], f_E=GR["f_E"],
                      n_iter=N_ITER, sort_every=case["sort"], **kw)
-    # positions and velocities are rows of one array each, so that going back
-    # to the start is two copies (and clearing the status bytes)
-    xs, us = x, u.float() if mixed else u
-    xw, uw = xs.clone(), us.clone()
-    t = dict(zip(_GR_NAMES, [xw[0], xw[1], xw[2], uw[0], uw[1], uw[2]]))
-    t["status"] = torch.zeros(n, dtype=torch.uint8, device="cuda")
-    return dict(case=case, ctx=ctx, prm=prm, start=(xs, us), work=(xw, uw), t=t,
+    if mixed:
+        u = u.float()
+    start, buf, t = _packed(list(zip(_GR_NAMES, [*x, *u])) + [
+        ("status", torch.zeros(n, dtype=torch.uint8, device="cuda"))])
+    return dict(case=case, ctx=ctx, prm=prm, start=start, buf=buf, t=t,
                 parts=gcb.gr_particles(t))
 
 
 def _run_gr(s):
-    s["work"][0].copy_(s["start"][0])
-    s["work"][1].copy_(s["start"][1])
-    s["t"]["status"].zero_()
+    s["buf"].copy_(s["start"])
     gcb.gcb_push_gr(s["ctx"].handle, s["parts"], s["prm"], s["case"]["steps"])
     return dict(s["t"])
 
