@@ -530,7 +530,7 @@ GCB_HD void gca_step_vjp(const Acc& acc, Sink& sink, const PushConst& pc, const 
         keep.put(1, s);
         uint32_t fl = 0;
         upn = parallel_update(L, upar, conserved_mu(mu), qm, curv, K, fl);
-        drift_terms(L, upn, conserved_mu(mu), inv_qm, curv, K, Fn[0], Fn[1]);
+        drift_terms(L, s, upn, conserved_mu(mu), inv_qm, curv, K, Fn[0], Fn[1]);
     }
     double Rk[kMaxAdjIter + 1][2];
     Rk[0][0] = x;
@@ -545,7 +545,7 @@ GCB_HD void gca_step_vjp(const Acc& acc, Sink& sink, const PushConst& pc, const 
             LocalD L;
             local_at<kYee>(acc, pc, K, Rk[k][0], Rk[k][1], s, L);
             keep.put(1 + k, s);
-            drift_terms(L, upn, conserved_mu(mu), inv_qm, curv, K, F[0], F[1]);
+            drift_terms(L, s, upn, conserved_mu(mu), inv_qm, curv, K, F[0], F[1]);
         }
         Rk[k + 1][0] = x + h * (Fn[0] + F[0]);
         Rk[k + 1][1] = y + h * (Fn[1] + F[1]);

@@ -317,7 +317,7 @@ GCB_HD void gca_step_vjp3(const GlobalAcc3<double>& acc, Sink& sink, const PushC
         keep.put(1, s);
         uint32_t fl = 0;
         upn = parallel_update(L, upar, conserved_mu(mu), qm, curv, K, fl);
-        drift_terms3(L, upn, conserved_mu(mu), inv_qm, curv, K, Fn);
+        drift_terms3(L, s, upn, conserved_mu(mu), inv_qm, curv, K, Fn);
     }
     double Rk[kMaxAdjIter + 1][3];
     for (int a = 0; a < 3; ++a) Rk[0][a] = x[a];
@@ -330,7 +330,7 @@ GCB_HD void gca_step_vjp3(const GlobalAcc3<double>& acc, Sink& sink, const PushC
             LocalD L;
             local_at3<kYee>(acc, pc, K, Rk[k], s, L);
             keep.put(1 + k, s);
-            drift_terms3(L, upn, conserved_mu(mu), inv_qm, curv, K, F);
+            drift_terms3(L, s, upn, conserved_mu(mu), inv_qm, curv, K, F);
         }
         for (int a = 0; a < 3; ++a) Rk[k + 1][a] = x[a] + h * (Fn[a] + F[a]);
     }

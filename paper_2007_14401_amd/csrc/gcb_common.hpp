@@ -55,37 +55,61 @@ constexpr double kDFloor = 1.0e-12;
 // NaN, have no field: a gather there returns NaN (a runaway iteration).
 constexpr double kFarLattice = 1073741824.0;   // 2^30
 
-// 1/sqrt(x) for finite x > 0 in binary64: the hardware estimate refined by
-// two Newton-Raphson steps y <- y + y (1 - x y^2)/2 (each roughly doubles
-// the number of correct bits; the result is within a few units in the last
+// 1/sqrt(x) for finite x > 0 in binary64: the hardware estimate (good to
+// about 2^-24) refined by one third-order step, y <- y (1 + e/2 + 3 e^2/8) with
+// e = 1 - x y^2: the next term of the series, 5 e^3/16, lies below 2^-68.
+// Five operations where two Newton-Raphson steps took eight, with the same
+// error (the rounding of e and of the last sum: within two units in the last
 // place).
 GCB_HD double rsqrt_nr(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    double y = __builtin_amdgcn_rsq(x);
+    const double y = __builtin_amdgcn_rsq(x);
 #else
-    double y = 1.0 / sqrt(x);
+    const double y = 1.0 / sqrt(x);
 #endif
-    double e = fma(-(x * y), y, 1.0);
-    y = fma(0.5 * y, e, y);
-    e = fma(-(x * y), y, 1.0);
-    y = fma(0.5 * y, e, y);
-    return y;
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// 1/x for finite normal x in binary64: the hardware estimate refined by two
-// Newton-Raphson steps y <- y + y (1 - x y); within a few units in the last
-// place.
+// 1/x for finite normal x in binary64: the hardware estimate refined by one
+// third-order step, y <- y (1 + e + e^2) with e = 1 - x y (the next term, e^3,
+// lies below 2^-68); within a unit in the last place.
 GCB_HD double rcp_nr(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    double y = __builtin_amdgcn_rcp(x);
+    const double y = __builtin_amdgcn_rcp(x);
 #else
-    double y = 1.0 / x;
+    const double y = 1.0 / x;
 #endif
-    double e = fma(-x, y, 1.0);
-    y = fma(y, e, y);
-    e = fma(-x, y, 1.0);
-    y = fma(y, e, y);
-    return y;
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// The same where x may be 0 or infinite: the estimate, 1/x there, stays.
+GCB_HD double rcp_nr0(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rcp(x);
+#else
+    const double y = 1.0 / x;
+#endif
+    const double e = fma(-x, y, 1.0);
+    return e == e ? fma(y, fma(e, e, e), y) : y;
+}
+
+// sqrt(x) for finite x >= 0 in binary64, from the refined reciprocal square
+// root (NaN stays NaN)
+GCB_HD double sqrt_nr(double x) {
+    if (x == 0.0) return x;
+    const double y = rsqrt_nr(x);
+    const double s = x * y;
+    return fma(fma(-s, s, x), 0.5 * y, s);
+}
+
+// a/b in binary64 from the refined reciprocal: the quotient corrected by its
+// own remainder (rounded as a division, up to ties)
+GCB_HD double div_nr(double a, double b) {
+    const double r = rcp_nr(b);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
 }
 
 // 2D Yee lattice offsets (cells) of Ex, Ey, Ez, Bx, By, Bz.
@@ -98,7 +122,8 @@ struct PushConst {
     double f_rho, f_E, inv_dl, fp_tol;
     double inv_dx, inv_dy, Lx, Ly;
     double qm;               // used when the per-particle array is absent
-    double inv_Lx, inv_Ly;   // 1/Lx, 1/Ly (the production binary64 form)
+    // the production binary64 form: 1/Lx, 1/Ly, f_E^2 and c^2/dl
+    double inv_Lx, inv_Ly, f_E2, c2_inv_dl;
     double stagger[6][2];
     int32_t nx, ny;
     int32_t curvature, n_iter;

@@ -376,6 +376,7 @@ PushConst physics_const(const gcb_params* prm) {
     pc.c = prm->c;
     pc.c2 = prm->c * prm->c;
     pc.inv_c2 = 1.0 / (prm->c * prm->c);
+    pc.f_E2 = prm->f_E * prm->f_E;
     pc.f_rho = prm->f_rho;
     pc.f_E = prm->f_E;
     pc.fp_tol = prm->fp_tol;
@@ -390,6 +391,7 @@ PushConst physics_const(const gcb_params* prm) {
 PushConst make_const(const gcb_ctx* ctx, const gcb_params* prm) {
     PushConst pc = physics_const(prm);
     pc.inv_dl = 1.0 / std::sqrt(ctx->dx * ctx->dy);
+    pc.c2_inv_dl = pc.c2 * pc.inv_dl;
     pc.inv_dx = 1.0 / ctx->dx;
     pc.inv_dy = 1.0 / ctx->dy;
     pc.Lx = ctx->nx * ctx->dx;
@@ -407,6 +409,7 @@ PushConst3 make_const3(const gcb_ctx* ctx, const gcb_params* prm) {
     PushConst3 pc{};
     pc.b = physics_const(prm);
     pc.b.inv_dl = 1.0 / std::cbrt((ctx->d3[0] * ctx->d3[1]) * ctx->d3[2]);
+    pc.b.c2_inv_dl = pc.b.c2 * pc.b.inv_dl;
     pc.b.inv_dx = 1.0 / ctx->d3[0];
     pc.b.inv_dy = 1.0 / ctx->d3[1];
     pc.inv_dz = 1.0 / ctx->d3[2];

@@ -43,7 +43,19 @@ constexpr bool kMixed = std::is_same<R, float>::value;
 // from 1/sqrt(B^2), kappa and 1/kappa from 1/sqrt(1 - v_E^2/c^2), 1/Gamma
 // from 1/sqrt(1 + u^2/c^2)) and divisions by per-launch constants become
 // multiplications.  Each such value differs from the correctly rounded one
-// by a few units in the last place.
+// by a few units in the last place.  The production form also takes shorter
+// expressions of the same quantities where they are no less accurate:
+//   - the bilinear sample as nested linear interpolations, whose differences
+//     are the gradients' too; a sample's gradients are per cell, and the
+//     direction they are taken along is scaled by 1/dx, 1/dy instead
+//     (8 operations per component with gradients for 14 and the weights);
+//   - the curvature drift from the derivative of B along one direction:
+//     b x (V.grad)b = b x (V.grad)B / B, because (V.grad)b is (V.grad)B / B
+//     less its part along b, for V = (u_par^2/Gamma) b + u_par v_E
+//     (v_curv_dir); likewise A and C, as v_E is perpendicular to b.
+// The step is bound by the issue of its binary64 arithmetic (VALU busy in two
+// thirds of the SIMD cycles, memory at a sixth), so time follows the count of
+// operations.
 #ifndef GCB_FAST_ARITH
 #define GCB_FAST_ARITH 0
 #endif
@@ -115,6 +127,27 @@ struct SampleEG : Sample<R> {
     R dEx[3], dEy[3];   // d E_i / dx, d E_i / dy
 };
 
+// The production form's bilinear sample of one component: f = f00 + wx cx +
+// wy cy + wx wy cxy, the gradients (per cell) cx + wy cxy and cy + wx cxy.
+// A cell's coefficients c = (f00, cx, cy, cxy):
+template <typename R>
+GCB_HD void cell_coefs(R f00, R f10, R f01, R f11, R c[4]) {
+    c[0] = f00;
+    c[1] = f10 - f00;
+    c[2] = f01 - f00;
+    c[3] = (f11 - f01) - c[1];
+}
+
+template <bool kGrad, typename R>
+GCB_HD void eval_coefs(const R c[4], R wx, R wy, R& val, R& ddx, R& ddy) {
+    const R gx = c[1] + wy * c[3];
+    val = (c[0] + wx * gx) + wy * c[2];
+    if constexpr (kGrad) {
+        ddx = gx;
+        ddy = c[2] + wx * c[3];
+    }
+}
+
 // One component at grid coordinates (gx, gy) = (X/dx, Y/dy) with lattice
 // offset (sx, sy) in cells (runtime stagger table).
 template <typename R, bool kGrad, class Acc>
@@ -130,6 +163,12 @@ GCB_HD void interp_comp(const Acc& acc, int k, double gx, double gy,
     double f00d, f10d, f01d, f11d;
     acc.quad(k, (int)fi, (int)fj, f00d, f10d, f01d, f11d);
     const R f00 = (R)f00d, f10 = (R)f10d, f01 = (R)f01d, f11 = (R)f11d;
+    if constexpr (kFastD<R>) {
+        R c[4];
+        cell_coefs(f00, f10, f01, f11, c);
+        eval_coefs<kGrad>(c, wx, wy, val, ddx, ddy);
+        return;
+    }
     const R ax = (R)1 - wx;
     const R ay = (R)1 - wy;
     val = (((ax * ay) * f00 + (wx * ay) * f10) + (ax * wy) * f01) + (wx * wy) * f11;
@@ -154,6 +193,19 @@ GCB_HD void interp_yee(const Loader& ld, const R wx[2], const R wy[2],
         const R ay = (R)1 - by;
         R f00, f10, f01, f11;
         ld.template load4<R>(set, k, f00, f10, f01, f11);
+        if constexpr (kFastD<R>) {
+            R c[4];
+            cell_coefs(f00, f10, f01, f11, c);
+            if (k < 3) {
+                if constexpr (S::kGradE)
+                    eval_coefs<true>(c, bx, by, s.E[k], s.dEx[k], s.dEy[k]);
+                else
+                    eval_coefs<false>(c, bx, by, s.E[k], s.E[k], s.E[k]);
+            } else {
+                eval_coefs<kGrad>(c, bx, by, s.B[k - 3], s.dBx[k - 3], s.dBy[k - 3]);
+            }
+            continue;
+        }
         const R val = (((ax * ay) * f00 + (bx * ay) * f10) + (ax * by) * f01) + (bx * by) * f11;
         if (k < 3) {
             s.E[k] = val;
@@ -232,8 +284,8 @@ GCB_HD void gather_at(const Acc& acc, const PushConst& pc, const Consts<R>& K, d
 // gathered at the origin instead, so that every node index stays a small
 // integer, and the values are replaced afterwards.
 template <typename R, bool kGrad, bool kYee, class Acc, class S>
-GCB_HD void gather(const Acc& acc, const PushConst& pc,
-                                       const Consts<R>& K, double X, double Y, S& s) {
+GCB_HD void gather(const Acc& acc, const PushConst& pc, const Consts<R>& K, double X, double Y,
+                   S& s) {
     double gx = X * pc.inv_dx;
     double gy = Y * pc.inv_dy;
     const bool far = !(fabs(gx) < kFarLattice && fabs(gy) < kFarLattice);
@@ -268,7 +320,7 @@ struct Local {
     R B, inv_B;
     R b[3], vE[3];
     R kappa, Epar;
-    R inv_kappa;   // production form only: sqrt(1 - v_E^2/c^2)
+    R inv_kappa, om;   // production form only: 1/kappa and 1/kappa^2
     R bgb[3], vgb[3];
     R A, C;
     R gB[3];   // grad|B| (the 2D step fills x, y)
@@ -331,6 +383,7 @@ GCB_HD uint32_t local_fields(const R E[3], const R Bv[3], const Consts<R>& K, Lo
             const R k = rsqrt_nr(om);
             L.kappa = k;
             L.inv_kappa = om * k;
+            L.om = om;
         } else {
             L.kappa = (R)1 / sqrt(om);
         }
@@ -356,13 +409,23 @@ GCB_HD void curvature_scalars(Local<R>& L) {
     L.C = (L.vE[0] * L.vgb[0] + L.vE[1] * L.vgb[1]) + L.vE[2] * L.vgb[2];
 }
 
+// a gradient of a sample in units of length: the production form's samples
+// carry gradients per cell
+template <typename R>
+GCB_HD void per_length(const R d[3], R inv_d, R out[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) out[i] = kFastD<R> ? d[i] * inv_d : d[i];
+}
+
 // 2D: gradients along x and y only.
 template <typename R>
 GCB_HD uint32_t local_from_sample(const Sample<R>& s, const Consts<R>& K, Local<R>& L) {
     const uint32_t flags = local_fields(s.E, s.B, K, L);
-    R dbx[3], dby[3];
-    L.gB[0] = db_along(L, s.dBx, dbx);
-    L.gB[1] = db_along(L, s.dBy, dby);
+    R gx[3], gy[3], dbx[3], dby[3];
+    per_length(s.dBx, K.inv_dx, gx);
+    per_length(s.dBy, K.inv_dy, gy);
+    L.gB[0] = db_along(L, gx, dbx);
+    L.gB[1] = db_along(L, gy, dby);
     L.gB[2] = (R)0;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -418,7 +481,10 @@ GCB_HD uint32_t local_fields_exact(const R E[3], const R Bv[3], const Consts<R>&
     }
     const R kappa = (R)1 / sqrt(om);
     L.kappa = kappa;
-    if constexpr (kFastD<R>) L.inv_kappa = (R)1 / kappa;
+    if constexpr (kFastD<R>) {
+        L.inv_kappa = (R)1 / kappa;
+        L.om = om;
+    }
     const R Bp2 = (R)0.5 * ((B2 - E2) + S * s);
     const R Bp = sqrt(Bp2 > (R)0 ? Bp2 : (R)0);
     const bool bpzero = (Bp == (R)0);
@@ -557,14 +623,19 @@ template <typename R>
 GCB_HD uint32_t local_exact_curv(const SampleEG<R>& s, const Consts<R>& K, Local<R>& L) {
     const uint32_t flags = local_fields_exact(s.E, s.B, K, L);
     Dual<R, 2> E[3], Bv[3], b[3];
+    R dEx[3], dEy[3], dBx[3], dBy[3];
+    per_length(s.dEx, K.inv_dx, dEx);
+    per_length(s.dEy, K.inv_dy, dEy);
+    per_length(s.dBx, K.inv_dx, dBx);
+    per_length(s.dBy, K.inv_dy, dBy);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         E[i].v = s.E[i];
-        E[i].d[0] = s.dEx[i];
-        E[i].d[1] = s.dEy[i];
+        E[i].d[0] = dEx[i];
+        E[i].d[1] = dEy[i];
         Bv[i].v = s.B[i];
-        Bv[i].d[0] = s.dBx[i];
-        Bv[i].d[1] = s.dBy[i];
+        Bv[i].d[0] = dBx[i];
+        Bv[i].d[1] = dBy[i];
     }
     bstar_dual<R, 2>(E, Bv, K, b);
 #pragma unroll
@@ -580,8 +651,8 @@ GCB_HD uint32_t local_exact_curv(const SampleEG<R>& s, const Consts<R>& K, Local
 // the local quantities of the guiding-center step in the chosen frame (any
 // sample type with E and B; the reduced frame's gradients come from it, the
 // exact frame's curvature terms from a sample with the E gradients)
-template <bool kExact, typename R, class S>
-GCB_HD uint32_t local_in_frame(const S& s, const Consts<R>& K, Local<R>& L) {
+template <bool kExact, typename R, class S, class KC>
+GCB_HD uint32_t local_in_frame(const S& s, const KC& K, Local<R>& L) {
     if constexpr (kExact && S::kGradE)
         return local_exact_curv(s, K, L);
     else if constexpr (kExact)
@@ -669,6 +740,61 @@ GCB_HD void v_curv_g(const Local<R>& L, R upar, const Gam<R>& G, R inv_qm,
     }
 }
 
+// (V.grad)B at a sample of the production form, V[j] in units of length
+template <typename R>
+GCB_HD void b_along(const Sample<R>& s, const R V[3], const Consts<R>& K, R g[3]) {
+    const R vx = V[0] * K.inv_dx, vy = V[1] * K.inv_dy;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) g[i] = vx * s.dBx[i] + vy * s.dBy[i];
+}
+
+// The curvature drift in the production form, from the sample's gradients and
+// L's b, v_E, kappa, B: (m c kappa^2/(q B^2)) b x (V.grad)B with
+// V = (u_par^2/Gamma) b + u_par v_E.
+template <typename R, class S, class KC>
+GCB_HD void v_curv_dir(const Local<R>& L, const S& s, R upar, R inv_gam, R inv_qm,
+                       const KC& K, R vc[3]) {
+    const R a1 = (upar * upar) * inv_gam;
+    const R V[3] = {a1 * L.b[0] + upar * L.vE[0], a1 * L.b[1] + upar * L.vE[1],
+                    a1 * L.b[2] + upar * L.vE[2]};
+    R w[3];
+    b_along(s, V, K, w);
+    const R kb = L.kappa * L.inv_B;
+    const R pre = (kb * kb) * (K.c * inv_qm);
+    vc[0] = pre * (L.b[1] * w[2] - L.b[2] * w[1]);
+    vc[1] = pre * (L.b[2] * w[0] - L.b[0] * w[2]);
+    vc[2] = pre * (L.b[0] * w[1] - L.b[1] * w[0]);
+}
+
+// A = v_E.(b.grad)b and C = v_E.(v_E.grad)b in the production form
+template <typename R, class S, class KC>
+GCB_HD void curvature_scalars_dir(const S& s, const KC& K, Local<R>& L) {
+    R gb[3], gv[3];
+    b_along(s, L.b, K, gb);
+    b_along(s, L.vE, K, gv);
+    L.A = ((L.vE[0] * gb[0] + L.vE[1] * gb[1]) + L.vE[2] * gb[2]) * L.inv_B;
+    L.C = ((L.vE[0] * gv[0] + L.vE[1] * gv[1]) + L.vE[2] * gv[2]) * L.inv_B;
+}
+
+// The local quantities of a step (kDir: the production form, whose drift and
+// scalars come from the sample by the three functions above)
+template <bool kDir, bool kExact, typename R, class S, class KC>
+GCB_HD uint32_t local_of(const S& s, const KC& K, Local<R>& L) {
+    if constexpr (kDir)
+        return local_fields(s.E, s.B, K, L);
+    else
+        return local_in_frame<kExact, R>(s, K, L);
+}
+
+template <bool kDir, typename R, class S, class KC>
+GCB_HD void v_curv_of(const Local<R>& L, const S& s, R upar, const Gam<R>& G, R inv_qm,
+                      const KC& K, R vc[3]) {
+    if constexpr (kDir)
+        v_curv_dir(L, s, upar, G.inv, inv_qm, K, vc);
+    else
+        v_curv_g(L, upar, G, inv_qm, K, vc);
+}
+
 // Curvature drift with the grad-B drift in its bracket (the mirror option):
 // (m c kappa^2/(q B)) b x [ (u_par^2/Gamma)(b.grad)b + u_par (v_E.grad)b
 //                           + (mu/(m kappa Gamma)) grad|B| ]
@@ -737,7 +863,15 @@ template <typename R>
 GCB_HD bool switch_gca(const R E[3], const R Bv[3], R ux, R uy, R uz,
                                            double qm, const PushConst& pc,
                                            const Consts<R>& K) {
-    if constexpr (!kMixed<R>) {
+    if constexpr (kFastD<R>) {
+        // the same ratios from the reciprocal square roots that the
+        // guiding-center step takes too, E/B < f_E as E^2/B^2 < f_E^2
+        const R B2 = (Bv[0] * Bv[0] + Bv[1] * Bv[1]) + Bv[2] * Bv[2];
+        const R E2 = (E[0] * E[0] + E[1] * E[1]) + E[2] * E[2];
+        const R inv_B = B2 > (R)0 ? rsqrt_nr(B2) : (R)0;
+        const R rr = ((gamma_full2(ux, uy, uz, K).g * inv_B) * fabs(rcp_nr0(qm))) * pc.c2_inv_dl;
+        return B2 > (R)0 && (rr < pc.f_rho) && ((E2 * inv_B) * inv_B < pc.f_E2);
+    } else if constexpr (!kMixed<R>) {
         return switch_gca_f64(E, Bv, ux, uy, uz, qm, pc);
     } else {
         const R B = sqrt((Bv[0] * Bv[0] + Bv[1] * Bv[1]) + Bv[2] * Bv[2]);
@@ -804,11 +938,18 @@ GCB_HD void boris(const R E[3], const R Bv[3], R& ux, R& uy, R& uz,
                                       R qm, const Consts<R>& K) {
     const R hq = (qm * K.dt) * (R)0.5;
     const R umx = ux + hq * E[0], umy = uy + hq * E[1], umz = uz + hq * E[2];
-    const R gm = gamma_full(umx, umy, umz, K);
-    const R f = hq / (K.c * gm);
+    R f;
+    if constexpr (kFastD<R>)   // a systematic rounding here would show in every rotation
+        f = div_nr(hq, K.c * sqrt_nr((R)1 + ((umx * umx + umy * umy) + umz * umz) * K.inv_c2));
+    else
+        f = hq / (K.c * gamma_full(umx, umy, umz, K));
     const R tx = f * Bv[0], ty = f * Bv[1], tz = f * Bv[2];
     const R t2 = (tx * tx + ty * ty) + tz * tz;
-    const R g = (R)2 / ((R)1 + t2);
+    R g;
+    if constexpr (kFastD<R>)
+        g = (R)2 * rcp_nr0((R)1 + t2);
+    else
+        g = (R)2 / ((R)1 + t2);
     const R sx = g * tx, sy = g * ty, sz = g * tz;
     const R upx = umx + (umy * tz - umz * ty);
     const R upy = umy + (umz * tx - umx * tz);
@@ -865,7 +1006,7 @@ GCB_HD R parallel_update(const Local<R>& Ln, R upar, const Gyr<R>& gy, R qm,
     const R DD = D * D;
     R k1;
     if constexpr (kFastD<R>)
-        k1 = (h * h) * (C * C) - (K.c2 * DD) * (Ln.inv_kappa * Ln.inv_kappa);
+        k1 = (h * h) * (C * C) - (K.c2 * DD) * Ln.om;
     else
         k1 = (h * h) * (C * C) - (K.c2 * DD) / (Ln.kappa * Ln.kappa);
     const R k2 = (upr * K.dt) * C;
@@ -873,15 +1014,27 @@ GCB_HD R parallel_update(const Local<R>& Ln, R upar, const Gyr<R>& gy, R qm,
     const R disc = k2 * k2 - ((R)4 * k1) * k3;
     const bool dok = fabs(D) >= (R)kDFloor;
     bool ok = (k1 < (R)0) && (disc >= (R)0) && dok;
-    const R sq = sqrt(disc >= (R)0 ? disc : (R)0);
+    R sq;
+    if constexpr (kFastD<R>)
+        sq = sqrt_nr(disc >= (R)0 ? disc : (R)0);
+    else
+        sq = sqrt(disc >= (R)0 ? disc : (R)0);
     const bool pos_k2 = k2 >= (R)0;
     const R num = pos_k2 ? k2 + sq : (R)2 * k3;
     R den = pos_k2 ? (R)(-2) * k1 : sq - k2;
     den = (ok && den > (R)0) ? den : (R)1;
-    const R gp = num / den;
+    R gp;
+    if constexpr (kFastD<R>)
+        gp = div_nr(num, den);
+    else
+        gp = num / den;
     ok = ok && (gp > (R)0) && __builtin_isfinite(gp);
     const R Ds = dok ? D : (R)1;
-    if (ok) return (upr + (h * gp) * C) / Ds;
+    if constexpr (kFastD<R>) {
+        if (ok) return div_nr(upr + (h * gp) * C, Ds);
+    } else {
+        if (ok) return (upr + (h * gp) * C) / Ds;
+    }
     flags |= ST_QUAD;
     if (dok) {
         const R gfb = gamma_gca(Ln, upr / Ds, gy, K);
@@ -911,10 +1064,10 @@ GCB_HD R mirror_parallel(const Local<R>& Ln, R upar, const Gyr<R>& gy, R qm,
 
 // x, y components of u_par b / Gamma + v_E + v_c at a point (v_c with the
 // grad-B drift under the mirror option).
-template <typename R>
-GCB_HD void drift_terms(const Local<R>& L, R upn, const Gyr<R>& gy, R inv_qm,
-                                            bool curvature, const Consts<R>& K, R& Fx,
-                                            R& Fy, bool mirror = false) {
+template <bool kDir = false, typename R>
+GCB_HD void drift_terms(const Local<R>& L, const Sample<R>& s, R upn, const Gyr<R>& gy,
+                        R inv_qm, bool curvature, const Consts<R>& K, R& Fx, R& Fy,
+                        bool mirror = false) {
     const Gam<R> G = gamma_gca2(L, upn, gy, K);
     const R a = over(upn, G);
     if (curvature) {
@@ -922,7 +1075,7 @@ GCB_HD void drift_terms(const Local<R>& L, R upn, const Gyr<R>& gy, R inv_qm,
         if (mirror)
             v_curv_mirror<2>(L, upn, G.g, inv_qm, gy.mu, K, vc);
         else
-            v_curv_g(L, upn, G, inv_qm, K, vc);
+            v_curv_of<kDir>(L, s, upn, G, inv_qm, K, vc);
         Fx = (a * L.b[0] + L.vE[0]) + vc[0];
         Fy = (a * L.b[1] + L.vE[1]) + vc[1];
     } else {
@@ -1015,7 +1168,13 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
     const double x = r.x, y = r.y;
     const R ux = r.ux, uy = r.uy, uz = r.uz;
     const R qm = (R)r.qm;
-    const R inv_qm = (R)1 / qm;
+    // the production form of the reduced frame (see v_curv_dir)
+    constexpr bool kDir = kFastD<R> && !kExact && !kMirror;
+    R inv_qm;
+    if constexpr (kFastD<R>)
+        inv_qm = rcp_nr0(qm);
+    else
+        inv_qm = (R)1 / qm;
 
     // 1. guiding-center variables at R^{n-1/2} = (x^n + x^{n-1})/2
     R upar, bpx, bpy, bpz;
@@ -1026,12 +1185,12 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
         Smp sh;
         gather<R, true, kYee>(acc, pc, K, Rhx, Rhy, sh);
         Local<R> Lh;
-        flags |= local_in_frame<kExact>(sh, K, Lh);
+        flags |= local_of<kDir, kExact, R>(sh, K, Lh);
         upar = (ux * Lh.b[0] + uy * Lh.b[1]) + uz * Lh.b[2];
         const Gam<R> G = gamma_full2(ux, uy, uz, K);
         const R gf = G.g;
         R vc[3] = {(R)0, (R)0, (R)0};
-        if (curv) v_curv_g(Lh, upar, G, inv_qm, K, vc);
+        if (curv) v_curv_of<kDir>(Lh, sh, upar, G, inv_qm, K, vc);
         const R upx = (ux - upar * Lh.b[0]) - (Lh.vE[0] + vc[0]) * gf;
         const R upy = (uy - upar * Lh.b[1]) - (Lh.vE[1] + vc[1]) * gf;
         const R upz = (uz - upar * Lh.b[2]) - (Lh.vE[2] + vc[2]) * gf;
@@ -1064,15 +1223,18 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
         if constexpr (kExCurv) {
             SampleEG<R> se;
             gather<R, true, kYee>(acc, pc, K, x, y, se);
-            flags |= local_in_frame<kExact>(se, K, Ln);
+            flags |= local_in_frame<kExact, R>(se, K, Ln);
         } else {
-            flags |= local_in_frame<kExact>(sn, K, Ln);
+            flags |= local_of<kDir, kExact, R>(sn, K, Ln);
+            if constexpr (kDir) {
+                if (curv) curvature_scalars_dir(sn, K, Ln);
+            }
         }
         if (mirror)
             upn = mirror_parallel<2>(Ln, upar, gy, qm, K, flags);
         else
             upn = parallel_update(Ln, upar, gy, qm, curv, K, flags);
-        drift_terms(Ln, upn, gy, inv_qm, curv, K, Fnx, Fny, mirror);
+        drift_terms<kDir>(Ln, sn, upn, gy, inv_qm, curv, K, Fnx, Fny, mirror);
         if constexpr (kPhase) {
             R d[3] = {bpx, bpy, bpz};
             phase_advance(Ln, upar, upn, gy, qm, K, d);
@@ -1095,8 +1257,8 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
             Smp sk;
             gather<R, true, kYee>(acc, pc, K, Rx, Ry, sk);
             Local<R> Lk;
-            flags |= local_in_frame<kExact>(sk, K, Lk);
-            drift_terms(Lk, upn, gy, inv_qm, curv, K, Fkx, Fky, mirror);
+            flags |= local_of<kDir, kExact, R>(sk, K, Lk);
+            drift_terms<kDir>(Lk, sk, upn, gy, inv_qm, curv, K, Fkx, Fky, mirror);
         }
         const double Rx_new = x + (double)(K.h * (Fnx + Fkx));
         const double Ry_new = y + (double)(K.h * (Fny + Fky));
@@ -1114,12 +1276,16 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
         Smp sm;
         gather<R, true, kYee>(acc, pc, K, Rmx, Rmy, sm);
         Local<R> Lm;
-        flags |= local_in_frame<kExact>(sm, K, Lm);
+        flags |= local_of<kDir, kExact, R>(sm, K, Lm);
         const Gam<R> G = gamma_gca2(Lm, upn, gy, K);
         const R gr = G.g;
         R vc[3] = {(R)0, (R)0, (R)0};
-        if (curv) v_curv_g(Lm, upn, G, inv_qm, K, vc);
-        const R um = sqrt(uperp_sq(Lm, gy));
+        if (curv) v_curv_of<kDir>(Lm, sm, upn, G, inv_qm, K, vc);
+        R um;
+        if constexpr (kFastD<R>)
+            um = sqrt_nr(uperp_sq(Lm, gy));
+        else
+            um = sqrt(uperp_sq(Lm, gy));
         r.ux = (upn * Lm.b[0] + (Lm.vE[0] + vc[0]) * gr) + um * bpx;
         r.uy = (upn * Lm.b[1] + (Lm.vE[1] + vc[1]) * gr) + um * bpy;
         r.uz = (upn * Lm.b[2] + (Lm.vE[2] + vc[2]) * gr) + um * bpz;

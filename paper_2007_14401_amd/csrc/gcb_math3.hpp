@@ -59,6 +59,27 @@ struct SampleEG3 : Sample3<R> {
 template <typename R>
 GCB_HD void trilerp(const R f[8], R wx, R wy, R wz, const Consts3<R>& K, bool grad, R& val,
                     R& ddx, R& ddy, R& ddz) {
+    if constexpr (kFastD<R>) {
+        // the production form: nested linear interpolations, whose
+        // differences are the (per-cell) gradients' too
+        R d[4], e[4];   // along x at (y, z) = (0,0), (1,0), (0,1), (1,1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            d[i] = f[2 * i + 1] - f[2 * i];
+            e[i] = f[2 * i] + wx * d[i];
+        }
+        const R y0 = e[1] - e[0], y1 = e[3] - e[2];
+        const R v0 = e[0] + wy * y0;
+        ddz = (e[2] + wy * y1) - v0;
+        val = v0 + wz * ddz;
+        if (grad) {
+            const R x0 = d[0] + wy * (d[1] - d[0]);
+            const R x1 = d[2] + wy * (d[3] - d[2]);
+            ddx = x0 + wz * (x1 - x0);
+            ddy = y0 + wz * (y1 - y0);
+        }
+        return;
+    }
     const R ax = (R)1 - wx, ay = (R)1 - wy, az = (R)1 - wz;
     const R v0 = (((ax * ay) * f[0] + (wx * ay) * f[1]) + (ax * wy) * f[2]) + (wx * wy) * f[3];
     const R v1 = (((ax * ay) * f[4] + (wx * ay) * f[5]) + (ax * wy) * f[6]) + (wx * wy) * f[7];
@@ -201,12 +222,15 @@ GCB_HD void gather3(const Acc& acc, const PushConst3& pc, const Consts3<R>& K, d
 // (b.grad)b = b_x d_x b + b_y d_y b + b_z d_z b, (v_E.grad)b likewise.
 
 template <typename R>
-GCB_HD uint32_t local_from_sample(const Sample3<R>& s, const Consts<R>& K, Local<R>& L) {
+GCB_HD uint32_t local_from_sample(const Sample3<R>& s, const Consts3<R>& K, Local<R>& L) {
     const uint32_t flags = local_fields(s.E, s.B, K, L);
-    R dbx[3], dby[3], dbz[3];
-    L.gB[0] = db_along(L, s.dBx, dbx);
-    L.gB[1] = db_along(L, s.dBy, dby);
-    L.gB[2] = db_along(L, s.dBz, dbz);
+    R gx[3], gy[3], gz[3], dbx[3], dby[3], dbz[3];
+    per_length(s.dBx, K.inv_dx, gx);
+    per_length(s.dBy, K.inv_dy, gy);
+    per_length(s.dBz, K.inv_dz, gz);
+    L.gB[0] = db_along(L, gx, dbx);
+    L.gB[1] = db_along(L, gy, dby);
+    L.gB[2] = db_along(L, gz, dbz);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         L.bgb[i] = (L.b[0] * dbx[i] + L.b[1] * dby[i]) + L.b[2] * dbz[i];
@@ -219,19 +243,25 @@ GCB_HD uint32_t local_from_sample(const Sample3<R>& s, const Consts<R>& K, Local
 // The exact frame with the curvature scheme in 3D: as the 2D
 // local_exact_curv, with d_j b* over j = x, y, z.
 template <typename R>
-GCB_HD uint32_t local_exact_curv(const SampleEG3<R>& s, const Consts<R>& K, Local<R>& L) {
+GCB_HD uint32_t local_exact_curv(const SampleEG3<R>& s, const Consts3<R>& K, Local<R>& L) {
     const uint32_t flags = local_fields_exact(s.E, s.B, K, L);
     Dual<R, 3> E[3], Bv[3], b[3];
+    R dE[3][3], dB[3][3];
+    per_length(s.dEx, K.inv_dx, dE[0]);
+    per_length(s.dEy, K.inv_dy, dE[1]);
+    per_length(s.dEz, K.inv_dz, dE[2]);
+    per_length(s.dBx, K.inv_dx, dB[0]);
+    per_length(s.dBy, K.inv_dy, dB[1]);
+    per_length(s.dBz, K.inv_dz, dB[2]);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         E[i].v = s.E[i];
-        E[i].d[0] = s.dEx[i];
-        E[i].d[1] = s.dEy[i];
-        E[i].d[2] = s.dEz[i];
         Bv[i].v = s.B[i];
-        Bv[i].d[0] = s.dBx[i];
-        Bv[i].d[1] = s.dBy[i];
-        Bv[i].d[2] = s.dBz[i];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            E[i].d[j] = dE[j][i];
+            Bv[i].d[j] = dB[j][i];
+        }
     }
     bstar_dual<R, 3>(E, Bv, K, b);
 #pragma unroll
@@ -244,11 +274,21 @@ GCB_HD uint32_t local_exact_curv(const SampleEG3<R>& s, const Consts<R>& K, Loca
     return flags;
 }
 
+// (V.grad)B at a 3D sample of the production form, V[j] in units of length
+template <typename R>
+GCB_HD void b_along(const Sample3<R>& s, const R V[3], const Consts3<R>& K, R g[3]) {
+    const R vx = V[0] * K.inv_dx, vy = V[1] * K.inv_dy;
+    const R vz = V[2] * K.inv_dz;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) g[i] = (vx * s.dBx[i] + vy * s.dBy[i]) + vz * s.dBz[i];
+}
+
 // u_par b / Gamma + v_E + v_c at a point, three components (v_c with the
 // grad-B drift under the mirror option)
-template <typename R>
-GCB_HD void drift_terms3(const Local<R>& L, R upn, const Gyr<R>& gy, R inv_qm, bool curvature,
-                         const Consts<R>& K, R F[3], bool mirror = false) {
+template <bool kDir = false, typename R>
+GCB_HD void drift_terms3(const Local<R>& L, const Sample3<R>& s, R upn, const Gyr<R>& gy,
+                         R inv_qm, bool curvature, const Consts3<R>& K, R F[3],
+                         bool mirror = false) {
     const Gam<R> G = gamma_gca2(L, upn, gy, K);
     const R a = over(upn, G);
     if (curvature) {
@@ -256,7 +296,7 @@ GCB_HD void drift_terms3(const Local<R>& L, R upn, const Gyr<R>& gy, R inv_qm, b
         if (mirror)
             v_curv_mirror<3>(L, upn, G.g, inv_qm, gy.mu, K, vc);
         else
-            v_curv_g(L, upn, G, inv_qm, K, vc);
+            v_curv_of<kDir>(L, s, upn, G, inv_qm, K, vc);
 #pragma unroll
         for (int i = 0; i < 3; ++i) F[i] = (a * L.b[i] + L.vE[i]) + vc[i];
     } else {
@@ -311,7 +351,13 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
     const double inv_box[3] = {pc.b.inv_Lx, pc.b.inv_Ly, pc.inv_Lz};
     const R ux = r.ux, uy = r.uy, uz = r.uz;
     const R qm = (R)r.qm;
-    const R inv_qm = (R)1 / qm;
+    // the production form of the reduced frame (see v_curv_dir)
+    constexpr bool kDir = kFastD<R> && !kExact && !kMirror;
+    R inv_qm;
+    if constexpr (kFastD<R>)
+        inv_qm = rcp_nr0(qm);
+    else
+        inv_qm = (R)1 / qm;
 
     // 1. guiding-center variables at R^{n-1/2} = (x^n + x^{n-1})/2
     R upar, bp[3];
@@ -324,12 +370,12 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
         Smp sh;
         gather3<R, true, kYee>(acc, pc, K, Rh[0], Rh[1], Rh[2], sh);
         Local<R> Lh;
-        flags |= local_in_frame<kExact, R>(sh, K, Lh);
+        flags |= local_of<kDir, kExact, R>(sh, K, Lh);
         upar = (ux * Lh.b[0] + uy * Lh.b[1]) + uz * Lh.b[2];
         const Gam<R> G = gamma_full2(ux, uy, uz, K);
         const R gf = G.g;
         R vc[3] = {(R)0, (R)0, (R)0};
-        if (curv) v_curv_g(Lh, upar, G, inv_qm, K, vc);
+        if (curv) v_curv_of<kDir>(Lh, sh, upar, G, inv_qm, K, vc);
         const R upx = (ux - upar * Lh.b[0]) - (Lh.vE[0] + vc[0]) * gf;
         const R upy = (uy - upar * Lh.b[1]) - (Lh.vE[1] + vc[1]) * gf;
         const R upz = (uz - upar * Lh.b[2]) - (Lh.vE[2] + vc[2]) * gf;
@@ -364,13 +410,16 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
             gather3<R, true, kYee>(acc, pc, K, x[0], x[1], x[2], se);
             flags |= local_in_frame<kExact, R>(se, K, Ln);
         } else {
-            flags |= local_in_frame<kExact, R>(sn, K, Ln);
+            flags |= local_of<kDir, kExact, R>(sn, K, Ln);
+            if constexpr (kDir) {
+                if (curv) curvature_scalars_dir(sn, K, Ln);
+            }
         }
         if (mirror)
             upn = mirror_parallel<3>(Ln, upar, gy, qm, K, flags);
         else
             upn = parallel_update(Ln, upar, gy, qm, curv, K, flags);
-        drift_terms3(Ln, upn, gy, inv_qm, curv, K, Fn, mirror);
+        drift_terms3<kDir>(Ln, sn, upn, gy, inv_qm, curv, K, Fn, mirror);
         if constexpr (kPhase) phase_advance(Ln, upar, upn, gy, qm, K, bp);
     }
 
@@ -387,8 +436,8 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
             Smp sk;
             gather3<R, true, kYee>(acc, pc, K, Rp[0], Rp[1], Rp[2], sk);
             Local<R> Lk;
-            flags |= local_in_frame<kExact, R>(sk, K, Lk);
-            drift_terms3(Lk, upn, gy, inv_qm, curv, K, Fk, mirror);
+            flags |= local_of<kDir, kExact, R>(sk, K, Lk);
+            drift_terms3<kDir>(Lk, sk, upn, gy, inv_qm, curv, K, Fk, mirror);
         }
         double d[3];
 #pragma unroll
@@ -410,12 +459,16 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
         Smp sm;
         gather3<R, true, kYee>(acc, pc, K, Rm[0], Rm[1], Rm[2], sm);
         Local<R> Lm;
-        flags |= local_in_frame<kExact, R>(sm, K, Lm);
+        flags |= local_of<kDir, kExact, R>(sm, K, Lm);
         const Gam<R> G = gamma_gca2(Lm, upn, gy, K);
         const R gr = G.g;
         R vc[3] = {(R)0, (R)0, (R)0};
-        if (curv) v_curv_g(Lm, upn, G, inv_qm, K, vc);
-        const R um = sqrt(uperp_sq(Lm, gy));
+        if (curv) v_curv_of<kDir>(Lm, sm, upn, G, inv_qm, K, vc);
+        R um;
+        if constexpr (kFastD<R>)
+            um = sqrt_nr(uperp_sq(Lm, gy));
+        else
+            um = sqrt(uperp_sq(Lm, gy));
         r.ux = (upn * Lm.b[0] + (Lm.vE[0] + vc[0]) * gr) + um * bp[0];
         r.uy = (upn * Lm.b[1] + (Lm.vE[1] + vc[1]) * gr) + um * bp[1];
         r.uz = (upn * Lm.b[2] + (Lm.vE[2] + vc[2]) * gr) + um * bp[2];
