@@ -154,16 +154,26 @@ struct TileAcc3 {
         const int o[3] = {oi, oj, ol};
         const int n[3] = {g.nx, g.ny, g.nz};
         int d[3][2];
+        // nearly every point lies at least one node inside the window: no
+        // periodic image to try, nothing else to check
         bool in = true;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            int da = fl[a][0] - o[a];
-            if (da < 0 || da > W - 2) da += (da < 0) ? n[a] : -n[a];
-            const int sa = fl[a][0] - fl[a][1];   // 0 or 1 for finite coordinates
-            d[a][0] = da;
-            d[a][1] = da - sa;
-            in = in && (unsigned)sa <= 1u && d[a][1] >= 0 && da <= W - 2;
+            d[a][0] = fl[a][0] - o[a];
+            in = in && (unsigned)(d[a][0] - 1) < (unsigned)(W - 2);
         }
+        if (__builtin_expect(!in, 0)) {
+            in = true;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                int& da = d[a][0];
+                if (da < 0 || da > W - 2) da += (da < 0) ? n[a] : -n[a];
+                const int sa = fl[a][0] - fl[a][1];   // 0 or 1 for finite coordinates
+                in = in && (unsigned)sa <= 1u && da - sa >= 0 && da <= W - 2;
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) d[a][1] = d[a][0] - (fl[a][0] - fl[a][1]);
         if (in) {
 #pragma unroll
             for (int s = 0; s < 8; ++s)

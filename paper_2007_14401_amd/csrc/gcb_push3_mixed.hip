@@ -3,7 +3,7 @@
 #include "gcb_push3_kernels.hpp"
 
 #ifndef GCB_TILED3_MIN_WAVES_MIXED
-#define GCB_TILED3_MIN_WAVES_MIXED 4
+#define GCB_TILED3_MIN_WAVES_MIXED 3
 #endif
 
 namespace gcb {

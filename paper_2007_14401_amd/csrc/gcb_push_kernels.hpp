@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kWG) void k_push_global(ParticlePtrs<R> in, Particl
 // One workgroup per tile of cell-sorted particles, for all `steps` steps of
 // a launch (the steps between two cell sorts, so the particle-to-tile
 // assignment of the last sort holds for all of them).  The tile's field
-// window (six W x W component planes) is staged in LDS once.  Its particles
+// window (W x W nodes of six components) is staged in LDS once.  Its particles
 // are taken in chunks of up to kTiledChunk: the switch is evaluated for each
 // at the launch's first step and the chunk is split into two queues
 // (guiding center first, Boris from the back).  The queues are cut into
@@ -238,12 +238,12 @@ k_push_tiled(ParticlePtrs<R> in_arg, ParticlePtrs<R> out_arg, const uint32_t* __
 
     // stage the window: a row of W records (6 W values, contiguous in the
     // node-interleaved array) per wave iteration, written to the six
-    // component planes; a lane's columns are the same in every row, so their
+    // LDS planes; a lane's columns are the same in every row, so their
     // offsets are formed once, and the loads of two rows are in flight
     // together (6 W <= 64 kCols: the host keeps W <= 64)
     {
         constexpr int kCols = 6;
-        int goff[kCols], loff[kCols];
+        int goff[kCols], loff[kCols], lrow[kCols];
 #pragma unroll
         for (int u = 0; u < kCols; ++u) {
             const int e = lane + 64 * u;
@@ -251,7 +251,8 @@ k_push_tiled(ParticlePtrs<R> in_arg, ParticlePtrs<R> out_arg, const uint32_t* __
             const int k = e - c * 6;
             const bool ok = e < W * 6;
             goff[u] = ok ? wrap_index(oi + c, pc.nx) * 6 + k : -1;
-            loff[u] = ok ? k * W * W + c : 0;
+            loff[u] = ok ? window_elem<T>(k, c, W * W) : 0;
+            lrow[u] = window_step<T>(k) * W;
         }
         constexpr int kRowStep = 2 * (kWG / 64);
         for (int rr = wave; rr < W; rr += kRowStep) {
@@ -268,8 +269,8 @@ k_push_tiled(ParticlePtrs<R> in_arg, ParticlePtrs<R> out_arg, const uint32_t* __
 #pragma unroll
             for (int u = 0; u < kCols; ++u) {
                 if (goff[u] >= 0) {
-                    lds[loff[u] + rr * W] = v0[u];
-                    if (two) lds[loff[u] + r2 * W] = v1[u];
+                    lds[loff[u] + rr * lrow[u]] = v0[u];
+                    if (two) lds[loff[u] + r2 * lrow[u]] = v1[u];
                 }
             }
         }
