@@ -220,4 +220,15 @@ struct TileAcc {
     }
 };
 
+// Whether a gather since the last reset fell outside the LDS window (never,
+// for a source without one).
+template <typename T>
+GCB_HD bool missed(const GlobalAcc<T>&) { return false; }
+template <typename T>
+GCB_HD bool missed(const TileAcc<T>& a) { return a.miss; }
+template <typename T>
+GCB_HD void set_missed(const GlobalAcc<T>&, bool) {}
+template <typename T>
+GCB_HD void set_missed(const TileAcc<T>& a, bool m) { a.miss = m; }
+
 }  // namespace gcb

@@ -186,4 +186,13 @@ struct TileAcc3 {
     }
 };
 
+template <typename T>
+GCB_HD bool missed(const GlobalAcc3<T>&) { return false; }
+template <typename T>
+GCB_HD bool missed(const TileAcc3<T>& a) { return a.miss; }
+template <typename T>
+GCB_HD void set_missed(const GlobalAcc3<T>&, bool) {}
+template <typename T>
+GCB_HD void set_missed(const TileAcc3<T>& a, bool m) { a.miss = m; }
+
 }  // namespace gcb

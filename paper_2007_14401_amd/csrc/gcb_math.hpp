@@ -1147,20 +1147,46 @@ GCB_HD double nan_max(double a, double b) {
     return a > b ? a : b;
 }
 
+// The end of a guiding-center step that the next step of the same particle
+// takes up: the sample and the local quantities at R^{n+1/2}, which is the
+// next step's R^{n-1/2} (the midpoint of the same two positions) whenever the
+// two come out as the same numbers -- always, but for a particle that crossed
+// the edge of the box.  The same numbers in, the same numbers out: the parity
+// arithmetic keeps its bits.  One gather and one set of local quantities in six
+// are left out.  Binary64 forms only: in the mixed one the compiler's choice of
+// fused operations, and so the side of fp_tol that a residual falls on, hangs
+// on where the values were computed.
+// Measured (16.8M particles, 4096^2, production arithmetic, 100 steps):
+// 11.66 -> 10.77 ms; 3D, 2M on 128^3, 9.11 -> 8.66 ms.
+template <typename R, class S>
+struct Midpoint {
+    S s;
+    Local<R> L;
+    double X[3];
+    bool have = false;
+    bool miss;   // its gather fell outside the LDS window
+
+    GCB_HD void drop() { have = false; }
+};
+
+template <class S>
+struct Midpoint<float, S> {
+    GCB_HD void drop() {}
+};
+
 // One guiding-center step.  sn is the gather (with gradients) at x^n.
 // Returns status flags; res receives |R^K - R^{K-1}|_inf.
 // kExact: the exact frame of Sec. 2.2 (with kExCurv its curvature scheme);
 // kMirror: the mirror force and grad-B drift (curvature scheme only);
 // kPhase: the gyration phase advanced over the step (GYR_PHASE).
 template <typename R, bool kYee, bool kExact = false, bool kMirror = false, bool kPhase = false,
-          bool kExCurv = false, class Acc>
-GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
-                                             const PushConst& pc, const Consts<R>& K,
-                                             double& res) {
+          bool kExCurv = false, class Acc, class Smp>
+GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r, const PushConst& pc,
+                         const Consts<R>& K, double& res, Midpoint<R, Smp>& mid) {
     // kExCurv: the exact frame with the curvature scheme, whose gathers carry
     // the E gradients
     static_assert(!kExCurv || kExact, "kExCurv is a form of the exact frame");
-    using Smp = std::conditional_t<kExCurv, SampleEG<R>, Sample<R>>;
+    static_assert(Smp::kGradE == kExCurv, "the samples of the step");
     uint32_t flags = 0;
     const bool curv = kExCurv || (!kExact && pc.curvature != 0);
     // the mirror terms ride on the curvature scheme (the host refuses others)
@@ -1183,9 +1209,18 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
         const double Rhx = x - 0.5 * min_image_i<R>(x - r.xp, pc.Lx, pc.inv_Lx);
         const double Rhy = y - 0.5 * min_image_i<R>(y - r.yp, pc.Ly, pc.inv_Ly);
         Smp sh;
-        gather<R, true, kYee>(acc, pc, K, Rhx, Rhy, sh);
         Local<R> Lh;
-        flags |= local_of<kDir, kExact, R>(sh, K, Lh);
+        if constexpr (kMixed<R>) {
+            gather<R, true, kYee>(acc, pc, K, Rhx, Rhy, sh);
+            flags |= local_of<kDir, kExact, R>(sh, K, Lh);
+        } else if (mid.have && Rhx == mid.X[0] && Rhy == mid.X[1]) {
+            sh = mid.s;
+            Lh = mid.L;
+            if (mid.miss) set_missed(acc, true);
+        } else {
+            gather<R, true, kYee>(acc, pc, K, Rhx, Rhy, sh);
+            flags |= local_of<kDir, kExact, R>(sh, K, Lh);
+        }
         upar = (ux * Lh.b[0] + uy * Lh.b[1]) + uz * Lh.b[2];
         const Gam<R> G = gamma_full2(ux, uy, uz, K);
         const R gf = G.g;
@@ -1274,9 +1309,23 @@ GCB_HD uint32_t gca_step(const Acc& acc, const Sample<R>& sn, Regs<R>& r,
         const double Rmx = x + 0.5 * (Rx - x);
         const double Rmy = y + 0.5 * (Ry - y);
         Smp sm;
+        bool before;
+        if constexpr (!kMixed<R>) {
+            before = missed(acc);
+            set_missed(acc, false);
+        }
         gather<R, true, kYee>(acc, pc, K, Rmx, Rmy, sm);
         Local<R> Lm;
         flags |= local_of<kDir, kExact, R>(sm, K, Lm);
+        if constexpr (!kMixed<R>) {
+            mid.s = sm;
+            mid.L = Lm;
+            mid.X[0] = Rmx;
+            mid.X[1] = Rmy;
+            mid.have = true;
+            mid.miss = missed(acc);
+            if (before) set_missed(acc, true);
+        }
         const Gam<R> G = gamma_gca2(Lm, upn, gy, K);
         const R gr = G.g;
         R vc[3] = {(R)0, (R)0, (R)0};

@@ -336,11 +336,12 @@ GCB_HD void boris_step3(const Sample3<R>& s, Regs3<R>& r, const PushConst3& pc,
 // whose gathers carry the E gradients);
 // kMirror: the mirror force and grad-B drift (curvature scheme only).
 template <typename R, bool kYee, bool kExact = false, bool kMirror = false, bool kPhase = false,
-          bool kExCurv = false, class Acc>
+          bool kExCurv = false, class Acc, class Smp>
 GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
-                          const PushConst3& pc, const Consts3<R>& K, double& res) {
+                          const PushConst3& pc, const Consts3<R>& K, double& res,
+                          Midpoint<R, Smp>& mid) {
     static_assert(!kExCurv || kExact, "kExCurv is a form of the exact frame");
-    using Smp = std::conditional_t<kExCurv, SampleEG3<R>, Sample3<R>>;
+    static_assert(Smp::kGradE == kExCurv, "the samples of the step");
     uint32_t flags = 0;
     const bool curv = kExCurv || (!kExact && pc.b.curvature != 0);
     // the mirror terms ride on the curvature scheme (the host refuses others)
@@ -368,9 +369,19 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
         for (int a = 0; a < 3; ++a)
             Rh[a] = x[a] - 0.5 * min_image_i<R>(x[a] - xprev[a], box[a], inv_box[a]);
         Smp sh;
-        gather3<R, true, kYee>(acc, pc, K, Rh[0], Rh[1], Rh[2], sh);
         Local<R> Lh;
-        flags |= local_of<kDir, kExact, R>(sh, K, Lh);
+        if constexpr (kMixed<R>) {
+            gather3<R, true, kYee>(acc, pc, K, Rh[0], Rh[1], Rh[2], sh);
+            flags |= local_of<kDir, kExact, R>(sh, K, Lh);
+        } else if (mid.have && Rh[0] == mid.X[0] && Rh[1] == mid.X[1] &&
+                                      Rh[2] == mid.X[2]) {
+            sh = mid.s;
+            Lh = mid.L;
+            if (mid.miss) set_missed(acc, true);
+        } else {
+            gather3<R, true, kYee>(acc, pc, K, Rh[0], Rh[1], Rh[2], sh);
+            flags |= local_of<kDir, kExact, R>(sh, K, Lh);
+        }
         upar = (ux * Lh.b[0] + uy * Lh.b[1]) + uz * Lh.b[2];
         const Gam<R> G = gamma_full2(ux, uy, uz, K);
         const R gf = G.g;
@@ -457,9 +468,24 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
 #pragma unroll
         for (int a = 0; a < 3; ++a) Rm[a] = x[a] + 0.5 * (Rp[a] - x[a]);
         Smp sm;
+        bool before;
+        if constexpr (!kMixed<R>) {
+            before = missed(acc);
+            set_missed(acc, false);
+        }
         gather3<R, true, kYee>(acc, pc, K, Rm[0], Rm[1], Rm[2], sm);
         Local<R> Lm;
         flags |= local_of<kDir, kExact, R>(sm, K, Lm);
+        if constexpr (!kMixed<R>) {
+            mid.s = sm;
+            mid.L = Lm;
+            mid.X[0] = Rm[0];
+            mid.X[1] = Rm[1];
+            mid.X[2] = Rm[2];
+            mid.have = true;
+            mid.miss = missed(acc);
+            if (before) set_missed(acc, true);
+        }
         const Gam<R> G = gamma_gca2(Lm, upn, gy, K);
         const R gr = G.g;
         R vc[3] = {(R)0, (R)0, (R)0};

@@ -79,10 +79,16 @@ __device__ __forceinline__ void record_state3(double* rec, int64_t n, int64_t i,
     rec[8 * n + i] = (double)r.uz;
 }
 
+// what a guiding-center step leaves for the next one, per variant
+template <typename R, int kVar>
+using MidpointOf3 =
+    Midpoint<R, std::conditional_t<kVar == kVarExactCurv, SampleEG3<R>, Sample3<R>>>;
+
 template <typename R, bool kYee, int kVar, class Acc>
 __device__ __forceinline__ uint32_t coupled_update3(const Acc& acc, bool gca, Regs3<R>& r,
                                                     const PushConst3& pc, const Consts3<R>& K,
-                                                    double& res) {
+                                                    double& res,
+                                                    MidpointOf3<R, kVar>& mid) {
     uint32_t fl = 0;
     res = 0.0;
     Sample3<R> s;
@@ -90,8 +96,9 @@ __device__ __forceinline__ uint32_t coupled_update3(const Acc& acc, bool gca, Re
         gather3<R, true, kYee>(acc, pc, K, r.x, r.y, r.z, s);
         fl = gca_step3<R, kYee, var_exact(kVar), kVar == kVarMirror, kVar == kVarPhase,
                        kVar == kVarExactCurv>(
-            acc, s, r, pc, K, res);
+            acc, s, r, pc, K, res, mid);
     } else {
+        mid.drop();
         gather3<R, false, kYee>(acc, pc, K, r.x, r.y, r.z, s);
         boris_step3(s, r, pc, K);
     }
@@ -117,6 +124,7 @@ __global__ __launch_bounds__(kWG) void k_push3_global(ParticlePtrs3<R> in,
         load_particle3(in, src, pc.b.qm, r);
         const int64_t ti = in.b.id ? (int64_t)in.b.id[src] : p;
         uint32_t fl = 0;
+        MidpointOf3<R, kVar> mid;
         for (int s = 0; s < ns; ++s) {
             uint8_t* tr = trace ? trace + (size_t)s * n : nullptr;
             bool gca;
@@ -128,7 +136,7 @@ __global__ __launch_bounds__(kWG) void k_push3_global(ParticlePtrs3<R> in,
                 gca = switch_gca(smp.E, smp.B, r.ux, r.uy, r.uz, r.qm, pc.b, K);
             }
             double res;
-            fl |= coupled_update3<R, kYee, kVar>(acc, gca, r, pc, K, res);
+            fl |= coupled_update3<R, kYee, kVar>(acc, gca, r, pc, K, res, mid);
             if (tr && !replay) tr[ti] = gca ? 0 : 1;
             if (gca) {
                 ++cnt_g;
@@ -233,15 +241,17 @@ k_push3_tiled(ParticlePtrs3<R> in_arg, ParticlePtrs3<R> out_arg,
             load_particle3(in, src, pc.b.qm, r);
             uint32_t fl = 0;
             bool gca = q < nG;
+            MidpointOf3<R, kVar> mid;
             for (int st = 0; st < steps; ++st) {
                 uint8_t* tr = trace ? trace + (int64_t)st * n : nullptr;
                 if constexpr (kRec) record_state3(in.b.rec + (int64_t)st * 9 * n, n, tid, r);
                 // the gather at x^n serves the switch and the update; the
                 // gradients are formed for the branch of the previous step
+                // (in binary64 always: no second gather where it changes)
                 const bool prev = gca;
                 Sample3<R> smp;
                 acc.miss = false;
-                if (prev)
+                if (!kMixed<R> || prev)
                     gather3<R, true, kYee>(acc, pc, K, r.x, r.y, r.z, smp);
                 else
                     gather3<R, false, kYee>(acc, pc, K, r.x, r.y, r.z, smp);
@@ -250,15 +260,18 @@ k_push3_tiled(ParticlePtrs3<R> in_arg, ParticlePtrs3<R> out_arg,
                         gca = tr[tid] == 0;
                     else
                         gca = switch_gca(smp.E, smp.B, r.ux, r.uy, r.uz, r.qm, pc.b, K);
-                    if (gca && !prev) gather3<R, true, kYee>(acc, pc, K, r.x, r.y, r.z, smp);
+                    if (kMixed<R> && gca && !prev) gather3<R, true, kYee>(acc, pc, K, r.x, r.y, r.z, smp);
                 }
                 double res = 0.0;
                 if (gca)
                     fl |= gca_step3<R, kYee, var_exact(kVar), kVar == kVarMirror,
                                     kVar == kVarPhase, kVar == kVarExactCurv>(acc, smp, r, pc,
-                                                                              K, res);
+                                                                              K, res, mid);
                 else
                     boris_step3(smp, r, pc, K);
+                if constexpr (!kMixed<R>) {
+                    if (!gca) mid.drop();
+                }
                 fl |= finite_flag3(r);
                 if (acc.miss) {
                     fl |= ST_HALO;

@@ -113,21 +113,28 @@ __device__ __forceinline__ void store_particle(const ParticlePtrs<R>& in,
     }
 }
 
+// what a guiding-center step leaves for the next one, per variant
+template <typename R, int kVar>
+using MidpointOf =
+    Midpoint<R, std::conditional_t<kVar == kVarExactCurv, SampleEG<R>, Sample<R>>>;
+
 // one coupled step for a particle already in registers (kVar: the
 // guiding-center branch in the paper's reduced frame, in the exact frame of
 // Sec. 2.2, or with the mirror terms)
 template <typename R, bool kYee, int kVar, class Acc>
 __device__ __forceinline__ uint32_t coupled_update(const Acc& acc, bool gca, Regs<R>& r,
                                                    const PushConst& pc, const Consts<R>& K,
-                                                   double& res) {
+                                                   double& res,
+                                                   MidpointOf<R, kVar>& mid) {
     uint32_t fl = 0;
     res = 0.0;
     if (gca) {
         Sample<R> s;
         gather<R, true, kYee>(acc, pc, K, r.x, r.y, s);
         fl = gca_step<R, kYee, var_exact(kVar), kVar == kVarMirror, kVar == kVarPhase,
-                      kVar == kVarExactCurv>(acc, s, r, pc, K, res);
+                      kVar == kVarExactCurv>(acc, s, r, pc, K, res, mid);
     } else {
+        mid.drop();
         Sample<R> s;
         gather<R, false, kYee>(acc, pc, K, r.x, r.y, s);
         boris_step(s, r, pc, K);
@@ -155,6 +162,7 @@ __global__ __launch_bounds__(kWG) void k_push_global(ParticlePtrs<R> in, Particl
         load_particle(in, src, pc.qm, r);
         const int64_t ti = in.id ? (int64_t)in.id[src] : p;
         uint32_t fl = 0;
+        MidpointOf<R, kVar> mid;
         for (int s = 0; s < ns; ++s) {
             uint8_t* tr = trace ? trace + (size_t)s * n : nullptr;
             if constexpr (kRec) record_state(in.rec + (int64_t)s * 7 * n, n, ti, r);
@@ -167,7 +175,7 @@ __global__ __launch_bounds__(kWG) void k_push_global(ParticlePtrs<R> in, Particl
                 gca = switch_gca(smp.E, smp.B, r.ux, r.uy, r.uz, r.qm, pc, K);
             }
             double res;
-            fl |= coupled_update<R, kYee, kVar>(acc, gca, r, pc, K, res);
+            fl |= coupled_update<R, kYee, kVar>(acc, gca, r, pc, K, res, mid);
             if (tr && !replay) tr[ti] = gca ? 0 : 1;
             if (gca) {
                 ++cnt_g;
@@ -319,15 +327,17 @@ k_push_tiled(ParticlePtrs<R> in_arg, ParticlePtrs<R> out_arg, const uint32_t* __
             load_particle(in, src, pc.qm, r);
             uint32_t fl = 0;
             bool gca = gslice;
+            MidpointOf<R, kVar> mid;
             for (int s = 0; s < steps; ++s) {
                 uint8_t* tr = trace ? trace + (int64_t)s * n : nullptr;
                 if constexpr (kRec) record_state(in.rec + (int64_t)s * 7 * n, n, tid, r);
                 // the gather at x^n serves the switch and the update; the
                 // gradients are formed for the branch of the previous step
+                // (in binary64 always: no second gather where it changes)
                 const bool prev = gca;
                 Sample<R> smp;
                 acc.miss = false;
-                if (prev)
+                if (!kMixed<R> || prev)
                     gather<R, true, kYee>(acc, pc, K, r.x, r.y, smp);
                 else
                     gather<R, false, kYee>(acc, pc, K, r.x, r.y, smp);
@@ -336,15 +346,18 @@ k_push_tiled(ParticlePtrs<R> in_arg, ParticlePtrs<R> out_arg, const uint32_t* __
                         gca = tr[tid] == 0;
                     else
                         gca = switch_gca(smp.E, smp.B, r.ux, r.uy, r.uz, r.qm, pc, K);
-                    if (gca && !prev) gather<R, true, kYee>(acc, pc, K, r.x, r.y, smp);
+                    if (kMixed<R> && gca && !prev) gather<R, true, kYee>(acc, pc, K, r.x, r.y, smp);
                 }
                 double res = 0.0;
                 if (gca)
                     fl |= gca_step<R, kYee, var_exact(kVar), kVar == kVarMirror,
                                    kVar == kVarPhase, kVar == kVarExactCurv>(acc, smp, r, pc,
-                                                                             K, res);
+                                                                             K, res, mid);
                 else
                     boris_step(smp, r, pc, K);
+                if constexpr (!kMixed<R>) {
+                    if (!gca) mid.drop();
+                }
                 fl |= finite_flag(r);
                 if (acc.miss) {
                     fl |= ST_HALO;
