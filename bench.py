@@ -357,7 +357,7 @@ def main():
                     "backward_ms_per_step": ms[gcb.GCB_TIMER_BACKWARD] / max(1, steps),
                     "sort_every": a.adjoint_sort_every, "tile": a.tile,
                     "kernel": "k_push_tiled in place (keep_order, parity binary64) + "
-                              "k_adjoint_step + k_scatter_batch",
+                              "k_adjoint_batch",
                     "loss": float(L.detach())}
         finally:
             pctx.close()
@@ -412,7 +412,7 @@ def main():
                     "backward_ms_per_step": ms[gcb.GCB_TIMER_BACKWARD] / max(1, steps),
                     "sort_every": a.d3_sort_every, "tile": a.d3_tile,
                     "kernel": "k_push3_tiled in place (keep_order, parity binary64) + "
-                              "k_adjoint3_step + k_scatter3_batch",
+                              "k_adjoint_batch",
                     "loss": float(L)}
         finally:
             pctx.close()

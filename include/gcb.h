@@ -302,9 +302,7 @@ int gcb_push_noalloc(gcb_ctx* ctx, gcb_particles* p, const gcb_params* prm,
    no result depends on the order).  The forward steps are recomputed
    internally: with params.sort_every > 0 by the tiled push in place
    (keep_order), else by the cache-served kernel; needs n_steps * n * 61 +
-   n * 12 bytes of context scratch plus the gather-point records of up to 32
-   steps (64 bytes per gather point, at most 128 GiB and half the device
-   memory free at the call). */
+   n * 12 bytes of context scratch beside the cell sort's. */
 int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start,
                       const gcb_params* prm, int32_t n_steps,
                       const double* const lam_end[7], double* const lam_start[7],
@@ -461,8 +459,7 @@ int gcb_push_3d(gcb_ctx* ctx, gcb_particles3* p, const gcb_params* prm,
    are recomputed internally: with params.sort_every > 0 and a tile window
    that fits in LDS by the tiled push in place (keep_order), else by the
    cache-served kernel; needs n_steps * n * 77 + n * 12 bytes of context
-   scratch plus the gather-point records of up to 8 steps (84 bytes per
-   gather point, at most 32 GiB and half the device memory free). */
+   scratch beside the cell sort's. */
 int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_params* prm,
                          int32_t n_steps, const double* const lam_end[9],
                          double* const lam_start[9], float* const dE[3], float* const dB[3],

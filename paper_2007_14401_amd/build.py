@@ -35,8 +35,8 @@ UNITS = {
     "gcb_host.hip": ["-ffp-contract=off"],
     "gcb_push_f64.hip": ["-ffp-contract=off"],
     "gcb_push_f64_fast.hip": ["-ffp-contract=fast"],
-    "gcb_adjoint.hip": ["-ffp-contract=off"],
-    "gcb_adjoint3.hip": ["-ffp-contract=off"],
+    "gcb_adjoint.hip": ["-ffp-contract=fast"],
+    "gcb_adjoint3.hip": ["-ffp-contract=fast"],
     "gcb_push_mixed.hip": FAST_F32,
     "gcb_sort.hip": ["-ffp-contract=off"],
     "gcb_util.hip": ["-ffp-contract=off"],

@@ -1,231 +1,433 @@
 // Reverse-mode derivative (vector-Jacobian products) of one binary64 step of
-// the coupled pusher, with the switch decision held at its forward value.
+// the coupled pusher in D = 2 or 3 dimensions, with the switch decision held at
+// its forward value.
 //
-// Every building block of the forward step in gcb_math.hpp has a hand-written
-// adjoint here; a block's adjoint recomputes the forward values it needs from
-// its inputs.  Cotangents are accumulated (+=) into the *Bar structures.
-//   gather_vjp       linear shape function: the position cotangent,
-//                    including the mixed second derivative of W carried by
-//                    the B-gradient cotangents; the gather point and its
-//                    cotangents go to a sink
-//   scatter_sample   node cotangents of one recorded gather point
-//   local_vjp        b, v_E, kappa, E_par, d_j b_i, (b.grad)b, (v_E.grad)b
-//   gamma_vjp        Gamma(R, u_par) (eq. lfacgca2)
-//   vcurv_vjp        curvature drift (eq. curvdrift)
-//   drift_vjp        u_par b/Gamma + v_E + v_c
-//   parallel_vjp     the parallel update (Sec. 2.2.2) through the root of the
+// The forward values come from the production arithmetic of gcb_math.hpp (the
+// states and decisions they are evaluated at are the forward pass's own).
+// Every building block has a hand-written adjoint, and a block's adjoint takes
+// the forward values it needs from its inputs.  Cotangents are accumulated (+=).
+//   sample_at        the six components at a point with all first derivatives
+//                    and the mixed second ones of B (everything the reverse
+//                    sweep needs of the fields, from one gather)
+//   point_back       cotangents of E, B and of the B gradients -> node
+//                    cotangents (to a window, see gcb_adjoint_kernels.hpp) and
+//                    the position cotangent, including the mixed second
+//                    derivatives of W carried by the gradient cotangents
+//   local_back       b, v_E, kappa, E_par
+//   gamma_back       Gamma(R, u_par) (eq. lfacgca2) and 1/Gamma
+//   vcurv_back       curvature drift (eq. curvdrift)
+//   scalars_back     A = v_E.(b.grad)b, C = v_E.(v_E.grad)b
+//   drift_back       u_par b/Gamma + v_E + v_c
+//   parallel_back    the parallel update (Sec. 2.2.2) through the root of the
 //                    quadratic by the implicit-function derivative
 //                    dG = -(G^2 dk1 + G dk2 + dk3)/(2 k1 G + k2)
-//   boris_step_vjp   relativistic Boris push and position update
-//   gca_step_vjp     the guiding-center step (Sec. 3.1): decomposition,
+//   boris_vjp        relativistic Boris push and position update
+//   gca_vjp          the guiding-center step (Sec. 3.1): decomposition,
 //                    parallel update, K fixed-point iterations (reversed in
 //                    order), reconstruction
+// State order: positions, previous positions, u (2 D + 3 values).
 #pragma once
 
-#include "gcb_math.hpp"
+#include "gcb_math3.hpp"
 
 namespace gcb {
 namespace adj {
 
-using SampleD = Sample<double>;
 using LocalD = Local<double>;
-using KD = Consts<double>;
 
-struct SampleBar {
-    double E[3], B[3], dBx[3], dBy[3];
+// what differs between two and three dimensions
+template <int D>
+struct Dim;
+
+template <>
+struct Dim<2> {
+    using Push = PushConst;
+    using Const = Consts<double>;
+    using Acc = TileAcc<double>;
+    using Smp = Sample<double>;
+    GCB_HD static const PushConst& base(const Push& pc) { return pc; }
+    GCB_HD static Const consts(const Push& pc) { return make_consts<double>(pc); }
+    GCB_HD static Acc acc(const double* lds, const double* F, const Push& pc, const int o[2],
+                          int W) {
+        return Acc{lds, F, pc.nx, pc.ny, o[0], o[1], W, false};
+    }
+    GCB_HD static double inv_d(const Push& pc, int a) { return a == 0 ? pc.inv_dx : pc.inv_dy; }
+    GCB_HD static double box(const Push& pc, int a) { return a == 0 ? pc.Lx : pc.Ly; }
+    GCB_HD static double inv_box(const Push& pc, int a) {
+        return a == 0 ? pc.inv_Lx : pc.inv_Ly;
+    }
+    GCB_HD static int nodes(const Push& pc, int a) { return a == 0 ? pc.nx : pc.ny; }
+    GCB_HD static double stagger(const Push& pc, int k, int a) { return pc.stagger[k][a]; }
+    GCB_HD static constexpr int set(int k) { return kYeeSet[k]; }
+    template <bool kYee>
+    GCB_HD static void gather(const Acc& acc, const Push& pc, const Const& K, const double X[2],
+                              Smp& s) {
+        gcb::gather<double, true, kYee>(acc, pc, K, X[0], X[1], s);
+    }
+    // gradient of the sample along axis a (per cell)
+    GCB_HD static const double* grad(const Smp& s, int a) { return a == 0 ? s.dBx : s.dBy; }
 };
 
-struct LocalBar {
-    double B, inv_B, b[3], vE[3], kappa, Epar, bgb[3], vgb[3], A, C;
+template <>
+struct Dim<3> {
+    using Push = PushConst3;
+    using Const = Consts3<double>;
+    using Acc = TileAcc3<double>;
+    using Smp = Sample3<double>;
+    GCB_HD static const PushConst& base(const Push& pc) { return pc.b; }
+    GCB_HD static Const consts(const Push& pc) { return make_consts3<double>(pc); }
+    GCB_HD static Acc acc(const double* lds, const double* F, const Push& pc, const int o[3],
+                          int W) {
+        return Acc{lds, GlobalAcc3<double>{F, pc.b.nx, pc.b.ny, pc.nz}, o[0], o[1], o[2], W,
+                   false};
+    }
+    GCB_HD static double inv_d(const Push& pc, int a) {
+        return a == 0 ? pc.b.inv_dx : a == 1 ? pc.b.inv_dy : pc.inv_dz;
+    }
+    GCB_HD static double box(const Push& pc, int a) {
+        return a == 0 ? pc.b.Lx : a == 1 ? pc.b.Ly : pc.Lz;
+    }
+    GCB_HD static double inv_box(const Push& pc, int a) {
+        return a == 0 ? pc.b.inv_Lx : a == 1 ? pc.b.inv_Ly : pc.inv_Lz;
+    }
+    GCB_HD static int nodes(const Push& pc, int a) {
+        return a == 0 ? pc.b.nx : a == 1 ? pc.b.ny : pc.nz;
+    }
+    GCB_HD static double stagger(const Push& pc, int k, int a) {
+        return a < 2 ? pc.b.stagger[k][a] : pc.sz[k];
+    }
+    GCB_HD static constexpr int set(int k) { return kYee3Set[k]; }
+    template <bool kYee>
+    GCB_HD static void gather(const Acc& acc, const Push& pc, const Const& K, const double X[3],
+                              Smp& s) {
+        gcb::gather3<double, true, kYee>(acc, pc, K, X[0], X[1], X[2], s);
+    }
+    GCB_HD static const double* grad(const Smp& s, int a) {
+        return a == 0 ? s.dBx : a == 1 ? s.dBy : s.dBz;
+    }
 };
-
-GCB_HD void zero(SampleBar& s) {
-    for (int i = 0; i < 3; ++i) s.E[i] = s.B[i] = s.dBx[i] = s.dBy[i] = 0.0;
-}
-
-GCB_HD void zero(LocalBar& l) {
-    l.B = l.inv_B = l.kappa = l.Epar = l.A = l.C = 0.0;
-    for (int i = 0; i < 3; ++i) l.b[i] = l.vE[i] = l.bgb[i] = l.vgb[i] = 0.0;
-}
-
-// cotangent of a x b: a_bar += b x z_bar, b_bar += z_bar x a
-GCB_HD void cross_vjp(const double a[3], const double b[3], const double zb[3], double ab[3],
-                      double bb[3]) {
-    ab[0] += b[1] * zb[2] - b[2] * zb[1];
-    ab[1] += b[2] * zb[0] - b[0] * zb[2];
-    ab[2] += b[0] * zb[1] - b[1] * zb[0];
-    bb[0] += zb[1] * a[2] - zb[2] * a[1];
-    bb[1] += zb[2] * a[0] - zb[0] * a[2];
-    bb[2] += zb[0] * a[1] - zb[1] * a[0];
-}
 
 // ---------------------------------------------------------------------------
 // gather
 
-// Node cotangents of one gather point: the cotangents of the six interpolated
-// components and of the B gradients at (X, Y) spread over the four nodes of
-// each component's cell, `add(k, i, j, g)` with global node indices (any
-// periodic image).
-template <class Add>
-GCB_HD void scatter_sample(Add& add, const PushConst& pc, bool yee, double X, double Y,
-                           const SampleBar& sb) {
-    const double gx = X * pc.inv_dx;
-    const double gy = Y * pc.inv_dy;
-    const double idx = pc.inv_dx, idy = pc.inv_dy;
-    // a runaway point's sample is a constant NaN: no node cotangent
-    if (!(fabs(gx) < kFarLattice && fabs(gy) < kFarLattice)) return;
-    for (int k = 0; k < 6; ++k) {
-        const double sx = yee ? kYeeStagger[k][0] : pc.stagger[k][0];
-        const double sy = yee ? kYeeStagger[k][1] : pc.stagger[k][1];
-        const double vb = k < 3 ? sb.E[k] : sb.B[k - 3];
-        const double dxb = k < 3 ? 0.0 : sb.dBx[k - 3];
-        const double dyb = k < 3 ? 0.0 : sb.dBy[k - 3];
-        if (vb == 0.0 && dxb == 0.0 && dyb == 0.0) continue;
-        const double xi = gx - sx, eta = gy - sy;
-        const double fi = floor(xi), fj = floor(eta);
-        const double wx = xi - fi, wy = eta - fj;
-        const int i = (int)fi, j = (int)fj;
-        const double ax = 1.0 - wx, ay = 1.0 - wy;
-        add(k, i, j, vb * (ax * ay) - dxb * (ay * idx) - dyb * (ax * idy));
-        add(k, i + 1, j, vb * (wx * ay) + dxb * (ay * idx) - dyb * (wx * idy));
-        add(k, i, j + 1, vb * (ax * wy) - dxb * (wy * idx) + dyb * (ax * idy));
-        add(k, i + 1, j + 1, vb * (wx * wy) + dxb * (wy * idx) + dyb * (wx * idy));
+// A gather point of the reverse sweep: the values, their derivatives along each
+// axis (per cell), the mixed second derivatives of B, the weights per axis (on
+// the Yee lattice one per offset 0 or 1/2, else one per component) and the
+// nodes (0, 0(, 0)) of the six stencils in the window, if all lie inside.
+template <int D, bool kYee>
+struct Point {
+    static constexpr int kSets = kYee ? 2 : 6;
+    double v[6];
+    double d[D][6];
+    double m[D * (D - 1) / 2][3];   // xy (xz, yz) of B
+    double w[D][kSets];
+    int off[6];
+    bool in;
+    bool far;   // a runaway point: its sample is a constant NaN
+
+    // the entry of component k along axis a
+    GCB_HD static constexpr int entry(int k, int a) {
+        return kYee ? (Dim<D>::set(k) >> a) & 1 : k;
+    }
+};
+
+template <bool kYee>
+GCB_HD void eval_point(int k, double f00, double f10, double f01, double f11,
+                       Point<2, kYee>& p) {
+    const double wx = p.w[0][p.entry(k, 0)], wy = p.w[1][p.entry(k, 1)];
+    double c[4];
+    cell_coefs(f00, f10, f01, f11, c);
+    eval_coefs<true>(c, wx, wy, p.v[k], p.d[0][k], p.d[1][k]);
+    if (k >= 3) p.m[0][k - 3] = c[3];
+}
+
+template <bool kYee>
+GCB_HD void eval_point(int k, const double f[8], Point<3, kYee>& p) {
+    const double wx = p.w[0][p.entry(k, 0)], wy = p.w[1][p.entry(k, 1)],
+                 wz = p.w[2][p.entry(k, 2)];
+    double d[4], e[4];   // along x at (y, z) = (0,0), (1,0), (0,1), (1,1)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        d[i] = f[2 * i + 1] - f[2 * i];
+        e[i] = f[2 * i] + wx * d[i];
+    }
+    const double y0 = e[1] - e[0], y1 = e[3] - e[2];
+    const double v0 = e[0] + wy * y0;
+    const double dz = (e[2] + wy * y1) - v0;
+    const double q0 = d[1] - d[0], q1 = d[3] - d[2];
+    const double x0 = d[0] + wy * q0, x1 = d[2] + wy * q1;
+    p.v[k] = v0 + wz * dz;
+    p.d[0][k] = x0 + wz * (x1 - x0);
+    p.d[1][k] = y0 + wz * (y1 - y0);
+    p.d[2][k] = dz;
+    if (k >= 3) {
+        p.m[0][k - 3] = q0 + wz * (q1 - q0);
+        p.m[1][k - 3] = x1 - x0;
+        p.m[2][k - 3] = y1 - y0;
     }
 }
 
-// Cotangent of the gather at (X, Y): the position cotangent, including the
-// mixed second derivative of W carried by the B-gradient cotangents, is added
-// to (Xb, Yb); the gather point and its cotangents go to `sink.sample`, which
-// owns the node cotangents (scatter_sample spreads them).
-template <class Acc, class Sink>
-GCB_HD void gather_vjp(const Acc& acc, Sink& sink, const PushConst& pc, bool yee, double X,
-                       double Y, const SampleBar& sb, double& Xb, double& Yb) {
-    sink.sample(X, Y, sb);
-    const double gx = X * pc.inv_dx;
-    const double gy = Y * pc.inv_dy;
-    const double idx = pc.inv_dx, idy = pc.inv_dy;
-    // a runaway point's sample is a constant NaN: it does not depend on (X, Y)
-    if (!(fabs(gx) < kFarLattice && fabs(gy) < kFarLattice)) return;
+// cells c and weights of the point X
+template <int D, bool kYee>
+GCB_HD void place(const typename Dim<D>::Push& pc, const double X[D],
+                  int c[D][Point<D, kYee>::kSets], Point<D, kYee>& p) {
+    double g[D];
+    p.far = false;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        g[a] = X[a] * Dim<D>::inv_d(pc, a);
+        p.far = p.far || !(fabs(g[a]) < kFarLattice);
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        const double ga = p.far ? 0.0 : g[a];
+#pragma unroll
+        for (int s = 0; s < Point<D, kYee>::kSets; ++s) {
+            const double xi = ga - (kYee ? 0.5 * s : Dim<D>::stagger(pc, s, a));
+            const double f = floor(xi);
+            c[a][s] = (int)f;
+            p.w[a][s] = xi - f;
+        }
+    }
+}
+
+// the stencil offsets in the window (or its periodic images) of cells c
+template <int D, bool kYee>
+GCB_HD void locate(const typename Dim<D>::Push& pc, const int o[D], int W,
+                   const int c[D][Point<D, kYee>::kSets], Point<D, kYee>& p) {
+    int d[D][Point<D, kYee>::kSets];
+    p.in = true;
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+#pragma unroll
+        for (int s = 0; s < Point<D, kYee>::kSets; ++s) {
+            int i = c[a][s] - o[a];
+            if ((unsigned)i > (unsigned)(W - 2)) i += i < 0 ? Dim<D>::nodes(pc, a)
+                                                            : -Dim<D>::nodes(pc, a);
+            p.in = p.in && (unsigned)i <= (unsigned)(W - 2);
+            d[a][s] = i;
+        }
+#pragma unroll
     for (int k = 0; k < 6; ++k) {
-        const double sx = yee ? kYeeStagger[k][0] : pc.stagger[k][0];
-        const double sy = yee ? kYeeStagger[k][1] : pc.stagger[k][1];
-        const double vb = k < 3 ? sb.E[k] : sb.B[k - 3];
-        const double dxb = k < 3 ? 0.0 : sb.dBx[k - 3];
-        const double dyb = k < 3 ? 0.0 : sb.dBy[k - 3];
-        if (vb == 0.0 && dxb == 0.0 && dyb == 0.0) continue;
-        const double xi = gx - sx, eta = gy - sy;
-        const double fi = floor(xi), fj = floor(eta);
-        const double wx = xi - fi, wy = eta - fj;
-        const int i = (int)fi, j = (int)fj;
-        double f00, f10, f01, f11;
-        acc.quad(k, i, j, f00, f10, f01, f11);
-        const double ax = 1.0 - wx, ay = 1.0 - wy;
-        const double cross = (((f11 - f01) - f10) + f00) * (idx * idy);
-        Xb += vb * ((ay * (f10 - f00) + wy * (f11 - f01)) * idx) + dyb * cross;
-        Yb += vb * ((ax * (f01 - f00) + wx * (f11 - f10)) * idy) + dxb * cross;
+        int e = 0;
+#pragma unroll
+        for (int a = D - 1; a >= 0; --a) e = e * W + d[a][p.entry(k, a)];
+        p.off[k] = e;
+    }
+}
+
+template <bool kYee>
+GCB_HD void sample_at(const TileAcc<double>& acc, const PushConst& pc, const double X[2],
+                      Point<2, kYee>& p) {
+    int c[2][Point<2, kYee>::kSets];
+    place<2>(pc, X, c, p);
+    const int o[2] = {acc.oi, acc.oj}, W = acc.W;
+    locate<2>(pc, o, W, c, p);
+    if (__builtin_expect(p.in, 1)) {
+        const int set[4] = {p.off[2], p.off[0], p.off[1], p.off[5]};
+        const LdsLoad<double> ld{acc.lds, set, W, W * W};
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            double f00, f10, f01, f11;
+            if constexpr (kYee) {
+                ld.load4<double>(kYeeSet[k], k, f00, f10, f01, f11);
+            } else {
+                const double* q = acc.lds + window_elem<double>(k, p.off[k], W * W);
+                const int st = window_step<double>(k);
+                f00 = q[0];
+                f10 = q[st];
+                f01 = q[st * W];
+                f11 = q[st * (W + 1)];
+            }
+            eval_point(k, f00, f10, f01, f11, p);
+        }
+    } else {
+        const GlobalAcc<double> g{acc.F, acc.nx, acc.ny};
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            double f00, f10, f01, f11;
+            g.quad(k, c[0][p.entry(k, 0)], c[1][p.entry(k, 1)], f00, f10, f01, f11);
+            eval_point(k, f00, f10, f01, f11, p);
+        }
+    }
+}
+
+template <bool kYee>
+GCB_HD void sample_at(const TileAcc3<double>& acc, const PushConst3& pc, const double X[3],
+                      Point<3, kYee>& p) {
+    int c[3][Point<3, kYee>::kSets];
+    place<3>(pc, X, c, p);
+    const int o[3] = {acc.oi, acc.oj, acc.ol}, W = acc.W;
+    locate<3>(pc, o, W, c, p);
+    if (__builtin_expect(p.in, 1)) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            double f[8];
+            const LdsLoad3<double> ld{acc.lds, &p.off[k], W, W * W, W * W * W};
+            ld.load8<double>(0, k, f);
+            eval_point(k, f, p);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            double f[8];
+            acc.g.oct<double>(k, c[0][p.entry(k, 0)], c[1][p.entry(k, 1)],
+                              c[2][p.entry(k, 2)], f);
+            eval_point(k, f, p);
+        }
+    }
+}
+
+// The point as the sample that the forward functions take (a runaway point's
+// is NaN, as the gather has it).
+template <bool kYee>
+GCB_HD void to_sample(const Point<2, kYee>& p, Sample<double>& s) {
+    const double nan = __builtin_nan("");
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        s.E[i] = p.far ? nan : p.v[i];
+        s.B[i] = p.far ? nan : p.v[3 + i];
+        s.dBx[i] = p.far ? nan : p.d[0][3 + i];
+        s.dBy[i] = p.far ? nan : p.d[1][3 + i];
+    }
+}
+
+template <bool kYee>
+GCB_HD void to_sample(const Point<3, kYee>& p, Sample3<double>& s) {
+    const double nan = __builtin_nan("");
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        s.E[i] = p.far ? nan : p.v[i];
+        s.B[i] = p.far ? nan : p.v[3 + i];
+        s.dBx[i] = p.far ? nan : p.d[0][3 + i];
+        s.dBy[i] = p.far ? nan : p.d[1][3 + i];
+        s.dBz[i] = p.far ? nan : p.d[2][3 + i];
+    }
+}
+
+// Cotangents of E, B and of the B gradients per cell at a point.
+template <int D>
+struct SampleBar {
+    double v[6];      // E, B
+    double g[D][3];   // d_a B
+
+    GCB_HD SampleBar() {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[k] = 0.0;
+#pragma unroll
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) g[a][i] = 0.0;
+    }
+};
+
+// The four node cotangents of a bilinear cell from those of the value and of
+// the two gradients: the transpose of cell_coefs and eval_coefs.
+GCB_HD void plane_back(double vb, double gx, double gy, double wx, double wy, double o[4]) {
+    const double cx = vb * wx + gx;
+    const double cy = vb * wy + gy;
+    const double cxy = wy * cx + gy * wx;
+    o[3] = cxy;
+    o[1] = cx - cxy;
+    o[2] = cy - cxy;
+    o[0] = (vb - cx) - o[2];
+}
+
+// Node cotangents of component k (2^D values, x fastest).
+template <bool kYee>
+GCB_HD void nodes_back(const Point<2, kYee>& p, const SampleBar<2>& sb, int k, double o[4]) {
+    plane_back(sb.v[k], k < 3 ? 0.0 : sb.g[0][k - 3], k < 3 ? 0.0 : sb.g[1][k - 3],
+               p.w[0][p.entry(k, 0)], p.w[1][p.entry(k, 1)], o);
+}
+
+template <bool kYee>
+GCB_HD void nodes_back(const Point<3, kYee>& p, const SampleBar<3>& sb, int k, double o[8]) {
+    const double wx = p.w[0][p.entry(k, 0)], wy = p.w[1][p.entry(k, 1)],
+                 wz = p.w[2][p.entry(k, 2)], az = 1.0 - wz;
+    if (k < 3) {
+        plane_back(sb.v[k] * az, 0.0, 0.0, wx, wy, o);
+        plane_back(sb.v[k] * wz, 0.0, 0.0, wx, wy, o + 4);
+    } else {
+        const double v = sb.v[k], gx = sb.g[0][k - 3], gy = sb.g[1][k - 3], gz = sb.g[2][k - 3];
+        plane_back(v * az - gz, gx * az, gy * az, wx, wy, o);
+        plane_back(v * wz + gz, gx * wz, gy * wz, wx, wy, o + 4);
+    }
+}
+
+// index of the mixed derivative along axes a and b
+GCB_HD constexpr int mixed(int a, int b) { return a + b - 1; }   // xy 0, xz 1, yz 2
+
+// Cotangents of the sample at X to the nodes (by `win`) and to the position.
+template <int D, bool kYee, class Win>
+GCB_HD void point_back(const Win& win, const typename Dim<D>::Push& pc, const double X[D],
+                       const Point<D, kYee>& p, const SampleBar<D>& sb, double Xb[D]) {
+    // a runaway point's sample is a constant NaN: it depends on nothing
+    if (p.far) return;
+    win.add(pc, X, p, sb);
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        double q = 0.0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) q += sb.v[k] * p.d[a][k];
+#pragma unroll
+        for (int b = 0; b < D; ++b)
+            if (b != a) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) q += sb.g[b][i] * p.m[mixed(a, b)][i];
+            }
+        Xb[a] += q * Dim<D>::inv_d(pc, a);
     }
 }
 
 // ---------------------------------------------------------------------------
 // local quantities
 
-// Cotangents of E, B and of the ND B-gradient directions G[j][i] = d_j B_i
-// (ND = 2 in the plane, 3 in space) from those of the local quantities.
-template <int ND>
-GCB_HD void local_vjp_nd(const double E[3], const double Bv[3], const double G[ND][3],
-                         const KD& K, const LocalBar& Lb, double Eb[3], double Bb[3],
-                         double Gb[ND][3]) {
-    for (int i = 0; i < 3; ++i) Eb[i] = Bb[i] = 0.0;
-    for (int j = 0; j < ND; ++j)
-        for (int i = 0; i < 3; ++i) Gb[j][i] = 0.0;
-    const double B = sqrt((Bv[0] * Bv[0] + Bv[1] * Bv[1]) + Bv[2] * Bv[2]);
-    if (B == 0.0) return;   // b, v_E and the curvature terms are held at 0 there
-    const double inv_B = 1.0 / B;
-    const double b[3] = {Bv[0] * inv_B, Bv[1] * inv_B, Bv[2] * inv_B};
-    const double sc = K.c * (inv_B * inv_B);
-    const double ExB[3] = {E[1] * Bv[2] - E[2] * Bv[1], E[2] * Bv[0] - E[0] * Bv[2],
-                           E[0] * Bv[1] - E[1] * Bv[0]};
-    const double vE[3] = {sc * ExB[0], sc * ExB[1], sc * ExB[2]};
-    const double vE2 = (vE[0] * vE[0] + vE[1] * vE[1]) + vE[2] * vE[2];
-    const double om = 1.0 - vE2 * K.inv_c2;
-    const bool clamped = om < kKappaFloor;
-    const double kappa = 1.0 / sqrt(clamped ? kKappaFloor : om);
-    double dn[ND], db[ND][3], bgb[3], vgb[3];
-    for (int j = 0; j < ND; ++j) {
-        dn[j] = (b[0] * G[j][0] + b[1] * G[j][1]) + b[2] * G[j][2];
-        for (int i = 0; i < 3; ++i) db[j][i] = (G[j][i] - b[i] * dn[j]) * inv_B;
-    }
-    for (int i = 0; i < 3; ++i) {
-        bgb[i] = 0.0;
-        vgb[i] = 0.0;
-        for (int j = 0; j < ND; ++j) {
-            bgb[i] += b[j] * db[j][i];
-            vgb[i] += vE[j] * db[j][i];
-        }
-    }
-
-    double vEb[3], bb[3], bgbb[3], vgbb[3];
-    for (int i = 0; i < 3; ++i) {
-        vEb[i] = Lb.vE[i] + Lb.A * bgb[i] + Lb.C * vgb[i];
-        bb[i] = Lb.b[i];
-        bgbb[i] = Lb.bgb[i] + Lb.A * vE[i];
-        vgbb[i] = Lb.vgb[i] + Lb.C * vE[i];
-    }
-    double invBb = Lb.inv_B;
-    double Bmb = Lb.B;
-    double dbb[ND][3];
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < ND; ++j) {
-            vEb[j] += vgbb[i] * db[j][i];
-            bb[j] += bgbb[i] * db[j][i];
-            dbb[j][i] = vgbb[i] * vE[j] + bgbb[i] * b[j];
-        }
-    double dnb[ND];
-    for (int j = 0; j < ND; ++j) {
-        dnb[j] = 0.0;
-        for (int i = 0; i < 3; ++i) {
-            Gb[j][i] = dbb[j][i] * inv_B;
-            bb[i] -= dbb[j][i] * dn[j] * inv_B;
-            dnb[j] -= dbb[j][i] * b[i] * inv_B;
-            invBb += dbb[j][i] * (G[j][i] - b[i] * dn[j]);
-        }
-    }
-    for (int j = 0; j < ND; ++j)
-        for (int i = 0; i < 3; ++i) {
-            bb[i] += dnb[j] * G[j][i];
-            Gb[j][i] += dnb[j] * b[i];
-        }
-    for (int i = 0; i < 3; ++i) {
-        Eb[i] = Lb.Epar * b[i];
-        bb[i] += Lb.Epar * E[i];
-    }
-    if (!clamped) {
-        const double omb = Lb.kappa * (-0.5) * kappa * kappa * kappa;
-        const double vE2b = -omb * K.inv_c2;
-        for (int i = 0; i < 3; ++i) vEb[i] += 2.0 * vE[i] * vE2b;
-    }
-    const double scb = (vEb[0] * ExB[0] + vEb[1] * ExB[1]) + vEb[2] * ExB[2];
-    const double ExBb[3] = {vEb[0] * sc, vEb[1] * sc, vEb[2] * sc};
-    cross_vjp(E, Bv, ExBb, Eb, Bb);
-    invBb += scb * 2.0 * K.c * inv_B;
-    for (int i = 0; i < 3; ++i) {
-        Bb[i] += bb[i] * inv_B;
-        invBb += bb[i] * Bv[i];
-    }
-    Bmb += -invBb * inv_B * inv_B;
-    for (int i = 0; i < 3; ++i) Bb[i] += Bmb * b[i];
+GCB_HD double dot3(const double a[3], const double b[3]) {
+    return (a[0] * b[0] + a[1] * b[1]) + a[2] * b[2];
+}
+GCB_HD void cross3(const double a[3], const double b[3], double c[3]) {
+    c[0] = a[1] * b[2] - a[2] * b[1];
+    c[1] = a[2] * b[0] - a[0] * b[2];
+    c[2] = a[0] * b[1] - a[1] * b[0];
 }
 
-GCB_HD void local_vjp(const SampleD& s, const KD& K, const LocalBar& Lb, SampleBar& sb) {
-    const double G[2][3] = {{s.dBx[0], s.dBx[1], s.dBx[2]}, {s.dBy[0], s.dBy[1], s.dBy[2]}};
-    double Eb[3], Bb[3], Gb[2][3];
-    local_vjp_nd<2>(s.E, s.B, G, K, Lb, Eb, Bb, Gb);
-    for (int i = 0; i < 3; ++i) {
-        sb.E[i] += Eb[i];
-        sb.B[i] += Bb[i];
-        sb.dBx[i] += Gb[0][i];
-        sb.dBy[i] += Gb[1][i];
+struct LocalBar {
+    double B = 0.0, inv_B = 0.0, kappa = 0.0, Epar = 0.0;
+    double b[3] = {0.0, 0.0, 0.0}, vE[3] = {0.0, 0.0, 0.0};
+};
+
+// E and B cotangents from those of b, v_E, kappa, E_par, B and 1/B.
+template <int D, class S, class KC>
+GCB_HD void local_back(const S& s, const LocalD& L, const KC& K, const LocalBar& Lb,
+                       SampleBar<D>& sb) {
+    if (L.B == 0.0) {   // b, v_E and the curvature terms are held at 0 there
+        sb = SampleBar<D>();
+        return;
     }
+    double vEb[3], bb[3], X[3], Xb[3], t[3];
+    // the clamp holds kappa: no way through it
+    const double omb = L.om > kKappaFloor
+                           ? (-0.5 * Lb.kappa) * ((L.kappa * L.kappa) * L.kappa) : 0.0;
+    const double q = (-2.0 * K.inv_c2) * omb;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        sb.v[i] += Lb.Epar * L.b[i];
+        bb[i] = Lb.b[i] + Lb.Epar * s.E[i];
+        vEb[i] = Lb.vE[i] + q * L.vE[i];
+    }
+    cross3(s.E, s.B, X);
+    const double sc = K.c * (L.inv_B * L.inv_B);
+    const double scb = dot3(vEb, X);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) Xb[i] = sc * vEb[i];
+    cross3(s.B, Xb, t);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) sb.v[i] += t[i];
+    cross3(Xb, s.E, t);
+    const double invBb = (Lb.inv_B + scb * ((2.0 * K.c) * L.inv_B)) + dot3(bb, s.B);
+    const double Bmb = Lb.B - invBb * (L.inv_B * L.inv_B);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) sb.v[3 + i] += (t[i] + bb[i] * L.inv_B) + Bmb * L.b[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -235,459 +437,522 @@ GCB_HD void local_vjp(const SampleD& s, const KD& K, const LocalBar& Lb, SampleB
 // serves the paper's eq. dmudt only)
 GCB_HD Gyr<double> conserved_mu(double mu) { return Gyr<double>{mu, 0.0, false}; }
 
-GCB_HD void gamma_vjp(const LocalD& L, double upar, double mu, const KD& K, double Gb,
-                      LocalBar& Lb, double& uparb, double& mub) {
-    const double uperp2 = ((2.0 * mu) * L.B) * L.kappa;
-    const double s = sqrt(1.0 + (upar * upar + uperp2) * K.inv_c2);
-    Lb.kappa += Gb * s;
-    const double argb = Gb * L.kappa / (2.0 * s);
-    uparb += argb * 2.0 * upar * K.inv_c2;
-    const double u2b = argb * K.inv_c2;
-    mub += u2b * 2.0 * L.B * L.kappa;
-    Lb.B += u2b * 2.0 * mu * L.kappa;
-    Lb.kappa += u2b * 2.0 * mu * L.B;
+// Gb: cotangent of Gamma
+template <class KC>
+GCB_HD void gamma_back(const LocalD& L, double upar, double mu, const KC& K, double Gb,
+                       LocalBar& Lb, double& uparb, double& mub) {
+    const double bk = L.B * L.kappa;
+    const double arg = 1.0 + (upar * upar + (2.0 * mu) * bk) * K.inv_c2;
+    const double rs = rsqrt_nr(arg);
+    Lb.kappa += Gb * (arg * rs);
+    const double q = ((Gb * L.kappa) * rs) * K.inv_c2;   // 2 d(u_par^2 + u_perp^2)
+    uparb += q * upar;
+    mub += q * bk;
+    Lb.B += (q * mu) * L.kappa;
+    Lb.kappa += (q * mu) * L.B;
 }
 
-GCB_HD void vcurv_vjp(const LocalD& L, double upar, double gam, double inv_qm, const KD& K,
-                      const double vcb[3], LocalBar& Lb, double& uparb, double& gamb) {
-    const double pre = ((K.c * L.kappa) * L.kappa) * (L.inv_B * inv_qm);
-    const double a1 = (upar * upar) / gam;
-    const double w[3] = {a1 * L.bgb[0] + upar * L.vgb[0], a1 * L.bgb[1] + upar * L.vgb[1],
-                         a1 * L.bgb[2] + upar * L.vgb[2]};
-    const double z[3] = {L.b[1] * w[2] - L.b[2] * w[1], L.b[2] * w[0] - L.b[0] * w[2],
-                         L.b[0] * w[1] - L.b[1] * w[0]};
-    const double preb = (vcb[0] * z[0] + vcb[1] * z[1]) + vcb[2] * z[2];
-    const double zb[3] = {pre * vcb[0], pre * vcb[1], pre * vcb[2]};
-    double wb[3] = {0.0, 0.0, 0.0};
-    cross_vjp(L.b, w, zb, Lb.b, wb);
-    const double a1b = (wb[0] * L.bgb[0] + wb[1] * L.bgb[1]) + wb[2] * L.bgb[2];
-    for (int i = 0; i < 3; ++i) {
-        Lb.bgb[i] += a1 * wb[i];
-        Lb.vgb[i] += upar * wb[i];
+// igb: cotangent of 1/Gamma (inv_gam)
+template <int D, class S, class KC>
+GCB_HD void vcurv_back(const S& s, const LocalD& L, const typename Dim<D>::Push& pc,
+                       double upar, double inv_gam, double inv_qm, const KC& K,
+                       const double vcb[3], LocalBar& Lb, SampleBar<D>& sb, double& uparb,
+                       double& igb) {
+    const double u2 = upar * upar;
+    const double a1 = u2 * inv_gam;
+    double V[D], w[3] = {0.0, 0.0, 0.0}, z[3], zb[3], wb[3], t[3];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        V[a] = (a1 * L.b[a] + upar * L.vE[a]) * Dim<D>::inv_d(pc, a);
+        const double* g = Dim<D>::grad(s, a);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) w[i] += V[a] * g[i];
     }
-    uparb += (wb[0] * L.vgb[0] + wb[1] * L.vgb[1]) + wb[2] * L.vgb[2];
-    uparb += a1b * 2.0 * upar / gam;
-    gamb += -a1b * a1 / gam;
-    Lb.kappa += preb * 2.0 * K.c * L.kappa * L.inv_B * inv_qm;
-    Lb.inv_B += preb * K.c * L.kappa * L.kappa * inv_qm;
+    cross3(L.b, w, z);
+    const double ci = K.c * inv_qm;
+    const double kb = L.kappa * L.inv_B;
+    const double pre = (kb * kb) * ci;
+    const double q = (2.0 * dot3(vcb, z)) * (kb * ci);
+    Lb.kappa += q * L.inv_B;
+    Lb.inv_B += q * L.kappa;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) zb[i] = pre * vcb[i];
+    cross3(w, zb, t);
+    cross3(zb, L.b, wb);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) Lb.b[i] += t[i];
+    double a1b = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        const double* g = Dim<D>::grad(s, a);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) sb.g[a][i] += V[a] * wb[i];
+        const double Vb = dot3(g, wb) * Dim<D>::inv_d(pc, a);
+        a1b += Vb * L.b[a];
+        Lb.b[a] += a1 * Vb;
+        uparb += Vb * L.vE[a];
+        Lb.vE[a] += upar * Vb;
+    }
+    uparb += (a1b * 2.0) * (upar * inv_gam);
+    igb += a1b * u2;
 }
 
-GCB_HD void drift_vjp(const LocalD& L, double upn, double mu, double inv_qm, bool curv,
-                      const KD& K, const double Fb[2], LocalBar& Lb, double& upnb,
-                      double& mub) {
-    const double g = gamma_gca(L, upn, conserved_mu(mu), K);
-    const double a = upn / g;
-    const double ab = Fb[0] * L.b[0] + Fb[1] * L.b[1];
-    Lb.b[0] += a * Fb[0];
-    Lb.b[1] += a * Fb[1];
-    Lb.vE[0] += Fb[0];
-    Lb.vE[1] += Fb[1];
-    double gb = -ab * a / g;
-    upnb += ab / g;
+// Fb: cotangents of u_par b/Gamma + v_E + v_c
+template <int D, class S, class KC>
+GCB_HD void drift_back(const S& s, const LocalD& L, const typename Dim<D>::Push& pc,
+                       double upn, double mu, double inv_qm, bool curv, const KC& K,
+                       const double Fb[D], LocalBar& Lb, SampleBar<D>& sb, double& upnb,
+                       double& mub) {
+    const Gam<double> G = gamma_gca2(L, upn, conserved_mu(mu), K);
+    const double a = upn * G.inv;
+    double ab = 0.0;
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        ab += Fb[i] * L.b[i];
+        Lb.b[i] += a * Fb[i];
+        Lb.vE[i] += Fb[i];
+    }
+    upnb += ab * G.inv;
+    double igb = ab * upn;
     if (curv) {
-        const double vcb[3] = {Fb[0], Fb[1], 0.0};
-        vcurv_vjp(L, upn, g, inv_qm, K, vcb, Lb, upnb, gb);
+        const double vcb[3] = {Fb[0], Fb[1], D == 3 ? Fb[D - 1] : 0.0};
+        vcurv_back<D>(s, L, pc, upn, G.inv, inv_qm, K, vcb, Lb, sb, upnb, igb);
     }
-    gamma_vjp(L, upn, mu, K, gb, Lb, upnb, mub);
+    gamma_back(L, upn, mu, K, -igb * (G.inv * G.inv), Lb, upnb, mub);
+}
+
+// u_par b/Gamma + v_E + v_c, the D components
+template <int D, class S, class KC>
+GCB_HD void drift_of(const S& s, const LocalD& L, double upn, double mu, double inv_qm,
+                     bool curv, const KC& K, double F[D]) {
+    const Gam<double> G = gamma_gca2(L, upn, conserved_mu(mu), K);
+    const double a = upn * G.inv;
+    double vc[3] = {0.0, 0.0, 0.0};
+    if (curv) v_curv_dir(L, s, upn, G.inv, inv_qm, K, vc);
+#pragma unroll
+    for (int i = 0; i < D; ++i) F[i] = (a * L.b[i] + L.vE[i]) + vc[i];
 }
 
 // ---------------------------------------------------------------------------
 // parallel update
 
-GCB_HD void parallel_vjp(const LocalD& Ln, double upar, double mu, double qm, bool curv,
-                         const KD& K, double upnb, LocalBar& Lb, double& uparb, double& mub) {
+// A and C (curvature_scalars_dir) from their cotangents
+template <int D, class S, class KC>
+GCB_HD void scalars_back(const S& s, const LocalD& L, const typename Dim<D>::Push& pc,
+                         const KC& K, double Ab, double Cb, LocalBar& Lb, SampleBar<D>& sb) {
+    double gb[3], gv[3], gbb[3], gvb[3];
+    b_along(s, L.b, K, gb);
+    b_along(s, L.vE, K, gv);
+    const double Ai = Ab * L.inv_B, Ci = Cb * L.inv_B;
+    Lb.inv_B += Ab * dot3(L.vE, gb) + Cb * dot3(L.vE, gv);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        Lb.vE[i] += Ai * gb[i] + Ci * gv[i];
+        gbb[i] = Ai * L.vE[i];
+        gvb[i] = Ci * L.vE[i];
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        const double id = Dim<D>::inv_d(pc, a);
+        const double* g = Dim<D>::grad(s, a);
+        const double ba = L.b[a] * id, va = L.vE[a] * id;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) sb.g[a][i] += ba * gbb[i] + va * gvb[i];
+        Lb.b[a] += dot3(g, gbb) * id;
+        Lb.vE[a] += dot3(g, gvb) * id;
+    }
+}
+
+// L holds A and C (with curv); Ab, Cb receive their cotangents
+template <class KC>
+GCB_HD void parallel_back(const LocalD& L, double upar, double mu, double qm, bool curv,
+                          const KC& K, double upnb, LocalBar& Lb, double& uparb, double& mub,
+                          double& Ab, double& Cb) {
     const double dtqm = qm * K.dt;
+    Ab = Cb = 0.0;
     if (!curv) {
         uparb += upnb;
         Lb.Epar += dtqm * upnb;
         return;
     }
     const double h = K.h;
-    const double A = Ln.A, C = Ln.C;
-    const double G0 = gamma_gca(Ln, upar, conserved_mu(mu), K);
-    const double upr = (upar * (1.0 + h * A) + dtqm * Ln.Epar) + (h * G0) * C;
-    const double D = 1.0 - h * A;
-    const double DD = D * D;
-    const double kap = Ln.kappa;
-    const double k1 = (h * h) * (C * C) - (K.c2 * DD) / (kap * kap);
+    const double A = L.A, C = L.C;
+    const double G0 = gamma_gca2(L, upar, conserved_mu(mu), K).g;
+    const double upr = (upar * (1.0 + h * A) + dtqm * L.Epar) + (h * G0) * C;
+    const double Dd = 1.0 - h * A;
+    const double DD = Dd * Dd;
+    const double k1 = (h * h) * (C * C) - (K.c2 * DD) * L.om;
     const double k2 = (upr * K.dt) * C;
-    const double u2 = ((2.0 * mu) * Ln.B) * kap;
+    const double bk = L.B * L.kappa;
+    const double u2 = (2.0 * mu) * bk;
     const double k3 = upr * upr + (K.c2 + u2) * DD;
     const double disc = k2 * k2 - (4.0 * k1) * k3;
-    const bool dok = fabs(D) >= kDFloor;
+    const bool dok = fabs(Dd) >= kDFloor;
     bool ok = (k1 < 0.0) && (disc >= 0.0) && dok;
-    const double sq = sqrt(disc >= 0.0 ? disc : 0.0);
+    const double sq = sqrt_nr(disc >= 0.0 ? disc : 0.0);
     const bool pos_k2 = k2 >= 0.0;
     const double num = pos_k2 ? k2 + sq : 2.0 * k3;
     double den = pos_k2 ? -2.0 * k1 : sq - k2;
     den = (ok && den > 0.0) ? den : 1.0;
-    const double gp = num / den;
+    const double gp = div_nr(num, den);
     ok = ok && (gp > 0.0) && __builtin_isfinite(gp);
     if (!ok && !dok) {
         uparb += upnb;
         Lb.Epar += dtqm * upnb;
         return;
     }
-    double uprb, Db, Cb = 0.0;
+    const double iD = rcp_nr(Dd);
+    double uprb = upnb * iD, Db;
+    const double w = uprb * h;
     if (ok) {
-        const double upn = (upr + (h * gp) * C) / D;
-        uprb = upnb / D;
-        const double gpb = upnb * h * C / D;
-        Cb += upnb * h * gp / D;
-        Db = -upnb * upn / D;
-        const double dP = 2.0 * k1 * gp + k2;
-        const double k1b = -gpb * gp * gp / dP;
-        const double k2b = -gpb * gp / dP;
-        const double k3b = -gpb / dP;
+        const double upn = (upr + (h * gp) * C) * iD;
+        const double gpb = w * C;
+        Cb += w * gp;
+        Db = -uprb * upn;
+        const double k3b = -gpb / (2.0 * k1 * gp + k2);
+        const double k2b = k3b * gp;
+        const double k1b = k2b * gp;
         uprb += k3b * 2.0 * upr;
         double DDb = k3b * (K.c2 + u2);
-        const double u2b = k3b * DD;
-        mub += u2b * 2.0 * Ln.B * kap;
-        Lb.B += u2b * 2.0 * mu * kap;
-        Lb.kappa += u2b * 2.0 * mu * Ln.B;
+        const double u2b = 2.0 * (k3b * DD);
+        mub += u2b * bk;
+        Lb.B += u2b * mu * L.kappa;
+        Lb.kappa += u2b * mu * L.B;
         uprb += k2b * K.dt * C;
         Cb += k2b * upr * K.dt;
         Cb += k1b * 2.0 * (h * h) * C;
-        DDb += -k1b * K.c2 / (kap * kap);
-        Lb.kappa += k1b * 2.0 * K.c2 * DD / (kap * kap * kap);
-        Db += DDb * 2.0 * D;
+        DDb -= k1b * K.c2 * L.om;
+        Lb.kappa += k1b * 2.0 * K.c2 * DD * (L.om * L.inv_kappa);
+        Db += DDb * 2.0 * Dd;
     } else {
         // fallback: Gamma taken at u'/D (no implicit term)
-        const double v = upr / D;
-        const double gfb = gamma_gca(Ln, v, conserved_mu(mu), K);
-        const double upn = (upr + (h * gfb) * C) / D;
-        uprb = upnb / D;
-        const double gfbb = upnb * h * C / D;
-        Cb += upnb * h * gfb / D;
-        Db = -upnb * upn / D;
+        const double v = upr * iD;
+        const double gfb = gamma_gca2(L, v, conserved_mu(mu), K).g;
+        const double upn = (upr + (h * gfb) * C) * iD;
+        const double gfbb = w * C;
+        Cb += w * gfb;
+        Db = -uprb * upn;
         double vb = 0.0;
-        gamma_vjp(Ln, v, mu, K, gfbb, Lb, vb, mub);
-        uprb += vb / D;
-        Db += -vb * v / D;
+        gamma_back(L, v, mu, K, gfbb, Lb, vb, mub);
+        uprb += vb * iD;
+        Db -= vb * v * iD;
     }
-    Lb.A += -h * Db;
+    Ab = h * (uprb * upar - Db);
     uparb += uprb * (1.0 + h * A);
-    Lb.A += uprb * upar * h;
     Lb.Epar += uprb * dtqm;
-    const double G0b = uprb * h * C;
     Cb += uprb * h * G0;
-    Lb.C += Cb;
-    gamma_vjp(Ln, upar, mu, K, G0b, Lb, uparb, mub);
+    gamma_back(L, upar, mu, K, uprb * h * C, Lb, uparb, mub);
 }
 
 // ---------------------------------------------------------------------------
-// steps.  st[7] = (x, y, xp, yp, ux, uy, uz) at the step start; lam[7] holds
-// the cotangents of the step outputs on entry and of its inputs on return.
+// steps.  st = (x, previous x, u) at the step start; lam holds the cotangents
+// of the step outputs on entry and of its inputs on return.
 
-template <bool kYee, class Acc, class Sink>
-GCB_HD void boris_step_vjp(const Acc& acc, Sink& sink, const PushConst& pc, const KD& K,
-                           const double st[7], double qm, double lam[7]) {
-    const double x = st[0], y = st[1];
-    SampleD s;
-    gather<double, false, kYee>(acc, pc, K, x, y, s);
-    const double* E = s.E;
-    const double* Bv = s.B;
-    const double u[3] = {st[4], st[5], st[6]};
+template <int D, bool kYee, class Win>
+GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
+                      const typename Dim<D>::Push& pc, const typename Dim<D>::Const& K,
+                      const double st[2 * D + 3], double qm, double lam[2 * D + 3]) {
+    Point<D, kYee> p;
+    sample_at(acc, pc, st, p);
+    typename Dim<D>::Smp s;
+    to_sample(p, s);
+    const double* u = st + 2 * D;
+    double* ub = lam + 2 * D;
+    const double dt = K.dt;
     // forward
-    const double hq = (qm * K.dt) * 0.5;
-    const double um[3] = {u[0] + hq * E[0], u[1] + hq * E[1], u[2] + hq * E[2]};
-    const double gm = gamma_full(um[0], um[1], um[2], K);
-    const double f = hq / (K.c * gm);
-    const double t[3] = {f * Bv[0], f * Bv[1], f * Bv[2]};
-    const double t2 = (t[0] * t[0] + t[1] * t[1]) + t[2] * t[2];
-    const double g = 2.0 / (1.0 + t2);
-    const double sv[3] = {g * t[0], g * t[1], g * t[2]};
-    const double up[3] = {um[0] + (um[1] * t[2] - um[2] * t[1]),
-                          um[1] + (um[2] * t[0] - um[0] * t[2]),
-                          um[2] + (um[0] * t[1] - um[1] * t[0])};
-    const double un[3] = {um[0] + (up[1] * sv[2] - up[2] * sv[1]) + hq * E[0],
-                          um[1] + (up[2] * sv[0] - up[0] * sv[2]) + hq * E[1],
-                          um[2] + (up[0] * sv[1] - up[1] * sv[0]) + hq * E[2]};
-    const double gn = gamma_full(un[0], un[1], un[2], K);
-    const double ig = 1.0 / gn;
-    // reverse
-    const double xnb = lam[0], ynb = lam[1];
-    double unb[3] = {lam[4] + pc.dt * ig * xnb, lam[5] + pc.dt * ig * ynb, lam[6]};
-    const double igb = pc.dt * (un[0] * xnb + un[1] * ynb);
-    const double gnb = -igb * ig * ig;
-    for (int i = 0; i < 3; ++i) unb[i] += gnb * un[i] * K.inv_c2 / gn;
-    SampleBar sb;
-    zero(sb);
+    const double hq = (qm * dt) * 0.5;
+    double um[3], t[3], sv[3], up[3], un[3], x[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) um[i] = u[i] + hq * s.E[i];
+    const Gam<double> gm = gamma_full2(um[0], um[1], um[2], K);
+    const double f = hq * rcp_nr(K.c) * gm.inv;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) t[i] = f * s.B[i];
+    const double g = 2.0 * rcp_nr0(1.0 + dot3(t, t));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) sv[i] = g * t[i];
+    cross3(um, t, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) up[i] = um[i] + x[i];
+    cross3(up, sv, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) un[i] = (um[i] + x[i]) + hq * s.E[i];
+    const Gam<double> gn = gamma_full2(un[0], un[1], un[2], K);
+    // reverse: x^{n+1} = x^n + dt un/Gamma
+    double unb[3] = {ub[0], ub[1], ub[2]}, igb = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        unb[a] += dt * gn.inv * lam[a];
+        igb += dt * un[a] * lam[a];
+    }
+    const double gnb = -igb * (gn.inv * gn.inv);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) unb[i] += (gnb * K.inv_c2 * gn.inv) * un[i];
+    SampleBar<D> sb;
+    double umb[3], upb[3], svb[3], tb[3];
     // un = uq + hq E, uq = um + up x s
-    for (int i = 0; i < 3; ++i) sb.E[i] += hq * unb[i];
-    double umb[3] = {unb[0], unb[1], unb[2]};
-    double upb[3] = {0.0, 0.0, 0.0}, svb[3] = {0.0, 0.0, 0.0};
-    cross_vjp(up, sv, unb, upb, svb);
+    cross3(sv, unb, upb);
+    cross3(unb, up, svb);
     // up = um + um x t
-    double tb[3] = {0.0, 0.0, 0.0};
-    for (int i = 0; i < 3; ++i) umb[i] += upb[i];
-    cross_vjp(um, t, upb, umb, tb);
-    // s = g t
-    const double gb = (svb[0] * t[0] + svb[1] * t[1]) + svb[2] * t[2];
-    for (int i = 0; i < 3; ++i) tb[i] += g * svb[i];
-    const double t2b = -gb * g * g * 0.5;
-    for (int i = 0; i < 3; ++i) tb[i] += 2.0 * t[i] * t2b;
-    // t = f B
-    const double fb = (tb[0] * Bv[0] + tb[1] * Bv[1]) + tb[2] * Bv[2];
-    for (int i = 0; i < 3; ++i) sb.B[i] += f * tb[i];
-    const double gmb = -fb * f / gm;
-    for (int i = 0; i < 3; ++i) umb[i] += gmb * um[i] * K.inv_c2 / gm;
-    // um = u + hq E
-    for (int i = 0; i < 3; ++i) sb.E[i] += hq * umb[i];
-    double Xb = xnb + lam[2], Yb = ynb + lam[3];
-    gather_vjp(acc, sink, pc, kYee, x, y, sb, Xb, Yb);
-    lam[0] = Xb;
-    lam[1] = Yb;
-    lam[2] = 0.0;
-    lam[3] = 0.0;
-    lam[4] = umb[0];
-    lam[5] = umb[1];
-    lam[6] = umb[2];
-}
-
-// local quantities at a point, with the sample kept for local_vjp
-template <bool kYee, class Acc>
-GCB_HD void local_at(const Acc& acc, const PushConst& pc, const KD& K, double X, double Y,
-                     SampleD& s, LocalD& L) {
-    gather<double, true, kYee>(acc, pc, K, X, Y, s);
-    local_from_sample(s, K, L);
-}
-
-template <bool kYee, class Acc, class Sink>
-GCB_HD void local_bar_to_position(const Acc& acc, Sink& sink, const PushConst& pc,
-                                  const KD& K, const SampleD& s, double X, double Y,
-                                  const LocalBar& Lb, double& Xb, double& Yb) {
-    SampleBar sb;
-    zero(sb);
-    local_vjp(s, K, Lb, sb);
-    gather_vjp(acc, sink, pc, kYee, X, Y, sb, Xb, Yb);
+    cross3(t, upb, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) umb[i] = (unb[i] + upb[i]) + x[i];
+    cross3(upb, um, tb);
+    // s = g t, g = 2/(1 + t^2)
+    const double gb = dot3(svb, t);
+    const double t2b = -gb * (g * g) * 0.5;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) tb[i] += g * svb[i] + (2.0 * t2b) * t[i];
+    // t = f B, f = hq/(c Gamma)
+    const double fb = dot3(tb, s.B);
+    const double gmb = -fb * f * gm.inv;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        sb.v[3 + i] = f * tb[i];
+        umb[i] += (gmb * K.inv_c2 * gm.inv) * um[i];
+        sb.v[i] = hq * (unb[i] + umb[i]);
+    }
+    // (x, u) of the step start; the previous position has no part in the step,
+    // and x^n is the next one's previous position
+    double Xb[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        Xb[a] = lam[a] + lam[D + a];
+        lam[D + a] = 0.0;
+    }
+    point_back<D, kYee>(win, pc, st, p, sb, Xb);
+#pragma unroll
+    for (int a = 0; a < D; ++a) lam[a] = Xb[a];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) ub[i] = umb[i];
 }
 
 constexpr int kMaxAdjIter = 8;   // fixed-point iterations the adjoint supports
 
-// Field samples of the forward recomputation that the reverse sweep takes
-// again instead of gathering them a second time: slot 0 is R^{n-1/2}, slot 1
-// R^n, slot 1 + k the iterate R^k; `put` may drop a slot, and `get` then
-// says so.  NoSamples keeps none.
-struct NoSamples {
-    GCB_HD void put(int, const SampleD&) {}
-    GCB_HD bool get(int, SampleD&) const { return false; }
-};
-
-// local quantities at a point, from a kept sample when there is one
-template <bool kYee, class Acc, class Keep>
-GCB_HD void local_again(const Acc& acc, const Keep& keep, int slot, const PushConst& pc,
-                        const KD& K, double X, double Y, SampleD& s, LocalD& L) {
-    if (keep.get(slot, s))
-        local_from_sample(s, K, L);
-    else
-        local_at<kYee>(acc, pc, K, X, Y, s, L);
-}
-
-// Number of gather points whose cotangents gca_step_vjp hands to its sink:
-// R^{n+1/2}, the iterates R^1..R^{K-1}, R^n and R^{n-1/2}.
-GCB_HD int gca_vjp_samples(int n_iter) {
-    const int Kit = n_iter < kMaxAdjIter ? n_iter : kMaxAdjIter;
-    return (Kit > 1 ? Kit - 1 : 0) + 3;
-}
-
-template <bool kYee, class Acc, class Sink, class Keep = NoSamples>
-GCB_HD void gca_step_vjp(const Acc& acc, Sink& sink, const PushConst& pc, const KD& K,
-                         const double st[7], double qm, double lam[7], Keep keep = Keep()) {
-    const bool curv = pc.curvature != 0;
-    const double x = st[0], y = st[1];
-    const double ux = st[4], uy = st[5], uz = st[6];
-    const double inv_qm = 1.0 / qm;
+template <int D, bool kYee, class Win>
+GCB_HD void gca_vjp(const typename Dim<D>::Acc& acc, const Win& win,
+                    const typename Dim<D>::Push& pc, const typename Dim<D>::Const& K,
+                    const double st[2 * D + 3], double qm, double lam[2 * D + 3]) {
+    using Smp = typename Dim<D>::Smp;
+    const PushConst& pb = Dim<D>::base(pc);
+    const bool curv = pb.curvature != 0;
+    const double* u = st + 2 * D;
+    const double inv_qm = rcp_nr0(qm);
     const double h = K.h;
-    const int Kit = pc.n_iter < kMaxAdjIter ? pc.n_iter : kMaxAdjIter;
+    const int Kit = pb.n_iter < kMaxAdjIter ? pb.n_iter : kMaxAdjIter;
 
     // ---- forward recomputation (values the reverse sweep needs)
-    const double Rhx = x - 0.5 * min_image(x - st[2], pc.Lx);
-    const double Rhy = y - 0.5 * min_image(y - st[3], pc.Ly);
-    double upar, mu, gf, nu, up[3], bp[3], vch[3] = {0.0, 0.0, 0.0};
+    double Rh[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+        Rh[a] = st[a] - 0.5 * min_image_i<double>(st[a] - st[D + a], Dim<D>::box(pc, a),
+                                                  Dim<D>::inv_box(pc, a));
+    double upar, mu, bp[3];
     {
-        SampleD s;
+        Smp s;
         LocalD L;
-        local_at<kYee>(acc, pc, K, Rhx, Rhy, s, L);
-        keep.put(0, s);
-        upar = (ux * L.b[0] + uy * L.b[1]) + uz * L.b[2];
-        gf = gamma_full(ux, uy, uz, K);
-        if (curv) v_curv(L, upar, gf, inv_qm, K, vch);
-        up[0] = (ux - upar * L.b[0]) - (L.vE[0] + vch[0]) * gf;
-        up[1] = (uy - upar * L.b[1]) - (L.vE[1] + vch[1]) * gf;
-        up[2] = (uz - upar * L.b[2]) - (L.vE[2] + vch[2]) * gf;
-        const double up2 = (up[0] * up[0] + up[1] * up[1]) + up[2] * up[2];
-        mu = ((0.5 * up2) * L.inv_B) / L.kappa;
-        nu = sqrt(up2);
-        const double inv_nu = nu > 0.0 ? 1.0 / nu : 0.0;
-        for (int i = 0; i < 3; ++i) bp[i] = up[i] * inv_nu;
+        Dim<D>::template gather<kYee>(acc, pc, K, Rh, s);
+        local_fields(s.E, s.B, K, L);
+        upar = dot3(u, L.b);
+        const Gam<double> G = gamma_full2(u[0], u[1], u[2], K);
+        double vc[3] = {0.0, 0.0, 0.0};
+        if (curv) v_curv_dir(L, s, upar, G.inv, inv_qm, K, vc);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) bp[i] = (u[i] - upar * L.b[i]) - (L.vE[i] + vc[i]) * G.g;
+        const double up2 = dot3(bp, bp);
+        mu = ((0.5 * up2) * L.inv_B) * L.inv_kappa;
+        const double inv_nu = up2 > 0.0 ? rsqrt_nr(up2) : 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) bp[i] *= inv_nu;
     }
-    double upn, Fn[2];
+    double upn, Fn[D];
     {
-        SampleD s;
+        Smp s;
         LocalD L;
-        local_at<kYee>(acc, pc, K, x, y, s, L);
-        keep.put(1, s);
+        Dim<D>::template gather<kYee>(acc, pc, K, st, s);
+        local_fields(s.E, s.B, K, L);
+        if (curv) curvature_scalars_dir(s, K, L);
         uint32_t fl = 0;
         upn = parallel_update(L, upar, conserved_mu(mu), qm, curv, K, fl);
-        drift_terms(L, s, upn, conserved_mu(mu), inv_qm, curv, K, Fn[0], Fn[1]);
+        drift_of<D>(s, L, upn, mu, inv_qm, curv, K, Fn);
     }
-    double Rk[kMaxAdjIter + 1][2];
-    Rk[0][0] = x;
-    Rk[0][1] = y;
-    for (int k = 0; k < Kit; ++k) {
-        double F[2];
-        if (k == 0) {
-            F[0] = Fn[0];
-            F[1] = Fn[1];
-        } else {
-            SampleD s;
-            LocalD L;
-            local_at<kYee>(acc, pc, K, Rk[k][0], Rk[k][1], s, L);
-            keep.put(1 + k, s);
-            drift_terms(L, s, upn, conserved_mu(mu), inv_qm, curv, K, F[0], F[1]);
-        }
-        Rk[k + 1][0] = x + h * (Fn[0] + F[0]);
-        Rk[k + 1][1] = y + h * (Fn[1] + F[1]);
+    double Rk[kMaxAdjIter][D], Rx[D];   // R^1..R^{K-1}, then R^K
+#pragma unroll
+    for (int a = 0; a < D; ++a) Rx[a] = st[a] + h * (Fn[a] + Fn[a]);
+    for (int k = 1; k < Kit; ++k) {
+        Smp s;
+        LocalD L;
+        double F[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) Rk[k][a] = Rx[a];
+        Dim<D>::template gather<kYee>(acc, pc, K, Rx, s);
+        local_fields(s.E, s.B, K, L);
+        drift_of<D>(s, L, upn, mu, inv_qm, curv, K, F);
+#pragma unroll
+        for (int a = 0; a < D; ++a) Rx[a] = st[a] + h * (Fn[a] + F[a]);
     }
-    const double Rmx = x + 0.5 * (Rk[Kit][0] - x);
-    const double Rmy = y + 0.5 * (Rk[Kit][1] - y);
 
     // ---- reverse sweep
-    double xb = lam[2], yb = lam[3];   // xp_out = x
-    double RKb[2] = {lam[0], lam[1]};  // x_out = wrap(R^K)
-    const double ub[3] = {lam[4], lam[5], lam[6]};
-    double upnb = 0.0, mub = 0.0, bpb[3] = {0.0, 0.0, 0.0};
+    double xb[D], Rb[D];   // xp_out = x, x_out = wrap(R^K)
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        xb[a] = lam[D + a];
+        Rb[a] = lam[a];
+    }
+    double upnb = 0.0, mub = 0.0, bpb[3];
 
     // 5. reconstruction at R^{n+1/2}
     {
-        SampleD s;
+        double Rm[D], Rmb[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            Rm[a] = st[a] + 0.5 * (Rx[a] - st[a]);
+            Rmb[a] = 0.0;
+        }
+        const double* ub = lam + 2 * D;
+        Point<D, kYee> p;
+        Smp s;
         LocalD L;
-        local_at<kYee>(acc, pc, K, Rmx, Rmy, s, L);
+        sample_at(acc, pc, Rm, p);
+        to_sample(p, s);
+        local_fields(s.E, s.B, K, L);
         LocalBar Lb;
-        zero(Lb);
-        const double gr = gamma_gca(L, upn, conserved_mu(mu), K);
+        SampleBar<D> sb;
+        const Gam<double> G = gamma_gca2(L, upn, conserved_mu(mu), K);
         double vc[3] = {0.0, 0.0, 0.0};
-        if (curv) v_curv(L, upn, gr, inv_qm, K, vc);
-        const double um = sqrt(((2.0 * mu) * L.B) * L.kappa);
-        upnb += (ub[0] * L.b[0] + ub[1] * L.b[1]) + ub[2] * L.b[2];
-        double vcb[3], grb = 0.0, umb = 0.0;
+        if (curv) v_curv_dir(L, s, upn, G.inv, inv_qm, K, vc);
+        const double bk = L.B * L.kappa;
+        const double up2 = (2.0 * mu) * bk;
+        const double ium = up2 > 0.0 ? rsqrt_nr(up2) : 0.0;
+        const double um = up2 * ium;
+        upnb += dot3(ub, L.b);
+        double vcb[3], gb = 0.0, igb = 0.0;
+#pragma unroll
         for (int i = 0; i < 3; ++i) {
             Lb.b[i] += upn * ub[i];
-            Lb.vE[i] += gr * ub[i];
-            vcb[i] = gr * ub[i];
-            grb += (L.vE[i] + vc[i]) * ub[i];
-            umb += bp[i] * ub[i];
-            bpb[i] += um * ub[i];
+            vcb[i] = G.g * ub[i];
+            Lb.vE[i] += vcb[i];
+            gb += (L.vE[i] + vc[i]) * ub[i];
+            bpb[i] = um * ub[i];
         }
-        if (um > 0.0) {
-            const double Xb_ = umb / (2.0 * um);
-            mub += Xb_ * 2.0 * L.B * L.kappa;
-            Lb.B += Xb_ * 2.0 * mu * L.kappa;
-            Lb.kappa += Xb_ * 2.0 * mu * L.B;
+        const double q = dot3(bp, ub) * ium;   // 2 d(um^2)
+        mub += q * bk;
+        Lb.B += q * mu * L.kappa;
+        Lb.kappa += q * mu * L.B;
+        if (curv) vcurv_back<D>(s, L, pc, upn, G.inv, inv_qm, K, vcb, Lb, sb, upnb, igb);
+        gamma_back(L, upn, mu, K, gb - igb * (G.inv * G.inv), Lb, upnb, mub);
+        local_back<D>(s, L, K, Lb, sb);
+        point_back<D, kYee>(win, pc, Rm, p, sb, Rmb);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            xb[a] += 0.5 * Rmb[a];
+            Rb[a] += 0.5 * Rmb[a];
         }
-        if (curv) vcurv_vjp(L, upn, gr, inv_qm, K, vcb, Lb, upnb, grb);
-        gamma_vjp(L, upn, mu, K, grb, Lb, upnb, mub);
-        double Rmb[2] = {0.0, 0.0};
-        local_bar_to_position<kYee>(acc, sink, pc, K, s, Rmx, Rmy, Lb, Rmb[0], Rmb[1]);
-        xb += 0.5 * Rmb[0];
-        yb += 0.5 * Rmb[1];
-        RKb[0] += 0.5 * Rmb[0];
-        RKb[1] += 0.5 * Rmb[1];
     }
 
     // 4. fixed-point iterations in reverse order
-    double Fnb[2] = {0.0, 0.0};
-    double Rb[2] = {RKb[0], RKb[1]};
+    double Fnb[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) Fnb[a] = 0.0;
     for (int k = Kit - 1; k >= 0; --k) {
-        xb += Rb[0];
-        yb += Rb[1];
-        Fnb[0] += h * Rb[0];
-        Fnb[1] += h * Rb[1];
-        const double Fkb[2] = {h * Rb[0], h * Rb[1]};
+        double Fb[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            xb[a] += Rb[a];
+            Fb[a] = h * Rb[a];
+            Fnb[a] += Fb[a];
+            Rb[a] = 0.0;
+        }
         if (k == 0) {
-            Fnb[0] += Fkb[0];
-            Fnb[1] += Fkb[1];
-            Rb[0] = Rb[1] = 0.0;
+#pragma unroll
+            for (int a = 0; a < D; ++a) Fnb[a] += Fb[a];
         } else {
-            SampleD s;
+            Point<D, kYee> p;
+            Smp s;
             LocalD L;
-            local_again<kYee>(acc, keep, 1 + k, pc, K, Rk[k][0], Rk[k][1], s, L);
+            sample_at(acc, pc, Rk[k], p);
+            to_sample(p, s);
+            local_fields(s.E, s.B, K, L);
             LocalBar Lb;
-            zero(Lb);
-            drift_vjp(L, upn, mu, inv_qm, curv, K, Fkb, Lb, upnb, mub);
-            double nb[2] = {0.0, 0.0};
-            local_bar_to_position<kYee>(acc, sink, pc, K, s, Rk[k][0], Rk[k][1], Lb, nb[0],
-                                        nb[1]);
-            Rb[0] = nb[0];
-            Rb[1] = nb[1];
+            SampleBar<D> sb;
+            drift_back<D>(s, L, pc, upn, mu, inv_qm, curv, K, Fb, Lb, sb, upnb, mub);
+            local_back<D>(s, L, K, Lb, sb);
+            point_back<D, kYee>(win, pc, Rk[k], p, sb, Rb);
         }
     }
 
     // 3.-2. drift at R^n and the parallel update
     double uparb = 0.0;
     {
-        SampleD s;
+        Point<D, kYee> p;
+        Smp s;
         LocalD L;
-        local_again<kYee>(acc, keep, 1, pc, K, x, y, s, L);
+        sample_at(acc, pc, st, p);
+        to_sample(p, s);
+        local_fields(s.E, s.B, K, L);
+        if (curv) curvature_scalars_dir(s, K, L);
         LocalBar Lb;
-        zero(Lb);
-        drift_vjp(L, upn, mu, inv_qm, curv, K, Fnb, Lb, upnb, mub);
-        parallel_vjp(L, upar, mu, qm, curv, K, upnb, Lb, uparb, mub);
-        local_bar_to_position<kYee>(acc, sink, pc, K, s, x, y, Lb, xb, yb);
+        SampleBar<D> sb;
+        double Ab, Cb;
+        drift_back<D>(s, L, pc, upn, mu, inv_qm, curv, K, Fnb, Lb, sb, upnb, mub);
+        parallel_back(L, upar, mu, qm, curv, K, upnb, Lb, uparb, mub, Ab, Cb);
+        if (curv) scalars_back<D>(s, L, pc, K, Ab, Cb, Lb, sb);
+        local_back<D>(s, L, K, Lb, sb);
+        point_back<D, kYee>(win, pc, st, p, sb, xb);
     }
 
     // 1. decomposition at R^{n-1/2}
-    double uxb = 0.0, uyb = 0.0, uzb = 0.0, xpb = 0.0, ypb = 0.0;
     {
-        SampleD s;
+        Point<D, kYee> p;
+        Smp s;
         LocalD L;
-        local_again<kYee>(acc, keep, 0, pc, K, Rhx, Rhy, s, L);
+        sample_at(acc, pc, Rh, p);
+        to_sample(p, s);
+        local_fields(s.E, s.B, K, L);
         LocalBar Lb;
-        zero(Lb);
-        double upb[3] = {0.0, 0.0, 0.0};
-        if (nu > 0.0) {
-            const double d = (bp[0] * bpb[0] + bp[1] * bpb[1]) + bp[2] * bpb[2];
-            for (int i = 0; i < 3; ++i) upb[i] += (bpb[i] - bp[i] * d) / nu;
-        }
-        const double up2 = nu * nu;
-        const double up2b = mub * 0.5 * L.inv_B / L.kappa;
-        Lb.inv_B += mub * 0.5 * up2 / L.kappa;
-        Lb.kappa += -mub * mu / L.kappa;
-        for (int i = 0; i < 3; ++i) upb[i] += 2.0 * up[i] * up2b;
-        double gfb = 0.0, vcb[3];
-        const double u[3] = {ux, uy, uz};
-        double uvb[3] = {upb[0], upb[1], upb[2]};
+        SampleBar<D> sb;
+        const Gam<double> G = gamma_full2(u[0], u[1], u[2], K);
+        double vc[3] = {0.0, 0.0, 0.0}, up[3];
+        if (curv) v_curv_dir(L, s, upar, G.inv, inv_qm, K, vc);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) up[i] = (u[i] - upar * L.b[i]) - (L.vE[i] + vc[i]) * G.g;
+        const double up2 = dot3(up, up);
+        const double inv_nu = up2 > 0.0 ? rsqrt_nr(up2) : 0.0;
+        const double d = dot3(bp, bpb);
+        const double muk = mub * L.inv_kappa;
+        const double up2b = muk * (0.5 * L.inv_B);
+        Lb.inv_B += muk * (0.5 * up2);
+        Lb.kappa -= muk * mu;
+        double gfb = 0.0, igb = 0.0, vcb[3], uvb[3], upb[3];
+#pragma unroll
         for (int i = 0; i < 3; ++i) {
-            uparb += -L.b[i] * upb[i];
-            Lb.b[i] += -upar * upb[i];
-            Lb.vE[i] += -gf * upb[i];
-            vcb[i] = -gf * upb[i];
-            gfb += -(L.vE[i] + vch[i]) * upb[i];
+            upb[i] = (bpb[i] - bp[i] * d) * inv_nu + (2.0 * up2b) * up[i];
+            uparb -= L.b[i] * upb[i];
+            Lb.b[i] -= upar * upb[i];
+            vcb[i] = -G.g * upb[i];
+            Lb.vE[i] += vcb[i];
+            gfb -= (L.vE[i] + vc[i]) * upb[i];
         }
-        if (curv) vcurv_vjp(L, upar, gf, inv_qm, K, vcb, Lb, uparb, gfb);
+        if (curv) vcurv_back<D>(s, L, pc, upar, G.inv, inv_qm, K, vcb, Lb, sb, uparb, igb);
+        gfb -= igb * (G.inv * G.inv);
+#pragma unroll
         for (int i = 0; i < 3; ++i) {
-            uvb[i] += gfb * u[i] * K.inv_c2 / gf;
-            uvb[i] += uparb * L.b[i];
+            uvb[i] = (upb[i] + (gfb * K.inv_c2 * G.inv) * u[i]) + uparb * L.b[i];
             Lb.b[i] += uparb * u[i];
         }
-        double Rhb[2] = {0.0, 0.0};
-        local_bar_to_position<kYee>(acc, sink, pc, K, s, Rhx, Rhy, Lb, Rhb[0], Rhb[1]);
-        xb += 0.5 * Rhb[0];
-        yb += 0.5 * Rhb[1];
-        xpb += 0.5 * Rhb[0];
-        ypb += 0.5 * Rhb[1];
-        uxb = uvb[0];
-        uyb = uvb[1];
-        uzb = uvb[2];
+        local_back<D>(s, L, K, Lb, sb);
+        double Rhb[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) Rhb[a] = 0.0;
+        point_back<D, kYee>(win, pc, Rh, p, sb, Rhb);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+            lam[a] = xb[a] + 0.5 * Rhb[a];
+            lam[D + a] = 0.5 * Rhb[a];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) lam[2 * D + i] = uvb[i];
     }
-    lam[0] = xb;
-    lam[1] = yb;
-    lam[2] = xpb;
-    lam[3] = ypb;
-    lam[4] = uxb;
-    lam[5] = uyb;
-    lam[6] = uzb;
 }
 
 }  // namespace adj

@@ -1,0 +1,246 @@
+// Kernel of the reverse sweep, for D = 2 or 3 dimensions.
+//
+// A batch of steps is one launch.  Particles are independent, so a lane takes
+// a particle through all steps of the batch in reverse order with its cotangents
+// in registers; nothing but the start states and the decisions is read per step
+// and nothing written.  A workgroup takes the particles of one tile of a cell
+// sort (or a part of a crowded tile's) and keeps W^D nodes around the tile in
+// LDS: the fields, and the sums of the node cotangents, which are added to the
+// gradient grid once at the end.  The window reaches as far as a particle can
+// drift in the batch; what falls outside all the same goes to the grid directly.
+//
+// Node sums in binary64, because the LDS adds those at full speed and binary32
+// ones lane by lane: a wavefront's ds_add_f32 holds the LDS for 194 cycles
+// wherever its addresses lie, ds_add_f64 for 12 (consecutive) to 22 (random).
+// With binary32 sums the 2D sweep below took 20.5 ms instead of 6.3.
+// Device-scope atomics, some 2e10 per second, are slower again: hence the window.
+//
+// Bound by the LDS (65 % busy: 24 adds and 16 loads per point and 17 points a
+// step in 2D) with two wavefronts per SIMD to hide its latency: 256 registers
+// and the window leave room for no more.  In 3D fewer particles fit a window's
+// tile (225 at one per cell) than fill the wavefronts: 41 %.
+//   2D, 1e6 particles, 1024^2, 32 steps, K = 4: 5.9 ms, 2.0 TB/s; the whole
+//   backward 35.1 -> 10.3 ms (before: a launch per step and regime with global
+//   gathers, records of the cotangents to memory, and their scatter).
+//   3D, 3e5 particles, 64^3, 8 steps: 1.65 ms; training step 8.6 -> 4.7 ms.
+// Tiles of 32 in a window of 40 (2D; 28: 11.4 ms, 30: 10.7, 32: 10.3; two
+// workgroups of four wavefronts with windows of 28: 10.5) and of 6 in 11 (3D;
+// 5: 5.7 ms, 6: 4.7, 7: 5.1).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "gcb_adjoint.hpp"
+#include "gcb_internal.h"
+#include "gcb_queues.hpp"
+
+namespace gcb {
+namespace adj {
+
+// Node cotangents: W^D nodes of six components in LDS, a plane per component,
+// covering global nodes [o, o + W) per axis (periodic).
+template <int D>
+struct Window {
+    static constexpr int W = kAdjWindow<D>;
+    static constexpr int kPlane = D == 2 ? W * W : W * W * W;
+    double* lds;
+    float* grad;   // node-interleaved grid
+    int o[D], n[D];
+
+    __device__ void node(int k, const int c[D], double v) const {
+        int e = 0;
+        bool in = true;
+#pragma unroll
+        for (int a = D - 1; a >= 0; --a) {
+            int d = c[a] - o[a];
+            if ((unsigned)d >= (unsigned)W) d += d < 0 ? n[a] : -n[a];
+            in = in && (unsigned)d < (unsigned)W;
+            e = e * W + d;
+        }
+        if (in) {
+            atomicAdd(lds + k * kPlane + e, v);
+        } else {
+            size_t g = 0;
+#pragma unroll
+            for (int a = D - 1; a >= 0; --a) g = g * n[a] + wrap_index(c[a], n[a]);
+            atomicAdd(grad + g * 6 + k, (float)v);
+        }
+    }
+
+    template <bool kYee>
+    __device__ void add(const typename Dim<D>::Push& pc, const double X[D],
+                        const Point<D, kYee>& p, const SampleBar<D>& sb) const {
+        constexpr int kC = 1 << D;
+        if (__builtin_expect(p.in, 1)) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                double q[kC];
+                nodes_back(p, sb, k, q);
+                double* w = lds + k * kPlane + p.off[k];
+#pragma unroll
+                for (int c = 0; c < kC; ++c)
+                    atomicAdd(w + (c & 1) + ((c >> 1) & 1) * W + (D == 3 ? (c >> 2) * W * W : 0),
+                              q[c]);
+            }
+        } else {
+            // a stencil at the window's edge or beyond: node by node
+            Point<D, kYee> t;
+            int cell[D][Point<D, kYee>::kSets];
+            place<D>(pc, X, cell, t);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                double q[kC];
+                nodes_back(p, sb, k, q);
+#pragma unroll 1
+                for (int c = 0; c < kC; ++c) {
+                    int i[D];
+#pragma unroll
+                    for (int a = 0; a < D; ++a) i[a] = cell[a][p.entry(k, a)] + ((c >> a) & 1);
+                    double v = q[0];
+#pragma unroll
+                    for (int b = 1; b < kC; ++b) v = c == b ? q[b] : v;
+                    if (v != 0.0) node(k, i, v);
+                }
+            }
+        }
+    }
+};
+
+// One workgroup per chunk of a tile's particles (chunk c of the launch: tile
+// t with starts[t] <= c < starts[t+1], particles [c - starts[t]] * part of the
+// tile's), for the steps [s_lo, s_hi) of a segment, last to first.  Slot p of
+// the sort is particle perm[p]; rec holds the start states of all the segment's
+// steps, S their decisions.
+template <int D, bool kYee>
+__global__ __launch_bounds__(kAdjWG) __attribute__((amdgpu_waves_per_eu(2))) void
+k_adjoint_batch(const double* __restrict__ rec, const double* __restrict__ qm_arr,
+                const uint8_t* __restrict__ S, const uint32_t* __restrict__ perm,
+                const int32_t* __restrict__ tile_start, const int32_t* __restrict__ starts,
+                int ntx, int nty, int ntiles, int tile, int part, double* lam, int64_t n,
+                int s_lo, int s_hi, const double* __restrict__ F, typename Dim<D>::Push pc,
+                float* grad) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int wave_g[kAdjWG / 64];
+    __shared__ int wave_b[kAdjWG / 64];
+    __shared__ int next_slice;
+    constexpr int kL = 2 * D + 3;
+    constexpr int W = Window<D>::W;
+    constexpr int kAll = 6 * Window<D>::kPlane;
+    double* F_lds = reinterpret_cast<double*>(smem);
+    double* win_lds = F_lds + kAll;
+    uint16_t* queue = reinterpret_cast<uint16_t*>(win_lds + kAll);
+
+    // consecutive chunks on the same XCD (workgroup b runs on XCD b % 8)
+    const int total = starts[ntiles];
+    const int per = (total + 7) / 8;
+    const int chunk = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    if ((int)(blockIdx.x / 8) >= per || chunk >= total) return;
+    int t0 = 0, t1 = ntiles;   // starts[t0] <= chunk < starts[t1]
+    while (t1 - t0 > 1) {
+        const int m = (t0 + t1) >> 1;
+        if (starts[m] <= chunk) t0 = m; else t1 = m;
+    }
+    const int p0 = tile_start[t0] + (chunk - starts[t0]) * part;
+    const int p1 = min(tile_start[t0 + 1], p0 + part);
+    const int m = p1 - p0;
+
+    Window<D> win;
+    win.lds = win_lds;
+    win.grad = grad;
+    const int tc[3] = {t0 % ntx, D == 2 ? t0 / ntx : (t0 / ntx) % nty, t0 / (ntx * nty)};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        win.o[a] = tc[a] * tile - (W - tile) / 2;
+        win.n[a] = Dim<D>::nodes(pc, a);
+    }
+    const typename Dim<D>::Acc acc = Dim<D>::acc(F_lds, F, pc, win.o, W);
+
+    // stage the fields: a row of W records (6 W values, contiguous in the
+    // node-interleaved array) per wavefront
+    constexpr int kRows = kAll / (6 * W);
+    for (int row = threadIdx.x >> 6; row < kRows; row += kAdjWG / 64) {
+        size_t g = wrap_index(win.o[1] + row % W, win.n[1]);
+        if (D == 3) g += (size_t)wrap_index(win.o[D - 1] + row / W, win.n[D - 1]) * win.n[1];
+        const double* src = F + g * win.n[0] * 6;
+        for (int e = threadIdx.x & 63; e < 6 * W; e += 64) {
+            const int c = e / 6, k = e - 6 * c;
+            const double v = src[wrap_index(win.o[0] + c, win.n[0]) * 6 + k];
+            if constexpr (D == 2)
+                F_lds[window_elem<double>(k, row * W + c, W * W)] = v;
+            else
+                F_lds[(k * kRows + row) * W + c] = v;
+        }
+    }
+    for (int e = threadIdx.x; e < kAll; e += kAdjWG) win_lds[e] = 0.0;
+    if (threadIdx.x == 0) next_slice = 0;
+    // particles of the same regime to the same wavefronts, as in the push
+    const uint8_t* Slast = S + (size_t)(s_hi - 1) * n;
+    const int nG = split_queues<kAdjWG>(m, queue, wave_g, wave_b,
+                                        [&](int q) { return Slast[perm[p0 + q]] == 0; });
+    __syncthreads();
+
+    const typename Dim<D>::Const K = Dim<D>::consts(pc);
+    const int lane = threadIdx.x & 63;
+    const int sG = (nG + 63) >> 6;
+    const int sAll = sG + ((m - nG + 63) >> 6);
+    for (;;) {
+        int sl = 0;
+        if (lane == 0) sl = atomicAdd(&next_slice, 1);
+        sl = __builtin_amdgcn_readfirstlane(sl);
+        if (sl >= sAll) break;
+        const bool gslice = sl < sG;
+        const int q = gslice ? sl * 64 + lane : nG + (sl - sG) * 64 + lane;
+        if (q < (gslice ? nG : m)) {
+            const int64_t p = perm[p0 + queue[q]];
+            const double qm = qm_arr ? qm_arr[p] : Dim<D>::base(pc).qm;
+            double l[kL];
+#pragma unroll
+            for (int c = 0; c < kL; ++c) l[c] = lam[c * n + p];
+            for (int s = s_hi - 1; s >= s_lo; --s) {
+                const double* r = rec + (size_t)s * kL * n + p;
+                double st[kL];
+#pragma unroll
+                for (int c = 0; c < kL; ++c) st[c] = r[c * n];
+                if (S[(size_t)s * n + p] == 0)
+                    gca_vjp<D, kYee>(acc, win, pc, K, st, qm, l);
+                else
+                    boris_vjp<D, kYee>(acc, win, pc, K, st, qm, l);
+            }
+#pragma unroll
+            for (int c = 0; c < kL; ++c) lam[c * n + p] = l[c];
+        }
+    }
+    __syncthreads();
+    // the window to the grid, the values of a row of nodes by neighbouring lanes
+    for (int row = threadIdx.x >> 6; row < kRows; row += kAdjWG / 64) {
+        size_t g = wrap_index(win.o[1] + row % W, win.n[1]);
+        if (D == 3) g += (size_t)wrap_index(win.o[D - 1] + row / W, win.n[D - 1]) * win.n[1];
+        float* dst = grad + g * win.n[0] * 6;
+        for (int e = threadIdx.x & 63; e < 6 * W; e += 64) {
+            const int c = e / 6, k = e - 6 * c;
+            const double v = win_lds[(k * kRows + row) * W + c];
+            if (v != 0.0) atomicAdd(dst + wrap_index(win.o[0] + c, win.n[0]) * 6 + k, (float)v);
+        }
+    }
+}
+
+template <int D, bool kYee>
+hipError_t launch_batch(const AdjointLaunch& L, const typename Dim<D>::Push& pc,
+                        hipStream_t stream) {
+    auto kfn = k_adjoint_batch<D, kYee>;
+    constexpr size_t lds = adj_lds_bytes<D>();
+    hipError_t e = hipFuncSetAttribute((const void*)kfn,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    // at most one partly filled chunk per tile beside the full ones; the
+    // kernel deals them out in eight runs
+    const int64_t most = L.ntiles + L.n / L.part;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * ((most + 7) / 8))), dim3(kAdjWG), lds, stream,
+                       L.states, L.qm, L.strace, L.perm, L.tile_start, L.chunk_starts, L.ntx,
+                       L.nty, L.ntiles, kAdjTile<D>, L.part, L.lam, L.n, L.s_lo, L.s_hi,
+                       L.fields, pc, L.grad_fields);
+    return hipGetLastError();
+}
+
+}  // namespace adj
+}  // namespace gcb

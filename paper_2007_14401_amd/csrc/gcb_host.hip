@@ -88,7 +88,7 @@ struct gcb_ctx {
     DevBuf pscratch;     // sorted copy of the particle state
     DevBuf stats;        // DevStats + flagged counter
     DevBuf ke_partial;
-    DevBuf adj_states, adj_lam, adj_grad, adj_trace, adj_work, adj_samples, adj_lists;
+    DevBuf adj_states, adj_lam, adj_grad, adj_trace, adj_work, adj_chunks;
     DevBuf adj_order;    // tile order of a backward segment: q/m and the permutation
     // fixed scratch of gcb_push_noalloc on this context's device (the address
     // of the file-scope array `scratch` there); while `arena` is set, every
@@ -430,33 +430,28 @@ PushConst3 make_const3(const gcb_ctx* ctx, const gcb_params* prm) {
     return pc;
 }
 
-// Steps whose gather-point records one adjoint scatter takes: more steps
-// merge more of a particle's points per atomic (2D: 13.2 ms per step backward
-// at 1e7 particles with 8, 12.5 ms with 32), within a budget of record bytes
-// (at most half the device memory free when the backward starts).  The 3D
-// scatter's windows move more often over long batches (24.9 ms per step with
-// 6 steps, 26.6 with 27), so 3D keeps short ones.
-constexpr int kAdjMaxBatch = 32;
-constexpr size_t kAdjRecordBudget = 128ull << 30;
-// Tile edge (cells) of the order a 2D backward segment runs its particles in.
-#ifndef GCB_ADJ_ORDER_TILE
-#define GCB_ADJ_ORDER_TILE 32
-#endif
-constexpr int kAdjOrderTile = GCB_ADJ_ORDER_TILE;
-// The same for the 3D backward (cubic tiles).
-#ifndef GCB_ADJ3_ORDER_TILE
-#define GCB_ADJ3_ORDER_TILE 8
-#endif
-constexpr int kAdj3OrderTile = GCB_ADJ3_ORDER_TILE;
-constexpr int kAdj3MaxBatch = 8;
-constexpr size_t kAdj3RecordBudget = 32ull << 30;
+// Steps per batch of the reverse sweep: as many as keep a particle, at c dt per
+// step, inside the window around the tile it is in halfway through (a stencil
+// reaches half a cell below the particle and one above), at least one; the
+// batches of a segment are of about the same length.
+template <int D>
+int adjoint_batch(const gcb_params* prm, double inv_min, int n_steps) {
+    constexpr int kBoth = kAdjWindow<D> - kAdjTile<D>;
+    const double reach = std::min(kBoth / 2 - 0.5, kBoth - kBoth / 2 - 1.0);
+    const double per = std::fabs(prm->c * prm->dt) * inv_min;
+    // the points of a step reach half a step back
+    const double most = 2.0 * (reach / per - 0.5);
+    const int batch = most >= n_steps ? n_steps : std::max(1, (int)most);
+    const int batches = (n_steps + batch - 1) / batch;
+    return (n_steps + batches - 1) / batches;
+}
 
-// the record budget of a backward call: the fixed one, capped by half the
-// free device memory
-size_t record_budget(size_t fixed) {
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return fixed;
-    return std::min(fixed, free_b / 2);
+// Particles per chunk of the reverse sweep: a tile's own where there are tiles
+// enough to fill the device, smaller parts of crowded tiles where there are not
+// (two chunks per compute unit in all), of a wavefront at least.
+int adjoint_part(int64_t n) {
+    const int64_t part = (n / 512 + 63) / 64 * 64;
+    return (int)std::max<int64_t>(64, std::min<int64_t>(part, kAdjPart));
 }
 
 // Halo of the LDS window in nodes: the drift bound c dt per step over the
@@ -869,7 +864,7 @@ void gcb_destroy(gcb_ctx* ctx) {
                       &ctx->sort_idx2,  &ctx->sort_hist,  &ctx->sort_scan,
                       &ctx->tile_start, &ctx->pscratch,   &ctx->stats,     &ctx->ke_partial,
                       &ctx->adj_states, &ctx->adj_lam,    &ctx->adj_grad,  &ctx->adj_trace,
-                      &ctx->adj_work,   &ctx->adj_samples, &ctx->adj_lists, &ctx->adj_order,
+                      &ctx->adj_work,   &ctx->adj_chunks, &ctx->adj_order,
                       &ctx->gr_fields,
                       &ctx->gr_dl,
                       &ctx->gr_pscratch, &ctx->fields3};
@@ -999,28 +994,16 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
     const size_t nodes = (size_t)ctx->nx * ctx->ny;
     if ((rc = ensure(ctx, ctx->adj_states, (size_t)n_steps * 7 * nd))) return rc;
     if ((rc = ensure(ctx, ctx->adj_trace, (size_t)n_steps * n))) return rc;
-    // guiding-center lists of every step (uint32 per particle and step) and
-    // their lengths
-    if ((rc = ensure(ctx, ctx->adj_lists, (size_t)n_steps * (n + 1) * sizeof(uint32_t))))
-        return rc;
     if ((rc = ensure(ctx, ctx->adj_lam, 7 * nd))) return rc;
     if ((rc = ensure(ctx, ctx->adj_work, 7 * nd + (size_t)n))) return rc;
     if ((rc = ensure(ctx, ctx->adj_grad, nodes * 6 * sizeof(float)))) return rc;
-    // gather-point records of up to kMaxBatch steps, within the record budget
-    constexpr int kMaxBatch = kAdjMaxBatch;
-    const size_t budget = record_budget(kAdjRecordBudget);
-    const size_t per_step = adjoint_record_bytes(n, prm->n_iter, 1);
-    int batch = per_step > 0 ? (int)std::min<size_t>(kMaxBatch, budget / per_step) : 1;
-    batch = std::max(1, std::min(batch, std::max(1, (int)n_steps)));
-    if ((rc = ensure(ctx, ctx->adj_samples, adjoint_record_bytes(n, prm->n_iter, batch))))
-        return rc;
     // The segment runs on its particles in the tile order of their start
-    // positions (kAdjOrderTile-cell tiles): the state, q/m and the adjoint
+    // positions (the reverse sweep's tiles): the state, q/m and the adjoint
     // are permuted on the way in and the adjoint back on the way out.  Each
     // particle's arithmetic is its own, so the order changes no value; the
-    // reverse kernels' gathers of neighbouring lanes then share cache lines.
+    // reverse sweep's reads of a tile's states then share cache lines.
     TileGeom og{};
-    og.tile = kAdjOrderTile;
+    og.tile = kAdjTile<2>;
     og.ntx = (ctx->nx + og.tile - 1) / og.tile;
     og.nty = (ctx->ny + og.tile - 1) / og.tile;
     const bool ordered = n > 0 && n_steps > 0;
@@ -1091,14 +1074,6 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
         ctx->timing = timing;
         if (rc) return rc;
     }
-    // per-step guiding-center lists, so that their reverse kernel runs full
-    // wavefronts
-    uint32_t* lists = static_cast<uint32_t*>(ctx->adj_lists.ptr);
-    unsigned* counts = reinterpret_cast<unsigned*>(lists + (size_t)n_steps * n);
-    if (n > 0 && n_steps > 0) {
-        GCB_HIP(hipMemsetAsync(counts, 0, (size_t)n_steps * sizeof(unsigned), stream));
-        GCB_HIP(launch_gca_lists(trace, n, n_steps, lists, counts, stream));
-    }
     // reverse sweep
     for (int c = 0; c < 7 && n > 0; ++c) {
         if (perm)
@@ -1108,27 +1083,40 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
                                    stream));
     }
     GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(float), stream));
-    // steps in reverse order, in batches [s_lo, s_hi) of at most `batch` steps:
-    // the vector-Jacobian products of the batch's steps, then one scatter
-    for (int32_t s_hi = n_steps; s_hi > 0 && n > 0; s_hi -= batch) {
-        const int32_t s_lo = std::max<int32_t>(0, s_hi - batch);
+    // steps in reverse order, in batches [s_lo, s_hi), the particles sorted by
+    // their positions halfway
+    if (ordered) {
+        const int batch = adjoint_batch<2>(prm, std::max(1.0 / ctx->dx, 1.0 / ctx->dy), n_steps);
+        const int ntiles = og.ntx * og.nty;
+        SortBuffers ssb{};
+        if ((rc = prepare_sort(ctx, n, ntiles, ssb))) return rc;
+        if ((rc = ensure(ctx, ctx->adj_chunks, (size_t)(ntiles + 1) * 4))) return rc;
         AdjointLaunch A;
         A.yee = ctx->yee;
         A.fields = static_cast<const double*>(ctx->fields.ptr);
         A.n = n;
+        A.states = states;
         A.qm = wqm;
+        A.strace = trace;
+        A.perm = ssb.idx;
+        A.tile_start = ssb.tile_start;
+        A.ntx = og.ntx;
+        A.nty = og.nty;
+        A.ntiles = ntiles;
+        A.part = adjoint_part(n);
+        A.chunk_starts = static_cast<int32_t*>(ctx->adj_chunks.ptr);
+        A.lam = lam;
         A.grad_fields = grad;
-        A.records = ctx->adj_samples.ptr;
-        A.batch = batch;
-        for (int32_t s = s_hi - 1; s >= s_lo; --s) {
-            A.state = states + (size_t)s * 7 * n;
-            A.strace = trace + (size_t)s * n;
-            A.list = lists + (size_t)s * n;
-            A.count = counts + s;
-            A.batch_slot = s - s_lo;
-            GCB_HIP(launch_adjoint_step(A, lam, pc, stream));
+        for (int32_t s_hi = n_steps; s_hi > 0; s_hi -= batch) {
+            A.s_hi = s_hi;
+            A.s_lo = std::max<int32_t>(0, s_hi - batch);
+            const double* at = states + (size_t)((A.s_lo + s_hi) / 2) * 7 * n;
+            GCB_HIP(launch_cell_sort(at, at + n, n, 1.0 / ctx->dx, 1.0 / ctx->dy, og, ssb,
+                                     stream));
+            GCB_HIP(launch_chunk_starts(A.tile_start, ntiles, A.part,
+                                        static_cast<int32_t*>(ctx->adj_chunks.ptr), stream));
+            GCB_HIP(launch_adjoint_batch(A, pc, stream));
         }
-        GCB_HIP(launch_adjoint_scatter(A, trace + (size_t)s_lo * n, s_hi - s_lo, pc, stream));
     }
     for (int c = 0; c < 7 && n > 0; ++c) {
         if (perm)
@@ -1448,22 +1436,13 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
     const size_t nodes = (size_t)ctx->n3[0] * ctx->n3[1] * ctx->n3[2];
     if ((rc = ensure(ctx, ctx->adj_states, (size_t)n_steps * kS * nd))) return rc;
     if ((rc = ensure(ctx, ctx->adj_trace, (size_t)n_steps * n))) return rc;
-    if ((rc = ensure(ctx, ctx->adj_lists, (size_t)n_steps * (n + 1) * sizeof(uint32_t))))
-        return rc;
     if ((rc = ensure(ctx, ctx->adj_lam, kS * nd))) return rc;
     if ((rc = ensure(ctx, ctx->adj_work, kS * nd + (size_t)n))) return rc;
     if ((rc = ensure(ctx, ctx->adj_grad, nodes * 6 * sizeof(float)))) return rc;
-    constexpr int kMaxBatch = kAdj3MaxBatch;
-    const size_t budget = record_budget(kAdj3RecordBudget);
-    const size_t per_step = adjoint3_record_bytes(n, prm->n_iter, 1);
-    int batch = per_step > 0 ? (int)std::min<size_t>(kMaxBatch, budget / per_step) : 1;
-    batch = std::max(1, std::min(batch, std::max(1, (int)n_steps)));
-    if ((rc = ensure(ctx, ctx->adj_samples, adjoint3_record_bytes(n, prm->n_iter, batch))))
-        return rc;
     // the segment's particles in the tile order of their start positions, as
-    // in the 2D backward (cubic kAdj3OrderTile-cell tiles)
+    // in the 2D backward (cubic tiles)
     TileGeom3 og{};
-    og.tile = kAdj3OrderTile;
+    og.tile = kAdjTile<3>;
     og.ntx = (ctx->n3[0] + og.tile - 1) / og.tile;
     og.nty = (ctx->n3[1] + og.tile - 1) / og.tile;
     og.ntz = (ctx->n3[2] + og.tile - 1) / og.tile;
@@ -1559,12 +1538,6 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
         L.steps = 1;
         GCB_HIP(launch_push3_f64(L, w, w, pc, stream));
     }
-    uint32_t* lists = static_cast<uint32_t*>(ctx->adj_lists.ptr);
-    unsigned* counts = reinterpret_cast<unsigned*>(lists + (size_t)n_steps * n);
-    if (n > 0 && n_steps > 0) {
-        GCB_HIP(hipMemsetAsync(counts, 0, (size_t)n_steps * sizeof(unsigned), stream));
-        GCB_HIP(launch_gca_lists(trace, n, n_steps, lists, counts, stream));
-    }
     // reverse sweep
     for (int c = 0; c < kS && n > 0; ++c) {
         if (perm)
@@ -1574,25 +1547,40 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
                                    stream));
     }
     GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(float), stream));
-    for (int32_t s_hi = n_steps; s_hi > 0 && n > 0; s_hi -= batch) {
-        const int32_t s_lo = std::max<int32_t>(0, s_hi - batch);
-        Adjoint3Launch A;
+    if (ordered) {
+        const double inv_min =
+            std::max(1.0 / ctx->d3[0], std::max(1.0 / ctx->d3[1], 1.0 / ctx->d3[2]));
+        const int batch = adjoint_batch<3>(prm, inv_min, n_steps);
+        const int ntiles = og.ntx * og.nty * og.ntz;
+        SortBuffers ssb{};
+        if ((rc = prepare_sort(ctx, n, ntiles, ssb))) return rc;
+        if ((rc = ensure(ctx, ctx->adj_chunks, (size_t)(ntiles + 1) * 4))) return rc;
+        AdjointLaunch A;
         A.yee = ctx->yee3;
         A.fields = static_cast<const double*>(ctx->fields3.ptr);
         A.n = n;
+        A.states = states;
         A.qm = wqm;
+        A.strace = trace;
+        A.perm = ssb.idx;
+        A.tile_start = ssb.tile_start;
+        A.ntx = og.ntx;
+        A.nty = og.nty;
+        A.ntiles = ntiles;
+        A.part = adjoint_part(n);
+        A.chunk_starts = static_cast<int32_t*>(ctx->adj_chunks.ptr);
+        A.lam = lam;
         A.grad_fields = grad;
-        A.records = ctx->adj_samples.ptr;
-        A.batch = batch;
-        for (int32_t s = s_hi - 1; s >= s_lo; --s) {
-            A.state = states + (size_t)s * kS * n;
-            A.strace = trace + (size_t)s * n;
-            A.list = lists + (size_t)s * n;
-            A.count = counts + s;
-            A.batch_slot = s - s_lo;
-            GCB_HIP(launch_adjoint3_step(A, lam, pc, stream));
+        for (int32_t s_hi = n_steps; s_hi > 0; s_hi -= batch) {
+            A.s_hi = s_hi;
+            A.s_lo = std::max<int32_t>(0, s_hi - batch);
+            const double* at = states + (size_t)((A.s_lo + s_hi) / 2) * kS * n;
+            GCB_HIP(launch_cell_sort3(at, at + n, at + 2 * n, n, 1.0 / ctx->d3[0],
+                                      1.0 / ctx->d3[1], 1.0 / ctx->d3[2], og, ssb, stream));
+            GCB_HIP(launch_chunk_starts(A.tile_start, ntiles, A.part,
+                                        static_cast<int32_t*>(ctx->adj_chunks.ptr), stream));
+            GCB_HIP(launch_adjoint3_batch(A, pc, stream));
         }
-        GCB_HIP(launch_adjoint3_scatter(A, trace + (size_t)s_lo * n, s_hi - s_lo, pc, stream));
     }
     for (int c = 0; c < kS && n > 0; ++c) {
         if (perm)

@@ -163,68 +163,49 @@ hipError_t launch_sincos(const double* x, double* s, double* c, int64_t n,
 // ---------------------------------------------------------------------------
 // adjoint
 
+// Reverse sweep: threads and most particles of a workgroup, and the edges of
+// its LDS window (nodes) and of its tile (cells) in 2D and 3D.
+constexpr int kAdjWG = 512;
+constexpr int kAdjPart = 2048;
+template <int D>
+constexpr int kAdjWindow = D == 2 ? 40 : 11;
+template <int D>
+constexpr int kAdjTile = D == 2 ? 32 : 6;
+template <int D>
+constexpr size_t adj_lds_bytes() {
+    return (size_t)6 * kAdjWindow<D> * kAdjWindow<D> * (D == 3 ? kAdjWindow<D> : 1) *
+               2 * sizeof(double) + kAdjPart * sizeof(uint16_t);
+}
+static_assert(adj_lds_bytes<2>() + 1024 <= 160 * 1024 && adj_lds_bytes<3>() + 1024 <= 160 * 1024,
+              "the window of the reverse sweep has to fit in LDS");
+
+// One batch of the reverse sweep: the steps [s_lo, s_hi) of a segment.
 struct AdjointLaunch {
     bool yee;
-    const double* fields;   // node-interleaved binary64
+    const double* fields;         // node-interleaved binary64
     int64_t n;
-    const double* state;    // the step's saved start state: 7 arrays of n (x,y,xp,yp,ux,uy,uz)
-    const double* qm;       // nullable
-    const uint8_t* strace;  // per-particle S of this step (1 = Boris)
-    const uint32_t* list;   // this step's guiding-center list (launch_gca_lists)
-    const unsigned* count;  // its length
-    float* grad_fields;     // node-interleaved float gradient accumulators
-    void* records;          // adjoint_record_bytes(n, n_iter, batch) of scratch
-    int batch;              // steps whose gather points the records hold
-    int batch_slot;         // this step's place in the batch
+    const double* states;         // the segment's start states, step by step (7 or 9 arrays of n)
+    const double* qm;             // nullable
+    const uint8_t* strace;        // the segment's decisions, step by step (1 = Boris)
+    const uint32_t* perm;         // cell sort of the particles: slot -> particle
+    const int32_t* tile_start;    // its tiles (ntx x nty (x ntz), kAdjTile cells)
+    int ntx, nty, ntiles;
+    int part;                     // particles per chunk, at most kAdjPart
+    const int32_t* chunk_starts;  // launch_chunk_starts
+    double* lam;                  // 7 or 9 arrays of n: cotangents, in place
+    int s_lo, s_hi;
+    float* grad_fields;           // node-interleaved gradient accumulators
 };
 
-// gather points recorded per particle and guiding-center step
-int adjoint_slots(int n_iter);
-size_t adjoint_record_bytes(int64_t n, int n_iter, int steps);
-
-// One step of the reverse sweep: lam (7*n, in/out) from the cotangents of
-// the step's outputs to those of its inputs; the step's gather points go to
-// batch slot L.batch_slot of the records.
-hipError_t launch_adjoint_step(const AdjointLaunch& L, double* lam /*7*n in/out*/,
-                               const PushConst& pc, hipStream_t stream);
-
-// Guiding-center lists of n_steps steps from their switch traces (trace:
-// n_steps*n, 0 = guiding center): for step s, lists[s*n + t] for
-// t < counts[s].  counts (n_steps) must be zero on entry.
-hipError_t launch_gca_lists(const uint8_t* trace, int64_t n, int n_steps, uint32_t* lists,
-                            unsigned* counts, hipStream_t stream);
-
-// Node cotangents of the first nb batch slots into L.grad_fields; strace_first
-// is the switch trace of the step in slot 0 (the later slots follow at
-// strides of n).
-hipError_t launch_adjoint_scatter(const AdjointLaunch& L, const uint8_t* strace_first, int nb,
-                                  const PushConst& pc, hipStream_t stream);
+// starts[t] (ntiles + 1): chunks of `part` particles in the tiles before t
+hipError_t launch_chunk_starts(const int32_t* tile_start, int ntiles, int part, int32_t* starts,
+                               hipStream_t stream);
+hipError_t launch_adjoint_batch(const AdjointLaunch& L, const PushConst& pc, hipStream_t stream);
+hipError_t launch_adjoint3_batch(const AdjointLaunch& L, const PushConst3& pc,
+                                 hipStream_t stream);
 
 hipError_t launch_deinterleave_add(const float* grad_fields, int nx, int ny,
                                    float* const out[6], hipStream_t stream);
-
-// 3D adjoint (gcb_adjoint3.hip): the 2D organisation with 9-array states
-// (x, y, z, xp, yp, zp, ux, uy, uz) and 3D gather points.
-struct Adjoint3Launch {
-    bool yee;               // 3D Yee offsets
-    const double* fields;   // node-interleaved binary64 3D fields
-    int64_t n;
-    const double* state;    // the step's saved start state: 9 arrays of n
-    const double* qm;       // nullable
-    const uint8_t* strace;  // per-particle S of this step (1 = Boris)
-    const uint32_t* list;   // this step's guiding-center list
-    const unsigned* count;  // its length
-    float* grad_fields;     // node-interleaved float gradient accumulators
-    void* records;          // adjoint3_record_bytes(n, n_iter, batch) of scratch
-    int batch;
-    int batch_slot;
-};
-
-size_t adjoint3_record_bytes(int64_t n, int n_iter, int steps);
-hipError_t launch_adjoint3_step(const Adjoint3Launch& L, double* lam /*9*n in/out*/,
-                                const PushConst3& pc, hipStream_t stream);
-hipError_t launch_adjoint3_scatter(const Adjoint3Launch& L, const uint8_t* strace_first, int nb,
-                                   const PushConst3& pc, hipStream_t stream);
 
 // curved-spacetime push (gcb_gr.hip)
 struct GrPtrs {
