@@ -1265,7 +1265,8 @@ int gcb_push_gr(gcb_ctx* ctx, gcb_gr_particles* p, const gcb_params* prm, int32_
         const size_t ub = prm->form == GCB_FORM_F64 ? sizeof(double) : sizeof(float);
         SortBuffers sb;
         int rc;
-        if ((rc = prepare_sort(ctx, n, 1, sb))) return rc;
+        const int ntiles = ((g.nr + kGrTile - 1) / kGrTile) * ((g.nth + kGrTile - 1) / kGrTile);
+        if ((rc = prepare_sort(ctx, n, ntiles, sb))) return rc;
         const size_t bytes = (size_t)n * (3 * sizeof(double) + 3 * ub + sizeof(double) +
                                           sizeof(int32_t) + 1);
         if ((rc = ensure(ctx, ctx->gr_pscratch, bytes))) return rc;

@@ -2,13 +2,26 @@
 // are contiguous (coalesced structure-of-arrays access) and the tiled push
 // kernel can stage one field window per workgroup.
 //
-// Pipeline (all on the caller's stream):
-//   k_tile_keys   key = tile index of (x, y); idx = slot
-//   LSD radix sort of (key, idx), 8 bits per pass, stable:
-//     k_radix_hist     per-block digit histogram, digit-major [256][nblocks]
-//     scan             exclusive scan of the histogram (3 kernels)
-//     k_radix_scatter  wave-level multisplit ranks -> stable scatter
-//   k_tile_bounds tile_start from the boundaries of the sorted keys
+// Pipeline (all on the caller's stream), stable.  Up to 256 tiles, or 65536
+// with at most kSelfScan blocks of 4096 particles:
+//   k_keys_hist    key = tile index; per block the histogram of the key's upper
+//                  digit (the bits above the lowest `low`, eight at most)
+//   k_scatter      (key, slot) into the buckets of the upper digit: wave-level
+//                  multisplit ranks; every block sums the histograms of the
+//                  blocks before it itself (more than kSelfScan of them take an
+//                  exclusive scan, 3 kernels)
+//   k_bucket_sort  a workgroup per bucket: counting sort by the low bits, which
+//                  also gives tile_start (with 256 tiles or fewer the scatter
+//                  does that, and is the last step)
+// Launches and their gaps are most of a sort of 1e5 particles, and the passes
+// over the keys of one of 1e6: two or three kernels where an LSD radix sort of
+// two digits has twelve (keys; histogram, scan, scatter of each digit; tile
+// bounds).  1e6 particles, 2704 tiles: 92 -> 35 us.  A bucket that holds far
+// more particles than the others is sorted by one workgroup, as its tiles are
+// pushed by one each.
+// Otherwise LSD radix sort, 8 bits per pass, and k_tile_bounds: with 256 buckets
+// of many particles each the bucket sort has too few wavefronts (1e7 particles,
+// 1024 (r, theta) tiles: 12.66 ms of a push with it, 12.44 without).
 // The push kernel of the sort's step then reads the state through idx (the
 // permutation) and writes it in tile order, so there is no permutation pass
 // (the same for the curved-spacetime and 3D states).
@@ -23,29 +36,11 @@ namespace gcb {
 namespace {
 
 constexpr int kSortWG = 256;
-constexpr int kItemsPerWave = 1024;
-constexpr int kItems = kItemsPerWave * (kSortWG / 64);   // 4096 per block
+constexpr int kGroups = 4;                 // of 64 particles per wavefront
+constexpr int kWaves = 16;                 // per block
+constexpr int kItems = kWaves * kGroups * 64;
 constexpr int kScanWG = 256;
 constexpr int kScanItems = 4096;                          // per block of the scan
-
-__global__ __launch_bounds__(kSortWG) void k_tile_keys(const double* __restrict__ x,
-                                                       const double* __restrict__ y,
-                                                       int64_t n, double inv_dx,
-                                                       double inv_dy, TileGeom g,
-                                                       uint32_t* keys, uint32_t* idx) {
-    const int64_t p = (int64_t)blockIdx.x * kSortWG + threadIdx.x;
-    if (p >= n) return;
-    const double gx = floor(x[p] * inv_dx);
-    const double gy = floor(y[p] * inv_dy);
-    // clamp into the tile range (non-finite positions land in tile 0)
-    int tx = (gx >= 0.0 && gx < 2.0e9) ? (int)gx / g.tile : 0;
-    int ty = (gy >= 0.0 && gy < 2.0e9) ? (int)gy / g.tile : 0;
-    tx = tx < g.ntx ? tx : g.ntx - 1;
-    ty = ty < g.nty ? ty : g.nty - 1;
-    const uint32_t key = (uint32_t)(ty * g.ntx + tx);
-    keys[p] = key;
-    idx[p] = (uint32_t)p;
-}
 
 // clamped tile coordinate of one position component (non-finite -> 0)
 __device__ __forceinline__ int tile_coord(double v, double inv_d, int tile, int nt) {
@@ -54,20 +49,68 @@ __device__ __forceinline__ int tile_coord(double v, double inv_d, int tile, int 
     return t < nt ? t : nt - 1;
 }
 
-__global__ __launch_bounds__(kSortWG) void k_tile_keys3(const double* __restrict__ x,
-                                                        const double* __restrict__ y,
-                                                        const double* __restrict__ z,
-                                                        int64_t n, double inv_dx,
-                                                        double inv_dy, double inv_dz,
-                                                        TileGeom3 g, uint32_t* keys,
-                                                        uint32_t* idx) {
-    const int64_t p = (int64_t)blockIdx.x * kSortWG + threadIdx.x;
-    if (p >= n) return;
-    const int tx = tile_coord(x[p], inv_dx, g.tile, g.ntx);
-    const int ty = tile_coord(y[p], inv_dy, g.tile, g.nty);
-    const int tz = tile_coord(z[p], inv_dz, g.tile, g.ntz);
-    keys[p] = (uint32_t)((tz * g.nty + ty) * g.ntx + tx);
-    idx[p] = (uint32_t)p;
+// The key of particle p: its tile, row-major.
+struct Key2 {
+    const double* x;
+    const double* y;
+    double inv_dx, inv_dy;
+    TileGeom g;
+    __device__ uint32_t operator()(int64_t p) const {
+        return (uint32_t)(tile_coord(y[p], inv_dy, g.tile, g.nty) * g.ntx +
+                          tile_coord(x[p], inv_dx, g.tile, g.ntx));
+    }
+};
+
+struct Key3 {
+    const double* x;
+    const double* y;
+    const double* z;
+    double inv_dx, inv_dy, inv_dz;
+    TileGeom3 g;
+    __device__ uint32_t operator()(int64_t p) const {
+        const int tx = tile_coord(x[p], inv_dx, g.tile, g.ntx);
+        const int ty = tile_coord(y[p], inv_dy, g.tile, g.nty);
+        const int tz = tile_coord(z[p], inv_dz, g.tile, g.ntz);
+        return (uint32_t)((tz * g.nty + ty) * g.ntx + tx);
+    }
+};
+
+// (r, theta) tile of the particle's grid cell
+struct KeyGr {
+    const double* r;
+    const double* th;
+    gr::GrConst g;
+    int tile, ntx;
+    __device__ uint32_t operator()(int64_t p) const {
+        int i, j;
+        double wx, wy;
+        gr::grid_cell(g, r[p], th[p], i, j, wx, wy);
+        return (uint32_t)((j / tile) * ntx + i / tile);
+    }
+};
+
+// Keys, and per block the histogram of their digits, digit-major (for the scan) or, kByBlock, block by block.
+template <bool kByBlock, class Key>
+__global__ __launch_bounds__(kWaves * 64) void k_keys_hist(Key key, int64_t n, int shift,
+                                                           int nblocks, uint32_t* keys,
+                                                           uint32_t* hist) {
+    __shared__ uint32_t h[256];
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t b0 = (int64_t)blockIdx.x * (kWaves * kGroups * 64);
+#pragma unroll
+    for (int gi = 0; gi < kGroups; ++gi) {
+        const int64_t p = b0 + gi * (kWaves * 64) + threadIdx.x;
+        if (p < n) {
+            const uint32_t k = key(p);
+            keys[p] = k;
+            atomicAdd(&h[(k >> shift) & 255u], 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 256)
+        hist[kByBlock ? (int64_t)blockIdx.x * 256 + threadIdx.x
+                      : (int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
 // tile_start[t] = first sorted slot whose key is >= t, for t in [0, ntiles]:
@@ -80,21 +123,6 @@ __global__ __launch_bounds__(kSortWG) void k_tile_bounds(const uint32_t* __restr
     const int lo = i == 0 ? -1 : (int)keys[i - 1];
     const int hi = i == n ? ntiles : (int)keys[i];
     for (int t = lo + 1; t <= hi; ++t) tile_start[t] = (int32_t)i;
-}
-
-// key = (r, theta) tile of the particle's grid cell, row-major tiles
-__global__ __launch_bounds__(kSortWG) void k_gr_tile_keys(const double* __restrict__ r,
-                                                          const double* __restrict__ th,
-                                                          int64_t n, gr::GrConst g, int tile,
-                                                          int ntx, uint32_t* keys,
-                                                          uint32_t* idx) {
-    const int64_t p = (int64_t)blockIdx.x * kSortWG + threadIdx.x;
-    if (p >= n) return;
-    int i, j;
-    double wx, wy;
-    gr::grid_cell(g, r[p], th[p], i, j, wx, wy);
-    keys[p] = (uint32_t)((j / tile) * ntx + i / tile);
-    idx[p] = (uint32_t)p;
 }
 
 __global__ __launch_bounds__(kSortWG) void k_radix_hist(const uint32_t* __restrict__ keys,
@@ -188,54 +216,130 @@ __global__ __launch_bounds__(kScanWG) void k_scan_down(const uint32_t* __restric
     }
 }
 
-__global__ __launch_bounds__(kSortWG) void k_radix_scatter(
-    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ idx, int64_t n, int shift,
-    int nblocks, const uint32_t* __restrict__ offsets, uint32_t* keys_out, uint32_t* idx_out) {
-    __shared__ uint32_t wcount[kSortWG / 64][256];
-    __shared__ uint32_t gbase[256];
+// exclusive scan of 256 values in LDS by one wavefront
+__device__ __forceinline__ void scan_256(uint32_t* v) {
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    for (int d = threadIdx.x; d < 256 * (kSortWG / 64); d += kSortWG)
-        (&wcount[0][0])[d] = 0;
-    gbase[threadIdx.x] = offsets[(int64_t)threadIdx.x * nblocks + blockIdx.x];
-    __syncthreads();
+    uint32_t c[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        c[i] = v[lane * 4 + i];
+        sum += c[i];
+    }
+    uint32_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = __shfl_up(inc, off);
+        inc += lane >= off ? t : 0u;
+    }
+    uint32_t run = inc - sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[lane * 4 + i] = run;
+        run += c[i];
+    }
+}
 
-    const int64_t w0 = (int64_t)blockIdx.x * kItems + (int64_t)wave * kItemsPerWave;
+// Rank of each of a wavefront's kGroups x 64 consecutive items (from w0, below
+// end) among the items of the same digit, given the counts so far in `count`
+// (256 of the wavefront's own, updated).
+__device__ __forceinline__ void wave_ranks(const uint32_t* __restrict__ keys, int64_t w0,
+                                           int64_t end, int shift, uint32_t mask, int bits,
+                                           uint32_t* count, uint32_t rank[kGroups],
+                                           uint32_t dig[kGroups]) {
+    const int lane = threadIdx.x & 63;
     const unsigned long long lt = (1ull << lane) - 1ull;
-    constexpr int kGroups = kItemsPerWave / 64;
-    uint32_t rank[kGroups];
-    uint32_t dig[kGroups];
-    // pass A: ranks within this wave's sub-range, in order
 #pragma unroll
     for (int gi = 0; gi < kGroups; ++gi) {
         const int64_t p = w0 + gi * 64 + lane;
-        const bool valid = p < n;
-        const uint32_t d = valid ? (keys[p] >> shift) & 255u : 0u;
-        unsigned long long peers = __ballot(valid);
+        dig[gi] = p < end ? (keys[p] >> shift) & mask : 0u;
+    }
 #pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
+    for (int gi = 0; gi < kGroups; ++gi) {
+        const bool valid = w0 + gi * 64 + lane < end;
+        const uint32_t d = dig[gi];
+        unsigned long long peers = __ballot(valid);
+        for (int bit = 0; bit < bits; ++bit) {
             const unsigned long long bal = __ballot(valid && ((d >> bit) & 1u));
             peers &= ((d >> bit) & 1u) ? bal : ~bal;
         }
         uint32_t before = 0;
-        if (valid) before = wcount[wave][d];
+        if (valid) before = count[d];
         // wave-synchronous: every lane has read the counter before the leader updates it
         __builtin_amdgcn_wave_barrier();
         if (valid) {
             const int leader = __ffsll((long long)peers) - 1;
-            if (lane == leader) wcount[wave][d] = before + (uint32_t)__popcll(peers);
+            if (lane == leader) count[d] = before + (uint32_t)__popcll(peers);
         }
         __builtin_amdgcn_wave_barrier();
         rank[gi] = before + (uint32_t)__popcll(peers & lt);
-        dig[gi] = d;
     }
+}
+
+// Stable scatter by one digit.  idx null: the slots are 0, 1, 2, ...;
+// keys_out null: not kept.  kSelf: hist holds the blocks' histograms
+// (k_keys_hist, by block), else their scan.  With `tile_start` the digit is the
+// key's upper one, and the buckets' starts are noted at their first tiles.
+template <bool kSelf>
+__global__ __launch_bounds__(kWaves * 64) void k_scatter(
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ idx, int64_t n, int shift,
+    int nblocks, const uint32_t* __restrict__ hist, uint32_t* keys_out, uint32_t* idx_out,
+    int32_t* tile_start, int ntiles) {
+    constexpr int kWG = kWaves * 64;
+    __shared__ uint32_t wcount[kWaves][256];
+    __shared__ uint32_t gbase[256];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    if constexpr (kSelf) {
+        // kWG / 256 threads per digit, each over its share of the blocks; the
+        // partial sums meet in wcount
+        constexpr int kParts = kWG / 256;
+        const int d = threadIdx.x & 255, part = threadIdx.x >> 8;
+        uint32_t before = 0, all = 0;
+#pragma unroll 16
+        for (int b = part; b < nblocks; b += kParts) {
+            const uint32_t v = hist[b * 256 + d];
+            before += b < (int)blockIdx.x ? v : 0u;
+            all += v;
+        }
+        wcount[part][d] = before;
+        wcount[kParts + part][d] = all;
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            before = all = 0;
+#pragma unroll
+            for (int i = 0; i < kParts; ++i) {
+                before += wcount[i][d];
+                all += wcount[kParts + i][d];
+            }
+            gbase[d] = all;
+        }
+        __syncthreads();
+        if (wave == 0) scan_256(gbase);
+        __syncthreads();
+        if (threadIdx.x < 256) gbase[d] += before;
+        __syncthreads();
+    } else if (threadIdx.x < 256) {
+        gbase[threadIdx.x] = hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+    }
+    if (tile_start && blockIdx.x == 0 && threadIdx.x < 256) {
+        const int64_t t = (int64_t)threadIdx.x << shift;
+        if (t < ntiles) tile_start[t] = (int32_t)gbase[threadIdx.x];
+        if (threadIdx.x == 0) tile_start[ntiles] = (int32_t)n;
+    }
+    for (int d = threadIdx.x; d < 256 * kWaves; d += kWG) (&wcount[0][0])[d] = 0;
+    __syncthreads();
+
+    const int64_t w0 = ((int64_t)blockIdx.x * kWaves + wave) * (kGroups * 64);
+    uint32_t rank[kGroups];
+    uint32_t dig[kGroups];
+    wave_ranks(keys, w0, n, shift, 255u, 8, wcount[wave], rank, dig);
     __syncthreads();
     // exclusive prefix of the per-wave counts, per digit
-    {
+    if (threadIdx.x < 256) {
         const int d = threadIdx.x;
-        uint32_t run = 0;
+        uint32_t run = gbase[d];
 #pragma unroll
-        for (int w = 0; w < kSortWG / 64; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             const uint32_t c = wcount[w][d];
             wcount[w][d] = run;
             run += c;
@@ -246,10 +350,65 @@ __global__ __launch_bounds__(kSortWG) void k_radix_scatter(
     for (int gi = 0; gi < kGroups; ++gi) {
         const int64_t p = w0 + gi * 64 + lane;
         if (p < n) {
-            const uint32_t d = dig[gi];
-            const uint32_t dst = gbase[d] + wcount[wave][d] + rank[gi];
-            keys_out[dst] = keys[p];
-            idx_out[dst] = idx[p];
+            const uint32_t dst = wcount[wave][dig[gi]] + rank[gi];
+            if (keys_out) keys_out[dst] = keys[p];
+            idx_out[dst] = idx ? idx[p] : (uint32_t)p;
+        }
+    }
+}
+
+// Counting sort of one bucket (the particles of the 2^low tiles from
+// blockIdx.x << low) by the low bits, and the starts of its tiles.
+constexpr int kBucketWG = 1024;
+__global__ __launch_bounds__(kBucketWG) void k_bucket_sort(
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ idx, int64_t n, int low,
+    int ntiles, int32_t* tile_start, uint32_t* idx_out) {
+    constexpr int kWaves = kBucketWG / 64, kChunk = kBucketWG * kGroups;
+    __shared__ uint32_t wcount[kWaves][256];
+    __shared__ uint32_t base[256];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const uint32_t mask = (1u << low) - 1u;
+    const int t0 = (int)blockIdx.x << low;
+    const int64_t s = tile_start[t0];
+    const int64_t e = t0 + (1 << low) < ntiles ? tile_start[t0 + (1 << low)] : n;
+    if (threadIdx.x < 256) base[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t p = s + threadIdx.x; p < e; p += kBucketWG)
+        atomicAdd(&base[keys[p] & mask], 1u);
+    __syncthreads();
+    if (wave == 0) scan_256(base);
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        const int d = threadIdx.x;
+        base[d] += (uint32_t)s;
+        if (d > 0 && d < (1 << low) && t0 + d < ntiles) tile_start[t0 + d] = (int32_t)base[d];
+    }
+    for (int64_t c0 = s; c0 < e; c0 += kChunk) {
+        __syncthreads();
+        for (int d = threadIdx.x; d < 256 * kWaves; d += kBucketWG) (&wcount[0][0])[d] = 0;
+        __syncthreads();
+        const int64_t w0 = c0 + wave * (kGroups * 64);
+        uint32_t rank[kGroups];
+        uint32_t dig[kGroups];
+        wave_ranks(keys, w0, e, 0, mask, low, wcount[wave], rank, dig);
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            const int d = threadIdx.x;
+            uint32_t run = base[d];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t c = wcount[w][d];
+                wcount[w][d] = run;
+                run += c;
+            }
+            base[d] = run;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int gi = 0; gi < kGroups; ++gi) {
+            const int64_t p = w0 + gi * 64 + lane;
+            if (p < e) idx_out[wcount[wave][dig[gi]] + rank[gi]] = idx[p];
         }
     }
 }
@@ -266,6 +425,86 @@ hipError_t scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_t
 
 }  // namespace
 
+namespace {
+
+constexpr int kMaxBucketBits = 16;   // an upper digit of 8 bits, a lower of 8
+constexpr int kSelfScan = 256;       // blocks whose histograms a scatter sums
+
+int key_bits(int ntiles) {
+    int nbits = 0;
+    while (((int64_t)1 << nbits) < ntiles) ++nbits;
+    return nbits;
+}
+
+// keys and the scatter by the digit at `shift`; `upper`: the upper digit
+template <bool kSelf, class Key>
+hipError_t first_pass(const Key& key, int64_t n, int shift, uint32_t* kin, uint32_t* kout,
+                      uint32_t* iout, int ntiles, bool upper, const SortBuffers& b,
+                      hipStream_t stream) {
+    const int nblocks = (int)((n + kItems - 1) / kItems);
+    hipLaunchKernelGGL((k_keys_hist<kSelf, Key>), dim3(nblocks), dim3(kWaves * 64), 0,
+                       stream, key, n, shift, nblocks, kin, b.hist);
+    if constexpr (!kSelf) {
+        hipError_t e = scan_exclusive(b.hist, b.hist, 256ll * nblocks, b.scan_tmp, stream);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_scatter<kSelf>, dim3(nblocks), dim3(kWaves * 64), 0, stream,
+                       kin, nullptr, n, shift, nblocks, b.hist, kout, iout,
+                       upper ? b.tile_start : nullptr, ntiles);
+    return hipGetLastError();
+}
+
+hipError_t tile_bounds(const uint32_t* keys, int64_t n, int ntiles, const SortBuffers& b,
+                       hipStream_t stream) {
+    const unsigned blocks = (unsigned)((n + 1 + kSortWG - 1) / kSortWG);
+    hipLaunchKernelGGL(k_tile_bounds, dim3(blocks), dim3(kSortWG), 0, stream, keys, n, ntiles,
+                       b.tile_start);
+    return hipGetLastError();
+}
+
+// b.idx = the stable order of the particles by key, b.tile_start their starts
+template <class Key>
+hipError_t cell_sort(const Key& key, int64_t n, int ntiles, const SortBuffers& b,
+                     hipStream_t stream) {
+    if (n == 0) return tile_bounds(b.keys, n, ntiles, b, stream);
+    const int nbits = key_bits(ntiles);
+    const int nblocks = (int)((n + kItems - 1) / kItems);
+    hipError_t e;
+    if (nbits <= 8 || (nbits <= kMaxBucketBits && nblocks <= kSelfScan)) {
+        const int low = nbits > 8 ? nbits - 8 : 0;
+        uint32_t* kout = low ? b.keys2 : nullptr;
+        uint32_t* iout = low ? b.idx2 : b.idx;
+        e = nblocks <= kSelfScan
+                ? first_pass<true>(key, n, low, b.keys, kout, iout, ntiles, true, b, stream)
+                : first_pass<false>(key, n, low, b.keys, kout, iout, ntiles, true, b, stream);
+        if (e != hipSuccess || !low) return e;
+        const int buckets = ((ntiles - 1) >> low) + 1;
+        hipLaunchKernelGGL(k_bucket_sort, dim3(buckets), dim3(kBucketWG), 0, stream, kout, iout,
+                           n, low, ntiles, b.tile_start, b.idx);
+        return hipGetLastError();
+    }
+    // LSD, the last pass into b.idx
+    const int passes = (nbits + 7) / 8;
+    uint32_t* ks[2] = {b.keys, b.keys2};
+    uint32_t* is[2] = {b.idx, b.idx2};
+    e = first_pass<false>(key, n, 0, ks[passes & 1], ks[(passes - 1) & 1],
+                          is[(passes - 1) & 1], ntiles, false, b, stream);
+    if (e != hipSuccess) return e;
+    for (int p = 1; p < passes; ++p) {
+        const int in = (passes - p) & 1, out = in ^ 1;
+        hipLaunchKernelGGL(k_radix_hist, dim3(nblocks), dim3(kSortWG), 0, stream, ks[in], n,
+                           8 * p, nblocks, b.hist);
+        e = scan_exclusive(b.hist, b.hist, 256ll * nblocks, b.scan_tmp, stream);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_scatter<false>, dim3(nblocks), dim3(kWaves * 64), 0, stream,
+                           ks[in], is[in], n, 8 * p, nblocks, b.hist, ks[out], is[out], nullptr,
+                           ntiles);
+    }
+    return tile_bounds(ks[0], n, ntiles, b, stream);
+}
+
+}  // namespace
+
 int64_t sort_hist_elems(int64_t n) {
     const int64_t nblocks = (n + kItems - 1) / kItems;
     return 256 * (nblocks > 0 ? nblocks : 1);
@@ -273,94 +512,24 @@ int64_t sort_hist_elems(int64_t n) {
 
 int64_t sort_scan_tmp_elems(int64_t n_scan) { return (n_scan + kScanItems - 1) / kScanItems + 1; }
 
-namespace {
-
-// Stable LSD radix sort of (b.keys, b.idx) on the low nbits of the keys;
-// the sorted keys end in *kfinal and the permutation in b.idx.
-hipError_t radix_sort(int64_t n, int nbits, const SortBuffers& b, hipStream_t stream,
-                      uint32_t** kfinal) {
-    uint32_t* kin = b.keys;
-    uint32_t* iin = b.idx;
-    *kfinal = kin;
-    if (n == 0) return hipSuccess;
-    const int nblocks = (int)((n + kItems - 1) / kItems);
-    const int64_t nh = 256ll * nblocks;
-    uint32_t* kout = b.keys2;
-    uint32_t* iout = b.idx2;
-    for (int shift = 0; shift < nbits; shift += 8) {
-        hipLaunchKernelGGL(k_radix_hist, dim3(nblocks), dim3(kSortWG), 0, stream, kin, n, shift,
-                           nblocks, b.hist);
-        hipError_t e = scan_exclusive(b.hist, b.hist, nh, b.scan_tmp, stream);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_radix_scatter, dim3(nblocks), dim3(kSortWG), 0, stream, kin, iin, n,
-                           shift, nblocks, b.hist, kout, iout);
-        uint32_t* t = kin; kin = kout; kout = t;
-        t = iin; iin = iout; iout = t;
-    }
-    // the sorted permutation must end in b.idx
-    if (iin != b.idx) {
-        hipError_t e = hipMemcpyAsync(b.idx, iin, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice,
-                                      stream);
-        if (e != hipSuccess) return e;
-    }
-    *kfinal = kin;
-    return hipGetLastError();
-}
-
-}  // namespace
-
 hipError_t launch_cell_sort(const double* x, const double* y, int64_t n, double inv_dx,
                             double inv_dy, const TileGeom& g, const SortBuffers& b,
                             hipStream_t stream) {
-    const int ntiles = g.ntx * g.nty;
-    if (n > 0) {
-        const unsigned blocks = (unsigned)((n + kSortWG - 1) / kSortWG);
-        hipLaunchKernelGGL(k_tile_keys, dim3(blocks), dim3(kSortWG), 0, stream, x, y, n,
-                           inv_dx, inv_dy, g, b.keys, b.idx);
-    }
-    int nbits = 0;
-    while ((1 << nbits) < ntiles) ++nbits;
-    uint32_t* kin = b.keys;
-    hipError_t e = radix_sort(n, nbits, b, stream, &kin);
-    if (e != hipSuccess) return e;
-    const unsigned blocks = (unsigned)((n + 1 + kSortWG - 1) / kSortWG);
-    hipLaunchKernelGGL(k_tile_bounds, dim3(blocks), dim3(kSortWG), 0, stream, kin, n, ntiles,
-                       b.tile_start);
-    return hipGetLastError();
+    return cell_sort(Key2{x, y, inv_dx, inv_dy, g}, n, g.ntx * g.nty, b, stream);
 }
 
 hipError_t launch_gr_cell_sort(const double* r, const double* th, int64_t n,
                                const gr::GrConst& g, int tile, const SortBuffers& b,
                                hipStream_t stream) {
-    if (n == 0) return hipSuccess;
     const int ntx = (g.nr + tile - 1) / tile, nty = (g.nth + tile - 1) / tile;
-    const unsigned blocks = (unsigned)((n + kSortWG - 1) / kSortWG);
-    hipLaunchKernelGGL(k_gr_tile_keys, dim3(blocks), dim3(kSortWG), 0, stream, r, th, n, g, tile,
-                       ntx, b.keys, b.idx);
-    int nbits = 0;
-    while ((1 << nbits) < ntx * nty) ++nbits;
-    uint32_t* kin = b.keys;
-    return radix_sort(n, nbits, b, stream, &kin);
+    return cell_sort(KeyGr{r, th, g, tile, ntx}, n, ntx * nty, b, stream);
 }
 
 hipError_t launch_cell_sort3(const double* x, const double* y, const double* z, int64_t n,
                              double inv_dx, double inv_dy, double inv_dz, const TileGeom3& g,
                              const SortBuffers& b, hipStream_t stream) {
-    const int ntiles = g.ntx * g.nty * g.ntz;
-    if (n > 0) {
-        const unsigned blocks = (unsigned)((n + kSortWG - 1) / kSortWG);
-        hipLaunchKernelGGL(k_tile_keys3, dim3(blocks), dim3(kSortWG), 0, stream, x, y, z, n,
-                           inv_dx, inv_dy, inv_dz, g, b.keys, b.idx);
-    }
-    int nbits = 0;
-    while ((1 << nbits) < ntiles) ++nbits;
-    uint32_t* kin = b.keys;
-    hipError_t e = radix_sort(n, nbits, b, stream, &kin);
-    if (e != hipSuccess) return e;
-    const unsigned blocks = (unsigned)((n + 1 + kSortWG - 1) / kSortWG);
-    hipLaunchKernelGGL(k_tile_bounds, dim3(blocks), dim3(kSortWG), 0, stream, kin, n, ntiles,
-                       b.tile_start);
-    return hipGetLastError();
+    return cell_sort(Key3{x, y, z, inv_dx, inv_dy, inv_dz, g}, n, g.ntx * g.nty * g.ntz, b,
+                     stream);
 }
 
 }  // namespace gcb
