@@ -346,27 +346,22 @@ int scratch_state(gcb_ctx* ctx, const ParticlePtrs<U>& like, int64_t n, Particle
     return GCB_OK;
 }
 
-// copy every array of a state (same shape) from a to b
+// the copies of every array of a state (same shape) from a to b
 template <typename U>
-hipError_t copy_state(const ParticlePtrs<U>& a, const ParticlePtrs<U>& b, int64_t n,
-                      hipStream_t stream) {
-    const size_t nd = (size_t)n * sizeof(double), nu = (size_t)n * sizeof(U);
-    const hipMemcpyKind k = hipMemcpyDeviceToDevice;
-    hipError_t e = hipSuccess;
-    auto cp = [&](void* dst, const void* src, size_t bytes) {
-        if (e == hipSuccess && src) e = hipMemcpyAsync(dst, src, bytes, k, stream);
-    };
-    cp(b.x, a.x, nd);
-    cp(b.y, a.y, nd);
-    cp(b.xp, a.xp, nd);
-    cp(b.yp, a.yp, nd);
-    cp(b.ux, a.ux, nu);
-    cp(b.uy, a.uy, nu);
-    cp(b.uz, a.uz, nu);
-    cp(b.status, a.status, (size_t)n);
-    cp(b.qm, a.qm, nd);
-    cp(b.id, a.id, (size_t)n * sizeof(int32_t));
-    return e;
+CopyList state_copies(const ParticlePtrs<U>& a, const ParticlePtrs<U>& b, int64_t n) {
+    const int64_t nd = n * (int64_t)sizeof(double), nu = n * (int64_t)sizeof(U);
+    CopyList L;
+    L.add(b.x, a.x, nd);
+    L.add(b.y, a.y, nd);
+    L.add(b.xp, a.xp, nd);
+    L.add(b.yp, a.yp, nd);
+    L.add(b.ux, a.ux, nu);
+    L.add(b.uy, a.uy, nu);
+    L.add(b.uz, a.uz, nu);
+    L.add(b.status, a.status, n);
+    L.add(b.qm, a.qm, nd);
+    L.add(b.id, a.id, n * (int64_t)sizeof(int32_t));
+    return L;
 }
 
 // the physics constants of a launch (geometry left to the caller)
@@ -700,7 +695,7 @@ int run_push(gcb_ctx* ctx, gcb_particles* p, const gcb_params* prm, int32_t n_st
     }
     if (cur.x != user.x) {
         Timer t(ctx, stream, GCB_TIMER_OTHER);
-        GCB_HIP(copy_state<U>(cur, user, n, stream));
+        GCB_HIP(launch_copy_arrays(state_copies<U>(cur, user, n), stream));
         t.done();
     }
     return GCB_OK;
@@ -808,14 +803,10 @@ int run_push3(gcb_ctx* ctx, gcb_particles3* p, const gcb_params* prm, int32_t n_
     }
     if (cur.b.x != user.b.x) {
         Timer t(ctx, stream, GCB_TIMER_OTHER);
-        hipError_t e = copy_state<U>(cur.b, user.b, n, stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(user.z, cur.z, (size_t)n * sizeof(double),
-                               hipMemcpyDeviceToDevice, stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(user.zp, cur.zp, (size_t)n * sizeof(double),
-                               hipMemcpyDeviceToDevice, stream);
-        if (e != hipSuccess) return fail(ctx, GCB_EHIP, "state copy: %s", hipGetErrorString(e));
+        CopyList L = state_copies<U>(cur.b, user.b, n);
+        L.add(user.z, cur.z, n * (int64_t)sizeof(double));
+        L.add(user.zp, cur.zp, n * (int64_t)sizeof(double));
+        GCB_HIP(launch_copy_arrays(L, stream));
         t.done();
     }
     return GCB_OK;
@@ -1297,19 +1288,18 @@ int gcb_push_gr(gcb_ctx* ctx, gcb_gr_particles* p, const gcb_params* prm, int32_
         }
         if (cur.r != ptrs.r) {
             Timer t(ctx, stream, GCB_TIMER_OTHER);
-            const hipMemcpyKind k = hipMemcpyDeviceToDevice;
-            const size_t nd = (size_t)n * sizeof(double);
-            GCB_HIP(hipMemcpyAsync(ptrs.r, cur.r, nd, k, stream));
-            GCB_HIP(hipMemcpyAsync(ptrs.th, cur.th, nd, k, stream));
-            GCB_HIP(hipMemcpyAsync(ptrs.ph, cur.ph, nd, k, stream));
-            GCB_HIP(hipMemcpyAsync(ptrs.ur, cur.ur, n * ub, k, stream));
-            GCB_HIP(hipMemcpyAsync(ptrs.uth, cur.uth, n * ub, k, stream));
-            GCB_HIP(hipMemcpyAsync(ptrs.uph, cur.uph, n * ub, k, stream));
-            GCB_HIP(hipMemcpyAsync(ptrs.status, cur.status, (size_t)n, k, stream));
-            if (p->qm)
-                GCB_HIP(hipMemcpyAsync(const_cast<double*>(ptrs.qm), cur.qm, nd, k, stream));
-            if (p->id)
-                GCB_HIP(hipMemcpyAsync(ptrs.id, cur.id, (size_t)n * sizeof(int32_t), k, stream));
+            const int64_t nd = n * (int64_t)sizeof(double), nu = n * (int64_t)ub;
+            CopyList L;
+            L.add(ptrs.r, cur.r, nd);
+            L.add(ptrs.th, cur.th, nd);
+            L.add(ptrs.ph, cur.ph, nd);
+            L.add(ptrs.ur, cur.ur, nu);
+            L.add(ptrs.uth, cur.uth, nu);
+            L.add(ptrs.uph, cur.uph, nu);
+            L.add(ptrs.status, cur.status, n);
+            if (p->qm) L.add(const_cast<double*>(ptrs.qm), cur.qm, nd);
+            if (p->id) L.add(ptrs.id, cur.id, n * (int64_t)sizeof(int32_t));
+            GCB_HIP(launch_copy_arrays(L, stream));
             t.done();
         }
     } else {

@@ -150,6 +150,21 @@ hipError_t launch_count_flagged(const uint8_t* status, int64_t n,
                                 unsigned long long* out, hipStream_t stream);
 
 // zero `words` 8-byte words at p (8-byte aligned) with a kernel
+// copies of whole arrays, all in one launch (no overlaps)
+struct CopyList {
+    void* dst[12];
+    const void* src[12];
+    int64_t bytes[12];
+    int n = 0;
+    void add(void* d, const void* s, int64_t b) {
+        if (!s || b <= 0) return;
+        dst[n] = d;
+        src[n] = s;
+        bytes[n++] = b;
+    }
+};
+hipError_t launch_copy_arrays(const CopyList& L, hipStream_t stream);
+
 hipError_t launch_zero_words(void* p, int64_t words, hipStream_t stream);
 
 // the library's binary64 sin and cos of n values (device arrays)
