@@ -69,12 +69,71 @@ constexpr bool kGrFast = (GCB_FAST_ARITH != 0) && std::is_same<R, double>::value
 // ---------------------------------------------------------------------------
 // metric
 
+// sincos_poly's sin and cos in the production form: the terms that reach
+// binary64's last place, and the quadrant without a 64-bit integer.
+GCB_HD void sincos_fast(double th, double& sn, double& cs) {
+    const double k = floor(fma(th, 2.0 / kTrigPi, 0.5));
+    const double y = (th - k * kPio2Hi) - k * kPio2Lo;
+    const double z = y * y;
+    double ps = 1.0 / 355687428096000.0;      // 1/17!
+    ps = ps * z + -1.0 / 1307674368000.0;     // -1/15!
+    ps = ps * z + 1.0 / 6227020800.0;         // 1/13!
+    ps = ps * z + -1.0 / 39916800.0;          // -1/11!
+    ps = ps * z + 1.0 / 362880.0;             // 1/9!
+    ps = ps * z + -1.0 / 5040.0;              // -1/7!
+    ps = ps * z + 1.0 / 120.0;                // 1/5!
+    ps = ps * z + -1.0 / 6.0;                 // -1/3!
+    double pc = -1.0 / 6402373705728000.0;    // -1/18!
+    pc = pc * z + 1.0 / 20922789888000.0;     // 1/16!
+    pc = pc * z + -1.0 / 87178291200.0;       // -1/14!
+    pc = pc * z + 1.0 / 479001600.0;          // 1/12!
+    pc = pc * z + -1.0 / 3628800.0;           // -1/10!
+    pc = pc * z + 1.0 / 40320.0;              // 1/8!
+    pc = pc * z + -1.0 / 720.0;               // -1/6!
+    pc = pc * z + 1.0 / 24.0;                 // 1/4!
+    pc = pc * z + -1.0 / 2.0;                 // -1/2!
+    const double s = y + (y * z) * ps;
+    const double c = 1.0 + z * pc;
+    const int q = (int)(k - 4.0 * floor(0.25 * k));
+    const double a = q & 1 ? c : s, b = q & 1 ? s : c;
+    sn = q & 2 ? -a : a;
+    cs = (q + 1) & 2 ? -b : b;
+}
+
+template <typename R>
+GCB_HD void sincos_of(double th, R& sn, R& cs) {
+    if constexpr (kGrFast<R>)
+        sincos_fast(th, sn, cs);
+    else
+        sincos_poly(th, sn, cs);
+}
+
+// sin and cos of th + d from those of th, |d| <= kMaxTurn: a correction of at
+// most 1/16, so the result is a rounding further off than sn, cs are.
+constexpr double kMaxTurn = 0.0625;
+GCB_HD void sincos_turn(double d, double sn0, double cs0, double& sn, double& cs) {
+    const double z = d * d;
+    double ps = 1.0 / 362880.0;
+    ps = ps * z + -1.0 / 5040.0;
+    ps = ps * z + 1.0 / 120.0;
+    ps = ps * z + -1.0 / 6.0;
+    double pc = 1.0 / 40320.0;
+    pc = pc * z + -1.0 / 720.0;
+    pc = pc * z + 1.0 / 24.0;
+    pc = pc * z + -1.0 / 2.0;
+    const double sd = d + (d * z) * ps;
+    const double cd = z * pc;   // cos d - 1
+    sn = sn0 + (cs0 * sd + sn0 * cd);
+    cs = cs0 + (cs0 * cd - sn0 * sd);
+}
+
 template <typename R>
 struct Metric {
     R alpha, beta_r;
     R gu_rr, gu_rph, gu_thth, gu_phph;   // gamma^ij
     R gd_rr, gd_rph, gd_thth, gd_phph;   // gamma_ij
     R sqrtg;
+    R sn, cs;   // of theta (binary64 forms)
     // d/dr, d/dtheta
     R dalpha[2], dbeta_r[2], dgu_rr[2], dgu_rph[2], dgu_thth[2], dgu_phph[2];
 };
@@ -85,12 +144,23 @@ struct Metric {
 // gamma_phph = sin^2 (rho^2 + a^2 (1+z) sin^2), and the inverse
 // gamma^rr = 1/(1+z) + a^2 sin^2/rho^2, gamma^rphi = a/rho^2,
 // gamma^thth = 1/rho^2, gamma^phph = 1/(rho^2 sin^2).
+template <typename R>
+GCB_HD void kerr_derivs(double a_, double r_, Metric<R>& m);
+// with the sine and cosine of theta
 template <bool kDerivs, typename R>
-GCB_HD void kerr_schild(double a_, double r_, double th, Metric<R>& m) {
+GCB_HD void kerr_schild_at(double a_, double r_, R sn, R cs, Metric<R>& m);
+
+template <bool kDerivs, typename R>
+GCB_HD void kerr_schild(double a, double r, double th, Metric<R>& m) {
+    R sn, cs;
+    sincos_of(th, sn, cs);
+    kerr_schild_at<kDerivs>(a, r, sn, cs, m);
+}
+
+template <bool kDerivs, typename R>
+GCB_HD void kerr_schild_at(double a_, double r_, R sn, R cs, Metric<R>& m) {
     const R a = (R)a_, r = (R)r_;
     const R a2 = a * a;
-    R sn, cs;
-    sincos_poly(th, sn, cs);
     const R s2 = sn * sn;
     const R c2 = cs * cs;
     const R rho2 = r * r + a2 * c2;
@@ -113,25 +183,9 @@ GCB_HD void kerr_schild(double a_, double r_, double th, Metric<R>& m) {
         m.gd_thth = rho2;
         m.gd_phph = s2 * (rho2 + (a2 * opz) * s2);
         m.sqrtg = ((opz * al) * rho2) * sn;
-        if (kDerivs) {
-            const R sc = sn * cs;
-            const R drho2[2] = {(R)2 * r, (R)-2 * (a2 * sc)};
-            const R ir4 = ir2 * ir2;
-            const R dz[2] = {((R)2 * (a2 * c2 - r * r)) * ir4, ((R)4 * (r * (a2 * sc))) * ir4};
-            const R iopz2 = iopz * iopz;
-            const R gp2 = m.gu_phph * m.gu_phph;
-            for (int i = 0; i < 2; ++i) {
-                m.dalpha[i] = (R)-0.5 * (al * iopz) * dz[i];
-                m.dbeta_r[i] = dz[i] * iopz2;
-                m.dgu_rph[i] = -(a * drho2[i]) * ir4;
-                m.dgu_thth[i] = -drho2[i] * ir4;
-            }
-            m.dgu_rr[0] = -(dz[0] * iopz2) - (a2 * s2) * drho2[0] * ir4;
-            m.dgu_rr[1] = (-(dz[1] * iopz2) + (a2 * ((R)2 * sc)) * ir2) -
-                          (a2 * s2) * drho2[1] * ir4;
-            m.dgu_phph[0] = -(drho2[0] * s2) * gp2;
-            m.dgu_phph[1] = -(drho2[1] * s2 + rho2 * ((R)2 * sc)) * gp2;
-        }
+        m.sn = sn;
+        m.cs = cs;
+        if (kDerivs) kerr_derivs(a_, r_, m);
         return;
     }
     const R z = ((R)2 * r) / rho2;
@@ -148,7 +202,11 @@ GCB_HD void kerr_schild(double a_, double r_, double th, Metric<R>& m) {
     m.gd_thth = rho2;
     m.gd_phph = s2 * (rho2 + (a2 * opz) * s2);
     m.sqrtg = (sq * rho2) * sn;
-    if (kDerivs) {
+    if constexpr (!kF32<R>) {
+        m.sn = sn;
+        m.cs = cs;
+        if (kDerivs) kerr_derivs(a_, r_, m);
+    } else if (kDerivs) {
         const R sc = sn * cs;
         const R drho2[2] = {(R)2 * r, (R)-2 * (a2 * sc)};
         const R rho4 = rho2 * rho2;
@@ -162,6 +220,54 @@ GCB_HD void kerr_schild(double a_, double r_, double th, Metric<R>& m) {
         }
         m.dgu_rr[0] = -(dz[0] / opz2) - (a2 * s2) * drho2[0] / rho4;
         m.dgu_rr[1] = (-(dz[1] / opz2) + (a2 * ((R)2 * sc)) / rho2) - (a2 * s2) * drho2[1] / rho4;
+        const R rs2 = rho2 * s2;
+        m.dgu_phph[0] = -(drho2[0] * s2) / (rs2 * rs2);
+        m.dgu_phph[1] = -(drho2[1] * s2 + rho2 * ((R)2 * sc)) / (rs2 * rs2);
+    }
+}
+
+// The derivatives of a metric evaluated at r (and its theta), binary64.
+template <typename R>
+GCB_HD void kerr_derivs(double a_, double r_, Metric<R>& m) {
+    const R a = (R)a_, r = (R)r_;
+    const R a2 = a * a;
+    const R sn = m.sn, cs = m.cs;
+    const R s2 = sn * sn;
+    const R c2 = cs * cs;
+    const R sc = sn * cs;
+    const R rho2 = m.gd_thth, opz = m.gd_rr;
+    const R drho2[2] = {(R)2 * r, (R)-2 * (a2 * sc)};
+    if constexpr (kGrFast<R>) {
+        const R ir2 = m.gu_thth, al = m.alpha;
+        const R iopz = al * al;
+        const R ir4 = ir2 * ir2;
+        const R dz[2] = {((R)2 * (a2 * c2 - r * r)) * ir4, ((R)4 * (r * (a2 * sc))) * ir4};
+        const R iopz2 = iopz * iopz;
+        const R gp2 = m.gu_phph * m.gu_phph;
+        for (int i = 0; i < 2; ++i) {
+            m.dalpha[i] = (R)-0.5 * (al * iopz) * dz[i];
+            m.dbeta_r[i] = dz[i] * iopz2;
+            m.dgu_rph[i] = -(a * drho2[i]) * ir4;
+            m.dgu_thth[i] = -drho2[i] * ir4;
+        }
+        m.dgu_rr[0] = -(dz[0] * iopz2) - (a2 * s2) * drho2[0] * ir4;
+        m.dgu_rr[1] =
+            (-(dz[1] * iopz2) + (a2 * ((R)2 * sc)) * ir2) - (a2 * s2) * drho2[1] * ir4;
+        m.dgu_phph[0] = -(drho2[0] * s2) * gp2;
+        m.dgu_phph[1] = -(drho2[1] * s2 + rho2 * ((R)2 * sc)) * gp2;
+    } else {
+        const R rho4 = rho2 * rho2;
+        const R dz[2] = {((R)2 * (a2 * c2 - r * r)) / rho4, ((R)4 * (r * (a2 * sc))) / rho4};
+        const R opz2 = opz * opz;
+        for (int i = 0; i < 2; ++i) {
+            m.dalpha[i] = (R)-0.5 * (m.alpha / opz) * dz[i];
+            m.dbeta_r[i] = dz[i] / opz2;
+            m.dgu_rph[i] = -(a * drho2[i]) / rho4;
+            m.dgu_thth[i] = -drho2[i] / rho4;
+        }
+        m.dgu_rr[0] = -(dz[0] / opz2) - (a2 * s2) * drho2[0] / rho4;
+        m.dgu_rr[1] =
+            (-(dz[1] / opz2) + (a2 * ((R)2 * sc)) / rho2) - (a2 * s2) * drho2[1] / rho4;
         const R rs2 = rho2 * s2;
         m.dgu_phph[0] = -(drho2[0] * s2) / (rs2 * rs2);
         m.dgu_phph[1] = -(drho2[1] * s2 + rho2 * ((R)2 * sc)) / (rs2 * rs2);
@@ -187,10 +293,15 @@ struct GrSample {
 // clamped cell of a point (a NaN coordinate is taken at the lower edge)
 GCB_HD void grid_cell(const GrConst& g, double r, double th, int& i, int& j, double& wx,
                       double& wy) {
+#if GCB_FAST_ARITH
+    const double rc = fmin(fmax(r, g.r_min), g.r_max);
+    const double tc = fmin(fmax(th, 0.0), kPi);
+#else
     double rc = r < g.r_min ? g.r_min : (r > g.r_max ? g.r_max : r);
     double tc = th < 0.0 ? 0.0 : (th > kPi ? kPi : th);
     if (rc != rc) rc = g.r_min;
     if (tc != tc) tc = 0.0;
+#endif
     const double xi = (rc - g.r_min) * g.inv_dr;
     const double eta = tc * g.inv_dth;
     double fi = floor(xi), fj = floor(eta);
@@ -270,13 +381,22 @@ GCB_HD R norm2_con(const Metric<R>& m, const R V[3]) {
     return (V[0] * lo[0] + V[1] * lo[1]) + V[2] * lo[2];
 }
 
+// square root (of a finite argument in the production form)
+template <typename R>
+GCB_HD R root(R v) {
+    if constexpr (kGrFast<R>)
+        return sqrt_nr(v);
+    else
+        return sqrt(v);
+}
+
 template <typename R>
 GCB_HD R gamma_of(const Metric<R>& m, const R u[3]) {
     const R n2 = norm2_cov(m, u);
     if constexpr (kF32<R>) {
         if (n2 > 1.0e6f) return (R)sqrt(1.0 + (double)n2);   // ultra-relativistic: binary64
     }
-    return sqrt((R)1 + n2);
+    return root((R)1 + n2);
 }
 
 GCB_HD double max_nan(double a, double b) { return (a > b || a != a) ? a : b; }
@@ -468,7 +588,7 @@ GCB_HD uint32_t gc_local(const Metric<R>& m, const GrSample<R>& f, GcLocal<R>& L
 // eq. grgcalfac with m = 1
 template <typename R>
 GCB_HD R gamma_gc(const GcLocal<R>& L, R upar, R mu) {
-    return L.kappa * sqrt(((R)1 + upar * upar) + (((R)2 * mu) * L.B) * L.kappa);
+    return L.kappa * root(((R)1 + upar * upar) + (((R)2 * mu) * L.B) * L.kappa);
 }
 
 // the same with, in the production form, its reciprocal
@@ -486,6 +606,15 @@ GCB_HD Lorentz<R> lorentz_gc(const GcLocal<R>& L, R upar, R mu) {
 template <typename R>
 GCB_HD bool switch_gca(const Metric<R>& m, const GrSample<R>& f, const R u[3], double qm,
                        double dl, const GrConst& g, double r, double th) {
+    if constexpr (kGrFast<R>) {
+        // the same test without its quotients and roots but B's, which the
+        // guiding-center quantities take too
+        const R B2 = norm2_con(m, f.B);
+        const R Bf = B2 > (R)0 ? B2 * rsqrt_nr(B2) : (R)0;
+        const R lim = g.f_E * Bf;
+        return B2 > (R)0 && gamma_of(m, u) < g.f_rho * ((fabs(qm) * Bf) * dl) &&
+               norm2_con(m, f.D) < lim * lim;
+    }
     const R Bm = sqrt(norm2_con(m, f.B));
     const R Dm = sqrt(norm2_con(m, f.D));
     const R Gam = gamma_of(m, u);
@@ -507,7 +636,7 @@ GCB_HD bool switch_gca(const Metric<R>& m, const GrSample<R>& f, const R u[3], d
 }
 
 GCB_HD double wrap_phi(double ph) {
-    double w = ph - kTwoPi * floor(ph / kTwoPi);
+    double w = ph - kTwoPi * floor(GCB_FAST_ARITH ? ph * (1.0 / kTwoPi) : ph / kTwoPi);
     if (w < 0.0) w = w + kTwoPi;
     if (w >= kTwoPi) w = w - kTwoPi;
     return w;
@@ -576,8 +705,10 @@ GCB_HD bool starts_gca(const T* __restrict__ F, const double* __restrict__ dl_ta
 // one pass: a wavefront whose lanes took different branches runs the shared
 // metric evaluations once, and only the branch-specific parts diverge.
 //
-// `start` carries the metric and the fields at x^{n+1} into the next step of
-// the same particle (start.valid false: evaluated here).
+// `start` carries what was evaluated at x^{n+1} into the next step of the same
+// particle (start.valid false: evaluated here).
+//
+// The precision form; the binary64 forms follow.
 template <typename R, typename T>
 GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_table,
                         const GrConst& g, double x[3], R u[3], double qm, uint8_t& status,
@@ -614,15 +745,9 @@ GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_t
         const R up2 = norm2_cov(m0, uperp);
         // the check of the neglect of the mirror terms (c = 1)
         if (g.mirror_tol > 0.0 && up2 > (R)g.mirror_tol * (Gf * Gf)) fl |= ST_MIRROR;
-        R inv_nu;
-        if constexpr (kGrFast<R>) {
-            mu = (((R)0.5 * up2) * L0.inv_B) * L0.inv_kappa;
-            inv_nu = up2 > (R)0 ? rsqrt_nr(up2) : (R)0;
-        } else {
-            mu = (((R)0.5 * up2) / L0.B) / L0.kappa;
-            const R nu = sqrt(up2);
-            inv_nu = nu > (R)0 ? (R)1 / nu : (R)0;
-        }
+        mu = (((R)0.5 * up2) / L0.B) / L0.kappa;
+        const R nu = sqrt(up2);
+        const R inv_nu = nu > (R)0 ? (R)1 / nu : (R)0;
         if (!(L0.B > (R)0)) mu = (R)0;
         for (int i = 0; i < 3; ++i) bperp[i] = uperp[i] * inv_nu;
         p1 = upar + ((R)qm * (m0.alpha * ((R)0.5 * dt))) * L0.Dpar;
@@ -651,12 +776,7 @@ GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_t
             R vu[3];
             raise(mb, Lb.vE, vu);
             R bG[3];
-            for (int i = 0; i < 3; ++i) {
-                if constexpr (kGrFast<R>)
-                    bG[i] = Lb.b_up[i] * Gam.inv;
-                else
-                    bG[i] = Lb.b_up[i] / Gam.g;
-            }
+            for (int i = 0; i < 3; ++i) bG[i] = Lb.b_up[i] / Gam.g;
             V[0] = mb.alpha * (pb * bG[0] + vu[0]) - mb.beta_r;
             V[1] = mb.alpha * (pb * bG[1] + vu[1]);
             V[2] = mb.alpha * (pb * bG[2] + vu[2]);
@@ -717,6 +837,154 @@ GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_t
     start.m = m1;
     start.f = f1;
     start.valid = true;
+    return gca ? 0 : 1;
+}
+
+// Binary64.  The first iteration's midpoint is x^n, where the step has the
+// metric and, on the guiding-center branch, the fields and the local quantities
+// already: only the derivatives are evaluated there.  The same values at the
+// same point, a sample, a metric and a set of local quantities in five left out
+// at K = 4.  The VALU issues in 83 % of the cycles, so instructions count:
+// production form, 1e7 particles, 512^2, 16 steps: 12.46 -> 11.10 ms, and 10.69
+// with the midpoints' sines from the step start's (sincos_turn); parity form,
+// 2e6: 4.63 -> 4.36 ms (with two wavefronts per SIMD, see there).  Carrying
+// the derivatives and the local quantities into the next step as well spills
+// 33 values: 13.0 ms.
+template <typename T>
+GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_table,
+                        const GrConst& g, double x[3], double u[3], double qm,
+                        uint8_t& status, double& res, StepStart<double>& at) {
+    using R = double;
+    res = 0.0;
+    if ((status & kStOut) || !inside(g, x[0], x[1])) {
+        if (!inside(g, x[0], x[1])) status |= kStOut;
+        return 2;
+    }
+    const R dt = g.dt;
+    if (!at.valid) {
+        kerr_schild<false>(g.a, x[0], x[1], at.m);
+        grid_sample(F, g, x[0], x[1], at.f);
+        at.valid = true;
+    }
+    const bool gca = switch_with(at.m, at.f, dl_table, g, x, u, qm);
+
+    uint32_t fl = 0;
+    // guiding-center state: mu, gyration direction, u_par after the half push
+    R mu = 0.0, bperp[3] = {0.0, 0.0, 0.0}, p1 = 0.0, pk = 0.0;
+    // full-orbit state: u after the half push, the iterate u''
+    R u1[3] = {u[0], u[1], u[2]}, uk[3];
+    GcLocal<R> L;
+    if (gca) {
+        fl |= gc_local(at.m, at.f, L, g.a, x[0], x[1]);
+        const R Gf = gamma_of(at.m, u);
+        const R upar = (L.b_up[0] * u[0] + L.b_up[1] * u[1]) + L.b_up[2] * u[2];
+        R uperp[3];
+        for (int i = 0; i < 3; ++i)
+            uperp[i] = (u[i] - upar * L.b_dn[i]) - L.vE[i] * Gf;
+        const R up2 = norm2_cov(at.m, uperp);
+        // the check of the neglect of the mirror terms (c = 1)
+        if (g.mirror_tol > 0.0 && up2 > g.mirror_tol * (Gf * Gf)) fl |= ST_MIRROR;
+        R inv_nu;
+        if constexpr (kGrFast<R>) {
+            mu = ((0.5 * up2) * L.inv_B) * L.inv_kappa;
+            inv_nu = up2 > 0.0 ? rsqrt_nr(up2) : 0.0;
+        } else {
+            mu = ((0.5 * up2) / L.B) / L.kappa;
+            const R nu = sqrt(up2);
+            inv_nu = nu > 0.0 ? 1.0 / nu : 0.0;
+        }
+        if (!(L.B > 0.0)) mu = 0.0;
+        for (int i = 0; i < 3; ++i) bperp[i] = uperp[i] * inv_nu;
+        p1 = upar + (qm * (at.m.alpha * (0.5 * dt))) * L.Dpar;
+        pk = p1;
+    } else {
+        half_push(at.m, at.f, u1, qm, g.dt);
+    }
+    for (int i = 0; i < 3; ++i) uk[i] = u1[i];
+
+    Metric<R> mb = at.m;
+    kerr_derivs(g.a, x[0], mb);
+    double Xk[3] = {x[0], x[1], x[2]};
+    for (int k = 0;; ++k) {
+        R V[3], ub[3];
+        Lorentz<R> Gam;
+        if (gca) {
+            const R pb = 0.5 * (pk + p1);
+            Gam = lorentz_gc(L, pb, mu);
+            R vu[3];
+            raise(mb, L.vE, vu);
+            R bG[3];
+            for (int i = 0; i < 3; ++i) {
+                if constexpr (kGrFast<R>)
+                    bG[i] = L.b_up[i] * Gam.inv;
+                else
+                    bG[i] = L.b_up[i] / Gam.g;
+            }
+            V[0] = mb.alpha * (pb * bG[0] + vu[0]) - mb.beta_r;
+            V[1] = mb.alpha * (pb * bG[1] + vu[1]);
+            V[2] = mb.alpha * (pb * bG[2] + vu[2]);
+            const R upg = root(((2.0 * mu) * L.kappa) * L.B);
+            for (int i = 0; i < 3; ++i)
+                ub[i] = (pb * L.b_dn[i] + L.vE[i] * Gam.g) + upg * bperp[i];
+        } else {
+            for (int i = 0; i < 3; ++i) ub[i] = 0.5 * (uk[i] + u1[i]);
+            Gam = lorentz_of(mb, ub);
+            geo_V(mb, ub, Gam, V);
+        }
+        R G[2];
+        geo_G(mb, ub, Gam, G);
+        double Xn[3];
+        for (int i = 0; i < 3; ++i) Xn[i] = x[i] + dt * V[i];
+        res = max_nan(max_nan(fabs(Xn[0] - Xk[0]), fabs(Xn[1] - Xk[1])), fabs(Xn[2] - Xk[2]));
+        for (int i = 0; i < 3; ++i) Xk[i] = Xn[i];
+        if (gca) {
+            const R Gb = G[0] * L.b_up[0] + G[1] * L.b_up[1];
+            pk = p1 + dt * Gb;
+        } else {
+            uk[0] = u1[0] + dt * G[0];
+            uk[1] = u1[1] + dt * G[1];
+            uk[2] = u1[2];
+        }
+        if (k + 1 >= g.n_iter) break;
+        const double Xb[2] = {0.5 * (Xk[0] + x[0]), 0.5 * (Xk[1] + x[1])};
+        const double d = Xb[1] - x[1];
+        R sn, cs;
+        if (kGrFast<R> && fabs(d) <= kMaxTurn)
+            sincos_turn(d, at.m.sn, at.m.cs, sn, cs);
+        else
+            sincos_of(Xb[1], sn, cs);
+        kerr_schild_at<true>(g.a, Xb[0], sn, cs, mb);
+        if (gca) {
+            GrSample<R> fb;
+            grid_sample(F, g, Xb[0], Xb[1], fb);
+            fl |= gc_local(mb, fb, L, g.a, Xb[0], Xb[1]);
+        }
+    }
+    kerr_schild<false>(g.a, Xk[0], Xk[1], at.m);
+    grid_sample(F, g, Xk[0], Xk[1], at.f);
+    if (gca) fl |= gc_local(at.m, at.f, L, g.a, Xk[0], Xk[1]);
+
+    R un[3];
+    if (gca) {
+        const R upar1 = pk + (qm * (at.m.alpha * (0.5 * dt))) * L.Dpar;
+        const R Gam1 = gamma_gc(L, upar1, mu);
+        const R upg1 = root(((2.0 * mu) * L.kappa) * L.B);
+        for (int i = 0; i < 3; ++i)
+            un[i] = (upar1 * L.b_dn[i] + L.vE[i] * Gam1) + upg1 * bperp[i];
+    } else {
+        half_push(at.m, at.f, uk, qm, g.dt);
+        for (int i = 0; i < 3; ++i) un[i] = uk[i];
+    }
+    if (res > g.fp_tol) fl |= ST_FPRES;
+    bool fin = true;
+    for (int i = 0; i < 3; ++i) fin = fin && __builtin_isfinite(Xk[i]) && __builtin_isfinite(un[i]);
+    if (!fin) fl |= ST_NONFINITE;
+    if (!inside(g, Xk[0], Xk[1])) fl |= kStOut;
+    x[0] = Xk[0];
+    x[1] = Xk[1];
+    x[2] = wrap_phi(Xk[2]);
+    for (int i = 0; i < 3; ++i) u[i] = un[i];
+    status = (uint8_t)(status | fl);
     return gca ? 0 : 1;
 }
 
