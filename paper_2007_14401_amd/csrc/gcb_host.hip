@@ -364,6 +364,20 @@ CopyList state_copies(const ParticlePtrs<U>& a, const ParticlePtrs<U>& b, int64_
     return L;
 }
 
+// dst = src taken through perm (inverse: put back), for `count` arrays of n; a
+// plain copy without perm
+hipError_t move_arrays(const double* const* src, double* const* dst, int count,
+                       const uint32_t* perm, int64_t n, bool inverse, hipStream_t stream) {
+    if (perm) {
+        PermuteList L;
+        for (int c = 0; c < count; ++c) L.add(src[c], dst[c]);
+        return launch_permute(L, perm, n, inverse, stream);
+    }
+    CopyList L;
+    for (int c = 0; c < count; ++c) L.add(dst[c], src[c], n * (int64_t)sizeof(double));
+    return launch_copy_arrays(L, stream);
+}
+
 // the physics constants of a launch (geometry left to the caller)
 PushConst physics_const(const gcb_params* prm) {
     PushConst pc{};
@@ -1024,16 +1038,17 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
         // the sort's buffers serve the recomputation's sorts too: keep the
         // permutation
         GCB_HIP(hipMemcpyAsync(perm, ssb.idx, (size_t)n * 4, hipMemcpyDeviceToDevice, stream));
-        if (start->qm) GCB_HIP(launch_permute_f64(start->qm, perm, n, qms, false, stream));
+        if (start->qm)
+            GCB_HIP(move_arrays(&start->qm, &qms, 1, perm, n, false, stream));
+    }
+    double* works[7];
+    double* lams[7];
+    for (int c = 0; c < 7; ++c) {
+        works[c] = work + c * (size_t)n;
+        lams[c] = lam + c * (size_t)n;
     }
     if (n > 0) {
-        for (int c = 0; c < 7; ++c) {
-            if (perm)
-                GCB_HIP(launch_permute_f64(src[c], perm, n, work + c * (size_t)n, false, stream));
-            else
-                GCB_HIP(hipMemcpyAsync(work + c * (size_t)n, src[c], nd,
-                                       hipMemcpyDeviceToDevice, stream));
-        }
+        GCB_HIP(move_arrays(src, works, 7, perm, n, false, stream));
         GCB_HIP(hipMemsetAsync(wstatus, 0, (size_t)n, stream));
     }
     double* wqm = (perm && start->qm) ? qms : start->qm;
@@ -1066,13 +1081,7 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
         if (rc) return rc;
     }
     // reverse sweep
-    for (int c = 0; c < 7 && n > 0; ++c) {
-        if (perm)
-            GCB_HIP(launch_permute_f64(lam_end[c], perm, n, lam + c * (size_t)n, false, stream));
-        else
-            GCB_HIP(hipMemcpyAsync(lam + c * (size_t)n, lam_end[c], nd, hipMemcpyDeviceToDevice,
-                                   stream));
-    }
+    if (n > 0) GCB_HIP(move_arrays(lam_end, lams, 7, perm, n, false, stream));
     GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(float), stream));
     // steps in reverse order, in batches [s_lo, s_hi), the particles sorted by
     // their positions halfway
@@ -1109,18 +1118,8 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
             GCB_HIP(launch_adjoint_batch(A, pc, stream));
         }
     }
-    for (int c = 0; c < 7 && n > 0; ++c) {
-        if (perm)
-            GCB_HIP(launch_permute_f64(lam + c * (size_t)n, perm, n, lam_start[c], true,
-                                       stream));
-        else
-            GCB_HIP(hipMemcpyAsync(lam_start[c], lam + c * (size_t)n, nd,
-                                   hipMemcpyDeviceToDevice, stream));
-    }
-    if (n_steps == 0 && n > 0)
-        for (int c = 0; c < 7; ++c)
-            GCB_HIP(hipMemcpyAsync(lam_start[c], lam_end[c], nd, hipMemcpyDeviceToDevice,
-                                   stream));
+    // (with no steps the cotangents come back as they went in)
+    if (n > 0) GCB_HIP(move_arrays(lams, lam_start, 7, perm, n, true, stream));
     float* const outs[6] = {dE[0], dE[1], dE[2], dB[0], dB[1], dB[2]};
     GCB_HIP(launch_deinterleave_add(grad, ctx->nx, ctx->ny, outs, stream));
     t.done();
@@ -1463,16 +1462,17 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
         GCB_HIP(launch_cell_sort3(start->x, start->y, start->z, n, 1.0 / ctx->d3[0],
                                   1.0 / ctx->d3[1], 1.0 / ctx->d3[2], og, ssb, stream));
         GCB_HIP(hipMemcpyAsync(perm, ssb.idx, (size_t)n * 4, hipMemcpyDeviceToDevice, stream));
-        if (start->qm) GCB_HIP(launch_permute_f64(start->qm, perm, n, qms, false, stream));
+        if (start->qm)
+            GCB_HIP(move_arrays(&start->qm, &qms, 1, perm, n, false, stream));
+    }
+    double* works[kS];
+    double* lams[kS];
+    for (int c = 0; c < kS; ++c) {
+        works[c] = work + c * (size_t)n;
+        lams[c] = lam + c * (size_t)n;
     }
     if (n > 0) {
-        for (int c = 0; c < kS; ++c) {
-            if (perm)
-                GCB_HIP(launch_permute_f64(src[c], perm, n, work + c * (size_t)n, false, stream));
-            else
-                GCB_HIP(hipMemcpyAsync(work + c * (size_t)n, src[c], nd,
-                                       hipMemcpyDeviceToDevice, stream));
-        }
+        GCB_HIP(move_arrays(src, works, kS, perm, n, false, stream));
         GCB_HIP(hipMemsetAsync(wstatus, 0, (size_t)n, stream));
     }
     double* wqm = (perm && start->qm) ? qms : start->qm;
@@ -1530,13 +1530,7 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
         GCB_HIP(launch_push3_f64(L, w, w, pc, stream));
     }
     // reverse sweep
-    for (int c = 0; c < kS && n > 0; ++c) {
-        if (perm)
-            GCB_HIP(launch_permute_f64(lam_end[c], perm, n, lam + c * (size_t)n, false, stream));
-        else
-            GCB_HIP(hipMemcpyAsync(lam + c * (size_t)n, lam_end[c], nd, hipMemcpyDeviceToDevice,
-                                   stream));
-    }
+    if (n > 0) GCB_HIP(move_arrays(lam_end, lams, kS, perm, n, false, stream));
     GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(float), stream));
     if (ordered) {
         const double inv_min =
@@ -1573,18 +1567,8 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
             GCB_HIP(launch_adjoint3_batch(A, pc, stream));
         }
     }
-    for (int c = 0; c < kS && n > 0; ++c) {
-        if (perm)
-            GCB_HIP(launch_permute_f64(lam + c * (size_t)n, perm, n, lam_start[c], true,
-                                       stream));
-        else
-            GCB_HIP(hipMemcpyAsync(lam_start[c], lam + c * (size_t)n, nd,
-                                   hipMemcpyDeviceToDevice, stream));
-    }
-    if (n_steps == 0 && n > 0)
-        for (int c = 0; c < kS; ++c)
-            GCB_HIP(hipMemcpyAsync(lam_start[c], lam_end[c], nd, hipMemcpyDeviceToDevice,
-                                   stream));
+    // (with no steps the cotangents come back as they went in)
+    if (n > 0) GCB_HIP(move_arrays(lams, lam_start, kS, perm, n, true, stream));
     // the 3D node-interleaved layout is the 2D one with nx columns and ny*nz rows
     float* const outs[6] = {dE[0], dE[1], dE[2], dB[0], dB[1], dB[2]};
     GCB_HIP(launch_deinterleave_add(grad, ctx->n3[0], ctx->n3[1] * ctx->n3[2], outs, stream));

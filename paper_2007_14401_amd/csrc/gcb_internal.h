@@ -169,8 +169,18 @@ hipError_t launch_zero_words(void* p, int64_t words, hipStream_t stream);
 
 // the library's binary64 sin and cos of n values (device arrays)
 // dst[s] = src[perm[s]] (inverse: dst[perm[s]] = src[s]) for n binary64 values
-hipError_t launch_permute_f64(const double* src, const uint32_t* perm, int64_t n, double* dst,
-                              bool inverse, hipStream_t stream);
+struct PermuteList {
+    static constexpr int kMax = 10;
+    const double* src[kMax];
+    double* dst[kMax];
+    int n = 0;
+    void add(const double* s, double* d) {
+        src[n] = s;
+        dst[n++] = d;
+    }
+};
+hipError_t launch_permute(const PermuteList& L, const uint32_t* perm, int64_t n, bool inverse,
+                          hipStream_t stream);
 
 hipError_t launch_sincos(const double* x, double* s, double* c, int64_t n,
                          hipStream_t stream);

@@ -148,30 +148,36 @@ __global__ __launch_bounds__(kWG) void k_copy_arrays(CopyList L) {
 
 }  // namespace
 
-// dst[s] = src[perm[s]] for n binary64 values (perm: sorted slot -> source slot)
-__global__ __launch_bounds__(kWG) void k_gather_f64(const double* __restrict__ src,
-                                                    const uint32_t* __restrict__ perm,
-                                                    int64_t n, double* __restrict__ dst) {
+// dst[s] = src[perm[s]] (perm: sorted slot -> source slot) or, kInverse,
+// dst[perm[s]] = src[s], for each array of the list.  One launch for the seven
+// or nine arrays of a state, with their loads in flight together: bound by
+// launches below 1e6 particles (a training step of 3e5 particles in 3D has six
+// of these in place of 54 of 5 us: 4.24 -> 4.16 ms), by the scattered
+// side's cache lines above.
+template <bool kInverse>
+__global__ __launch_bounds__(kWG) void k_permute(PermuteList L,
+                                                 const uint32_t* __restrict__ perm, int64_t n) {
     const int64_t s = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    if (s < n) dst[s] = src[perm[s]];
+    if (s >= n) return;
+    const int64_t p = perm[s];
+    const int64_t in = kInverse ? s : p, out = kInverse ? p : s;
+    double v[PermuteList::kMax];
+#pragma unroll
+    for (int a = 0; a < PermuteList::kMax; ++a)
+        if (a < L.n) v[a] = L.src[a][in];
+#pragma unroll
+    for (int a = 0; a < PermuteList::kMax; ++a)
+        if (a < L.n) L.dst[a][out] = v[a];
 }
 
-// dst[perm[s]] = src[s], the inverse of k_gather_f64
-__global__ __launch_bounds__(kWG) void k_scatter_f64(const double* __restrict__ src,
-                                                     const uint32_t* __restrict__ perm,
-                                                     int64_t n, double* __restrict__ dst) {
-    const int64_t s = (int64_t)blockIdx.x * kWG + threadIdx.x;
-    if (s < n) dst[perm[s]] = src[s];
-}
-
-hipError_t launch_permute_f64(const double* src, const uint32_t* perm, int64_t n, double* dst,
-                              bool inverse, hipStream_t stream) {
-    if (n == 0) return hipSuccess;
+hipError_t launch_permute(const PermuteList& L, const uint32_t* perm, int64_t n, bool inverse,
+                          hipStream_t stream) {
+    if (n == 0 || L.n == 0) return hipSuccess;
     const unsigned blocks = (unsigned)((n + kWG - 1) / kWG);
     if (inverse)
-        hipLaunchKernelGGL(k_scatter_f64, dim3(blocks), dim3(kWG), 0, stream, src, perm, n, dst);
+        hipLaunchKernelGGL(k_permute<true>, dim3(blocks), dim3(kWG), 0, stream, L, perm, n);
     else
-        hipLaunchKernelGGL(k_gather_f64, dim3(blocks), dim3(kWG), 0, stream, src, perm, n, dst);
+        hipLaunchKernelGGL(k_permute<false>, dim3(blocks), dim3(kWG), 0, stream, L, perm, n);
     return hipGetLastError();
 }
 
