@@ -106,6 +106,15 @@ struct Window {
     }
 };
 
+// element of the node-interleaved grid at which row `row` of a window's nodes
+// starts (at global column 0)
+template <int D>
+__device__ __forceinline__ size_t grid_row(const Window<D>& w, int row) {
+    size_t g = wrap_index(w.o[1] + row % Window<D>::W, w.n[1]);
+    if (D == 3) g += (size_t)wrap_index(w.o[D - 1] + row / Window<D>::W, w.n[D - 1]) * w.n[1];
+    return g * w.n[0] * 6;
+}
+
 // One workgroup per chunk of a tile's particles (chunk c of the launch: tile
 // t with starts[t] <= c < starts[t+1], particles [c - starts[t]] * part of the
 // tile's), for the steps [s_lo, s_hi) of a segment, last to first.  Slot p of
@@ -155,20 +164,36 @@ k_adjoint_batch(const double* __restrict__ rec, const double* __restrict__ qm_ar
     }
     const typename Dim<D>::Acc acc = Dim<D>::acc(F_lds, F, pc, win.o, W);
 
-    // stage the fields: a row of W records (6 W values, contiguous in the
-    // node-interleaved array) per wavefront
-    constexpr int kRows = kAll / (6 * W);
-    for (int row = threadIdx.x >> 6; row < kRows; row += kAdjWG / 64) {
-        size_t g = wrap_index(win.o[1] + row % W, win.n[1]);
-        if (D == 3) g += (size_t)wrap_index(win.o[D - 1] + row / W, win.n[D - 1]) * win.n[1];
-        const double* src = F + g * win.n[0] * 6;
-        for (int e = threadIdx.x & 63; e < 6 * W; e += 64) {
-            const int c = e / 6, k = e - 6 * c;
-            const double v = src[wrap_index(win.o[0] + c, win.n[0]) * 6 + k];
-            if constexpr (D == 2)
-                F_lds[window_elem<double>(k, row * W + c, W * W)] = v;
-            else
-                F_lds[(k * kRows + row) * W + c] = v;
+    // stage the fields: rows of W records (6 W values, contiguous in the
+    // node-interleaved array) by wavefronts, the loads of kFlight of them in
+    // flight together
+    constexpr int kRows = kAll / (6 * W), kCols = (6 * W + 63) / 64, kFlight = D == 2 ? 5 : 8;
+    int goff[kCols], loff[kCols], lrow[kCols];
+#pragma unroll
+    for (int u = 0; u < kCols; ++u) {
+        const int e = (threadIdx.x & 63) + 64 * u;
+        const int c = e / 6, k = e - 6 * c;
+        goff[u] = e < 6 * W ? wrap_index(win.o[0] + c, win.n[0]) * 6 + k : -1;
+        loff[u] = D == 2 ? window_elem<double>(k, c, W * W) : k * Window<D>::kPlane + c;
+        lrow[u] = W * (D == 2 ? window_step<double>(k) : 1);
+    }
+    for (int row0 = threadIdx.x >> 6; row0 < kRows; row0 += kFlight * (kAdjWG / 64)) {
+        double v[kFlight][kCols];
+#pragma unroll
+        for (int r = 0; r < kFlight; ++r) {
+            const int row = row0 + r * (kAdjWG / 64);
+            if (row < kRows) {
+                const double* src = F + grid_row(win, row);
+#pragma unroll
+                for (int u = 0; u < kCols; ++u) v[r][u] = goff[u] >= 0 ? src[goff[u]] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kFlight; ++r) {
+            const int row = row0 + r * (kAdjWG / 64);
+#pragma unroll
+            for (int u = 0; u < kCols; ++u)
+                if (row < kRows && goff[u] >= 0) F_lds[loff[u] + row * lrow[u]] = v[r][u];
         }
     }
     for (int e = threadIdx.x; e < kAll; e += kAdjWG) win_lds[e] = 0.0;
@@ -213,9 +238,7 @@ k_adjoint_batch(const double* __restrict__ rec, const double* __restrict__ qm_ar
     __syncthreads();
     // the window to the grid, the values of a row of nodes by neighbouring lanes
     for (int row = threadIdx.x >> 6; row < kRows; row += kAdjWG / 64) {
-        size_t g = wrap_index(win.o[1] + row % W, win.n[1]);
-        if (D == 3) g += (size_t)wrap_index(win.o[D - 1] + row / W, win.n[D - 1]) * win.n[1];
-        float* dst = grad + g * win.n[0] * 6;
+        float* dst = grad + grid_row(win, row);
         for (int e = threadIdx.x & 63; e < 6 * W; e += 64) {
             const int c = e / 6, k = e - 6 * c;
             const double v = win_lds[(k * kRows + row) * W + c];

@@ -195,19 +195,45 @@ k_push3_tiled(ParticlePtrs3<R> in_arg, ParticlePtrs3<R> out_arg,
     const int oj = ty * g.tile - g.halo;
     const int ol = tz * g.tile - g.halo;
 
-    // stage the window: one (j, l) row (W records of 6 values, contiguous in
-    // HBM) per wave iteration, written to the six component planes
-    for (int row = wave; row < W * W; row += kWG / 64) {
-        const int ll = row / W;
-        const int rr = row - ll * W;
-        const int gj = wrap_index(oj + rr, pc.b.ny);
-        const int gl = wrap_index(ol + ll, pc.nz);
-        const T* grow = F + ((size_t)gl * pc.b.ny + gj) * pc.b.nx * 6;
-        for (int e = lane; e < W * 6; e += 64) {
+    // stage the window: (j, l) rows (W records of 6 values, contiguous in HBM) by
+    // wavefronts, written to the six component planes; a lane's columns are the
+    // same in every row, and the loads of kRows rows are in flight together: with
+    // one row after the other a wavefront waited for 25 round trips (W = 10);
+    // 1e7 particles on 128^3, production arithmetic, 8 steps: 8.54 -> 8.19 ms,
+    // mixed, 1.5e6 on 100x72x61, 4 steps: 0.80 -> 0.77 (6 W <= 64 kCols: larger
+    // windows than W = 18 do not fit in LDS)
+    {
+        constexpr int kCols = 2, kRows = 9, kWaves = kWG / 64;
+        int goff[kCols], loff[kCols];
+#pragma unroll
+        for (int u = 0; u < kCols; ++u) {
+            const int e = lane + 64 * u;
             const int c = e / 6;
             const int k = e - c * 6;
-            const int gi = wrap_index(oi + c, pc.b.nx);
-            lds[((k * W + ll) * W + rr) * W + c] = grow[gi * 6 + k];
+            goff[u] = e < W * 6 ? wrap_index(oi + c, pc.b.nx) * 6 + k : -1;
+            loff[u] = k * WWW + c;
+        }
+        for (int row0 = wave; row0 < W * W; row0 += kRows * kWaves) {
+            T v[kRows][kCols];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int row = row0 + r * kWaves;
+                if (row < W * W) {
+                    const int ll = row / W;
+                    const int gj = wrap_index(oj + row - ll * W, pc.b.ny);
+                    const int gl = wrap_index(ol + ll, pc.nz);
+                    const T* grow = F + ((size_t)gl * pc.b.ny + gj) * pc.b.nx * 6;
+#pragma unroll
+                    for (int u = 0; u < kCols; ++u) v[r][u] = goff[u] >= 0 ? grow[goff[u]] : (T)0;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int row = row0 + r * kWaves;
+#pragma unroll
+                for (int u = 0; u < kCols; ++u)
+                    if (row < W * W && goff[u] >= 0) lds[loff[u] + row * W] = v[r][u];
+            }
         }
     }
     __syncthreads();
