@@ -12,17 +12,21 @@
 // Node sums in binary64, because the LDS adds those at full speed and binary32
 // ones lane by lane: a wavefront's ds_add_f32 holds the LDS for 194 cycles
 // wherever its addresses lie, ds_add_f64 for 12 (consecutive) to 22 (random).
-// With binary32 sums the 2D sweep below took 20.5 ms instead of 6.3.
+// With binary32 sums the 2D sweep below took 20.5 ms instead of 6.3 (its tiles of
+// 30 then).
 // Device-scope atomics, some 2e10 per second, are slower again: hence the window.
 //
-// Bound by the LDS (65 % busy: 24 adds and 16 loads per point and 17 points a
-// step in 2D) with two wavefronts per SIMD to hide its latency: 256 registers
-// and the window leave room for no more.  In 3D fewer particles fit a window's
-// tile (225 at one per cell) than fill the wavefronts: 41 %.
-//   2D, 1e6 particles, 1024^2, 32 steps, K = 4: 5.9 ms, 2.0 TB/s; the whole
-//   backward 35.1 -> 10.3 ms (before: a launch per step and regime with global
-//   gathers, records of the cotangents to memory, and their scatter).
-//   3D, 3e5 particles, 64^3, 8 steps: 1.65 ms; training step 8.6 -> 4.7 ms.
+// Bound by the LDS in 2D (65 % busy: at K = 4 a guiding-center step has six points
+// of 24 adds and eleven gathers of 16 loads; VALU 51 %) with two wavefronts per
+// SIMD to hide its latency: 256 registers and the window leave room for no
+// more.  In 3D fewer particles fit a window's tile (225 at one per cell) than
+// fill the wavefronts: LDS 41 %, VALU 30 %.
+//   2D, 1e6 particles, 1024^2, 32 steps, K = 4: 5.9 ms, the whole backward 35.1
+//   -> 10.3 ms, 9.7 with the sorts of today (before: a launch per step and
+//   regime with global gathers, records of the cotangents to memory, and their
+//   scatter: 18.5 and 11.7 ms).
+//   3D, 3e5 particles, 64^3, 8 steps: 1.6 ms; training step 8.6 -> 4.7 ms, 4.0
+//   with the sorts and staging of today.
 // Tiles of 32 in a window of 40 (2D; 28: 11.4 ms, 30: 10.7, 32: 10.3; two
 // workgroups of four wavefronts with windows of 28: 10.5) and of 6 in 11 (3D;
 // 5: 5.7 ms, 6: 4.7, 7: 5.1).

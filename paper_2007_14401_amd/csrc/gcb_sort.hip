@@ -25,9 +25,8 @@
 // The push kernel of the sort's step then reads the state through idx (the
 // permutation) and writes it in tile order, so there is no permutation pass
 // (the same for the curved-spacetime and 3D states).
-//   k_gr_tile_keys: the keys of the curved-spacetime state ((r, theta) tiles
-//                 of the grid cells)
-//   k_tile_keys3:   the keys of the 3D state (cubic tiles)
+// Key2, Key3, KeyGr: the tiles of the 2D, the 3D (cubic) and the
+// curved-spacetime state ((r, theta) tiles of the grid cells).
 #include <hip/hip_runtime.h>
 
 #include "gcb_internal.h"
