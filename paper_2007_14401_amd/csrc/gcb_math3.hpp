@@ -436,6 +436,7 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
 
     // 4. R^{n+1}: K fixed-point iterations R^{k+1} = R^k - H(R^k), R^0 = R^n
     double Rp[3] = {x[0], x[1], x[2]};
+    [[maybe_unused]] double Ro[3] = {x[0], x[1], x[2]};
     res = 0.0;
     for (int k = 0; k < pc.b.n_iter; ++k) {
         R Fk[3];
@@ -450,15 +451,21 @@ GCB_HD uint32_t gca_step3(const Acc& acc, const Sample3<R>& sn, Regs3<R>& r,
             flags |= local_of<kDir, kExact, R>(sk, K, Lk);
             drift_terms3<kDir>(Lk, sk, upn, gy, inv_qm, curv, K, Fk, mirror);
         }
-        double d[3];
+        [[maybe_unused]] double d[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const double Rn = x[a] + (double)(K.h * (Fn[a] + Fk[a]));
-            d[a] = fabs(Rn - Rp[a]);
+            if constexpr (kMixed<R>)
+                d[a] = fabs(Rn - Rp[a]);
+            else
+                Ro[a] = Rp[a];
             Rp[a] = Rn;
         }
-        res = nan_max(nan_max(d[0], d[1]), d[2]);
+        if constexpr (kMixed<R>) res = nan_max(nan_max(d[0], d[1]), d[2]);
     }
+    // the last increment, once
+    if constexpr (!kMixed<R>)
+        res = nan_max(nan_max(fabs(Rp[0] - Ro[0]), fabs(Rp[1] - Ro[1])), fabs(Rp[2] - Ro[2]));
     if (res > pc.b.fp_tol) flags |= ST_FPRES;
 
     // 5. particle variables at R^{n+1/2} = (R^n + R^{n+1})/2, gyration
