@@ -95,17 +95,21 @@ GCB_HD double rcp_nr0(double x) {
     return e == e ? fma(y, fma(e, e, e), y) : y;
 }
 
-// sqrt(x) for finite x >= 0 in binary64, from the refined reciprocal square
-// root (NaN stays NaN)
+// sqrt(x) for x >= 0 in binary64, from the refined reciprocal square root (0,
+// infinity and NaN stay)
 GCB_HD double sqrt_nr(double x) {
-    if (x == 0.0) return x;
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (__builtin_amdgcn_class(x, 0x260)) return x;   // -0, +0, +inf
+#else
+    if (x == 0.0 || x == __builtin_inf()) return x;
+#endif
     const double y = rsqrt_nr(x);
     const double s = x * y;
     return fma(fma(-s, s, x), 0.5 * y, s);
 }
 
-// a/b in binary64 from the refined reciprocal: the quotient corrected by its
-// own remainder (rounded as a division, up to ties)
+// a/b for finite normal b in binary64 from the refined reciprocal: the quotient
+// corrected by its own remainder (rounded as a division, up to ties)
 GCB_HD double div_nr(double a, double b) {
     const double r = rcp_nr(b);
     const double q = a * r;

@@ -939,10 +939,14 @@ GCB_HD void boris(const R E[3], const R Bv[3], R& ux, R& uy, R& uz,
     const R hq = (qm * K.dt) * (R)0.5;
     const R umx = ux + hq * E[0], umy = uy + hq * E[1], umz = uz + hq * E[2];
     R f;
-    if constexpr (kFastD<R>)   // a systematic rounding here would show in every rotation
-        f = div_nr(hq, K.c * sqrt_nr((R)1 + ((umx * umx + umy * umy) + umz * umz) * K.inv_c2));
-    else
+    if constexpr (kFastD<R>) {
+        // (a systematic rounding here would show in every rotation; no rotation
+        // where u^2 overflows)
+        const R g2 = (R)1 + ((umx * umx + umy * umy) + umz * umz) * K.inv_c2;
+        f = __builtin_isinf(g2) ? (R)0 : div_nr(hq, K.c * sqrt_nr(g2));
+    } else {
         f = hq / (K.c * gamma_full(umx, umy, umz, K));
+    }
     const R tx = f * Bv[0], ty = f * Bv[1], tz = f * Bv[2];
     const R t2 = (tx * tx + ty * ty) + tz * tz;
     R g;
