@@ -116,6 +116,13 @@ GCB_HD double div_nr(double a, double b) {
     return fma(fma(-b, q, a), r, q);
 }
 
+// E/B < f_E by the squares (production form).  Where the limit's square rounds
+// to 0, E^2 is either 0, and so below, or larger than it.
+GCB_HD bool below_limit(double E2, double B, double f_E) {
+    const double lim = f_E * B;
+    return E2 < fmax(lim * lim, 0x1p-1074) && f_E > 0.0;
+}
+
 // 2D Yee lattice offsets (cells) of Ex, Ey, Ez, Bx, By, Bz.
 constexpr double kYeeStagger[6][2] = {
     {0.5, 0.0}, {0.0, 0.5}, {0.0, 0.0}, {0.0, 0.5}, {0.5, 0.0}, {0.5, 0.5}};
@@ -126,8 +133,8 @@ struct PushConst {
     double f_rho, f_E, inv_dl, fp_tol;
     double inv_dx, inv_dy, Lx, Ly;
     double qm;               // used when the per-particle array is absent
-    // the production binary64 form: 1/Lx, 1/Ly, f_E^2 and c^2/dl
-    double inv_Lx, inv_Ly, f_E2, c2_inv_dl;
+    // the production binary64 form: 1/Lx, 1/Ly and c^2/dl
+    double inv_Lx, inv_Ly, c2_inv_dl;
     double stagger[6][2];
     int32_t nx, ny;
     int32_t curvature, n_iter;

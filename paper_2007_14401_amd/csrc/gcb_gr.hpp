@@ -611,9 +611,8 @@ GCB_HD bool switch_gca(const Metric<R>& m, const GrSample<R>& f, const R u[3], d
         // guiding-center quantities take too
         const R B2 = norm2_con(m, f.B);
         const R Bf = B2 > (R)0 ? B2 * rsqrt_nr(B2) : (R)0;
-        const R lim = g.f_E * Bf;
         return B2 > (R)0 && gamma_of(m, u) < g.f_rho * ((fabs(qm) * Bf) * dl) &&
-               norm2_con(m, f.D) < lim * lim;
+               below_limit(norm2_con(m, f.D), Bf, g.f_E);
     }
     const R Bm = sqrt(norm2_con(m, f.B));
     const R Dm = sqrt(norm2_con(m, f.D));

@@ -385,7 +385,6 @@ PushConst physics_const(const gcb_params* prm) {
     pc.c = prm->c;
     pc.c2 = prm->c * prm->c;
     pc.inv_c2 = 1.0 / (prm->c * prm->c);
-    pc.f_E2 = prm->f_E * prm->f_E;
     pc.f_rho = prm->f_rho;
     pc.f_E = prm->f_E;
     pc.fp_tol = prm->fp_tol;

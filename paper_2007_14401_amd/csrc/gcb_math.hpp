@@ -865,12 +865,12 @@ GCB_HD bool switch_gca(const R E[3], const R Bv[3], R ux, R uy, R uz,
                                            const Consts<R>& K) {
     if constexpr (kFastD<R>) {
         // the same ratios from the reciprocal square roots that the
-        // guiding-center step takes too, E/B < f_E as E^2/B^2 < f_E^2
+        // guiding-center step takes too
         const R B2 = (Bv[0] * Bv[0] + Bv[1] * Bv[1]) + Bv[2] * Bv[2];
         const R E2 = (E[0] * E[0] + E[1] * E[1]) + E[2] * E[2];
         const R inv_B = B2 > (R)0 ? rsqrt_nr(B2) : (R)0;
         const R rr = ((gamma_full2(ux, uy, uz, K).g * inv_B) * fabs(rcp_nr0(qm))) * pc.c2_inv_dl;
-        return B2 > (R)0 && (rr < pc.f_rho) && ((E2 * inv_B) * inv_B < pc.f_E2);
+        return B2 > (R)0 && (rr < pc.f_rho) && below_limit(E2, B2 * inv_B, pc.f_E);
     } else if constexpr (!kMixed<R>) {
         return switch_gca_f64(E, Bv, ux, uy, uz, qm, pc);
     } else {

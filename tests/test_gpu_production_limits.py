@@ -1,13 +1,15 @@
 """The production arithmetic at the ends of binary64's range, against the parity
 arithmetic on the same inputs: momenta whose square overflows (Gamma infinite, no
-rotation, the electric kick alone)."""
+rotation, the electric kick alone), and switch limits f_E whose square leaves the
+range (E/B < f_E decides, as stated, not the squares)."""
 import numpy as np
 import pytest
 import torch
 
 from gpu_util import GpuRun
 from test_gpu_3d import GpuRun3
-from workloads import make_config, make_config3
+from test_gpu_gr import GrRun, to_device
+from workloads import make_config, make_config3, make_gr_config
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +44,42 @@ def test_overflowing_momentum(dim, kernel, sort, tile):
         assert np.isfinite(b).all(), k
         # a handful of roundings of terms of order one, or of the component itself
         assert np.allclose(b, a, rtol=1e-14, atol=1e-14), k
+
+
+# scales of E and B, f_E, f_rho, and whether the guiding-center branch may be taken
+SWITCH = {"no E": (0.0, 1.0, 1e-170, 0.4, True), "E/B below": (1e-20, 1e150, 1e-165, 0.4, True),
+          "E/B above": (1e-20, 1e150, 1e-175, 0.4, False),
+          "large f_E": (1.0, 1e-160, 1e200, np.inf, True)}
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("case", SWITCH)
+def test_extreme_switch_limit(dim, case):
+    from paper_2007_14401_amd import gcb, state
+    e, b, f_E, f_rho, gca = SWITCH[case]
+    cfg, run = uniform(dim, tuple(e * np.array(E0)), tuple(b * np.array(B0)))
+    try:
+        tr = {}
+        for arith in (gcb.GCB_ARITH_EXACT, gcb.GCB_ARITH_FAST):
+            t = state.to_device(cfg.particles(n=130))
+            tr[arith] = run.push(t, 1, trace=True, f_E=f_E, f_rho=f_rho,
+                                 arith=arith)[0].cpu().numpy()
+    finally:
+        run.close()
+    assert (tr[gcb.GCB_ARITH_EXACT] == 0).any() == gca
+    assert np.array_equal(tr[gcb.GCB_ARITH_EXACT], tr[gcb.GCB_ARITH_FAST])
+
+
+def test_extreme_switch_limit_curved():
+    from paper_2007_14401_amd import gcb
+    cfg = make_gr_config("grbh64")
+    F = cfg.fields()
+    F[:3] = 0.0
+    run = GrRun(cfg, F)
+    try:
+        tr = [run.push(to_device(cfg.particles(n=130)), 1, f_E=1e-170, arith=a)[0].cpu().numpy()
+              for a in (gcb.GCB_ARITH_EXACT, gcb.GCB_ARITH_FAST)]
+    finally:
+        run.close()
+    assert (tr[0] == 0).any()
+    assert np.array_equal(tr[0], tr[1])
