@@ -108,8 +108,8 @@ GCB_HD void sincos_of(double th, R& sn, R& cs) {
         sincos_poly(th, sn, cs);
 }
 
-// sin and cos of th + d from those of th, |d| <= kMaxTurn: a correction of at
-// most 1/16, so the result is a rounding further off than sn, cs are.
+// sin and cos of th + d from those of th, |d| <= kMaxTurn: corrections of at
+// most 1/16, each a rounding of 2^-57 beside the errors that sn0, cs0 have.
 constexpr double kMaxTurn = 0.0625;
 GCB_HD void sincos_turn(double d, double sn0, double cs0, double& sn, double& cs) {
     const double z = d * d;
@@ -125,6 +125,16 @@ GCB_HD void sincos_turn(double d, double sn0, double cs0, double& sn, double& cs
     const double cd = z * pc;   // cos d - 1
     sn = sn0 + (cs0 * sd + sn0 * cd);
     cs = cs0 + (cs0 * cd - sn0 * sd);
+}
+
+// sin and cos of th1 = th0 + d from those of th0, turned while d is small and
+// the sine keeps half its size -- nearer to the axis the sum would cancel, and
+// 1/sin^2 magnify what is left -- evaluated otherwise.
+GCB_HD void sincos_near(double th1, double d, double sn0, double cs0, double& sn, double& cs) {
+    if (fabs(d) <= fmin(kMaxTurn, 0.5 * fabs(sn0)))
+        sincos_turn(d, sn0, cs0, sn, cs);
+    else
+        sincos_fast(th1, sn, cs);
 }
 
 template <typename R>
@@ -946,10 +956,9 @@ GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_t
         }
         if (k + 1 >= g.n_iter) break;
         const double Xb[2] = {0.5 * (Xk[0] + x[0]), 0.5 * (Xk[1] + x[1])};
-        const double d = Xb[1] - x[1];
         R sn, cs;
-        if (kGrFast<R> && fabs(d) <= kMaxTurn)
-            sincos_turn(d, at.m.sn, at.m.cs, sn, cs);
+        if constexpr (kGrFast<R>)
+            sincos_near(Xb[1], Xb[1] - x[1], at.m.sn, at.m.cs, sn, cs);
         else
             sincos_of(Xb[1], sn, cs);
         kerr_schild_at<true>(g.a, Xb[0], sn, cs, mb);
