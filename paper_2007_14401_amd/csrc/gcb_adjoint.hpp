@@ -665,7 +665,7 @@ GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
 #pragma unroll
     for (int i = 0; i < 3; ++i) um[i] = u[i] + hq * s.E[i];
     const Gam<double> gm = gamma_full2(um[0], um[1], um[2], K);
-    const double f = hq * rcp_nr(K.c) * gm.inv;
+    const double f = div_nr(hq, K.c * sqrt_nr(1.0 + dot3(um, um) * K.inv_c2));   // as the push
 #pragma unroll
     for (int i = 0; i < 3; ++i) t[i] = f * s.B[i];
     const double g = 2.0 * rcp_nr0(1.0 + dot3(t, t));
