@@ -95,17 +95,21 @@ GCB_HD double rcp_nr0(double x) {
     return e == e ? fma(y, fma(e, e, e), y) : y;
 }
 
-// sqrt(x) for x >= 0 in binary64, from the refined reciprocal square root (0,
-// infinity and NaN stay)
+// sqrt(x) for finite x > 0 in binary64, from the refined reciprocal square root
+GCB_HD double sqrt_pos(double x) {
+    const double y = rsqrt_nr(x);
+    const double s = x * y;
+    return fma(fma(-s, s, x), 0.5 * y, s);
+}
+
+// the same for x >= 0 (0, infinity and NaN stay)
 GCB_HD double sqrt_nr(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
     if (__builtin_amdgcn_class(x, 0x260)) return x;   // -0, +0, +inf
 #else
     if (x == 0.0 || x == __builtin_inf()) return x;
 #endif
-    const double y = rsqrt_nr(x);
-    const double s = x * y;
-    return fma(fma(-s, s, x), 0.5 * y, s);
+    return sqrt_pos(x);
 }
 
 // a/b for finite normal b in binary64 from the refined reciprocal: the quotient
@@ -116,11 +120,12 @@ GCB_HD double div_nr(double a, double b) {
     return fma(fma(-b, q, a), r, q);
 }
 
-// E/B < f_E by the squares (production form).  Where the limit's square rounds
-// to 0, E^2 is either 0, and so below, or larger than it.
+// E/B < f_E > 0 by the squares (production form; the smallest number added
+// matters where the limit's square rounds to 0: E^2 is then either 0, and so
+// below, or larger)
 GCB_HD bool below_limit(double E2, double B, double f_E) {
     const double lim = f_E * B;
-    return E2 < fmax(lim * lim, 0x1p-1074) && f_E > 0.0;
+    return E2 < fma(lim, lim, 0x1p-1074);
 }
 
 // 2D Yee lattice offsets (cells) of Ex, Ey, Ez, Bx, By, Bz.

@@ -378,6 +378,10 @@ hipError_t move_arrays(const double* const* src, double* const* dst, int count,
     return launch_copy_arrays(L, stream);
 }
 
+// The threshold of rho~/dl: f_rho, or 0 -- no particle below it -- where f_E is 0,
+// as no E/B is below that either.
+double rho_limit(const gcb_params* prm) { return prm->f_E > 0.0 ? prm->f_rho : 0.0; }
+
 // the physics constants of a launch (geometry left to the caller)
 PushConst physics_const(const gcb_params* prm) {
     PushConst pc{};
@@ -385,7 +389,7 @@ PushConst physics_const(const gcb_params* prm) {
     pc.c = prm->c;
     pc.c2 = prm->c * prm->c;
     pc.inv_c2 = 1.0 / (prm->c * prm->c);
-    pc.f_rho = prm->f_rho;
+    pc.f_rho = rho_limit(prm);
     pc.f_E = prm->f_E;
     pc.fp_tol = prm->fp_tol;
     pc.qm = prm->qm;
@@ -1222,7 +1226,7 @@ int gcb_push_gr(gcb_ctx* ctx, gcb_gr_particles* p, const gcb_params* prm, int32_
     gr::GrConst g = ctx->gr;
     g.dt = prm->dt;
     g.qm = prm->qm;
-    g.f_rho = prm->f_rho;
+    g.f_rho = rho_limit(prm);
     g.f_E = prm->f_E;
     g.fp_tol = prm->fp_tol;
     g.mirror_tol = prm->mirror_tol;

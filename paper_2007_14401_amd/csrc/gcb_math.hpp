@@ -943,7 +943,7 @@ GCB_HD void boris(const R E[3], const R Bv[3], R& ux, R& uy, R& uz,
         // (a systematic rounding here would show in every rotation; no rotation
         // where u^2 overflows)
         const R g2 = (R)1 + ((umx * umx + umy * umy) + umz * umz) * K.inv_c2;
-        f = __builtin_isinf(g2) ? (R)0 : div_nr(hq, K.c * sqrt_nr(g2));
+        f = __builtin_isinf(g2) ? (R)0 : div_nr(hq, K.c * sqrt_pos(g2));
     } else {
         f = hq / (K.c * gamma_full(umx, umy, umz, K));
     }

@@ -49,7 +49,7 @@ def test_overflowing_momentum(dim, kernel, sort, tile):
 # scales of E and B, f_E, f_rho, and whether the guiding-center branch may be taken
 SWITCH = {"no E": (0.0, 1.0, 1e-170, 0.4, True), "E/B below": (1e-20, 1e150, 1e-165, 0.4, True),
           "E/B above": (1e-20, 1e150, 1e-175, 0.4, False),
-          "large f_E": (1.0, 1e-160, 1e200, np.inf, True)}
+          "large f_E": (1.0, 1e-160, 1e200, np.inf, True), "f_E 0": (0.0, 1.0, 0.0, 0.4, False)}
 
 
 @pytest.mark.parametrize("dim", [2, 3])
