@@ -664,8 +664,11 @@ GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
     double um[3], t[3], sv[3], up[3], un[3], x[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) um[i] = u[i] + hq * s.E[i];
-    const Gam<double> gm = gamma_full2(um[0], um[1], um[2], K);
-    const double f = div_nr(hq, K.c * sqrt_nr(1.0 + dot3(um, um) * K.inv_c2));   // as the push
+    // (1/Gamma is 0 where u^2 overflows: no rotation, no motion, and cotangents
+    // of u that pass through)
+    const double g2 = 1.0 + dot3(um, um) * K.inv_c2;
+    const double igm = __builtin_isinf(g2) ? 0.0 : rsqrt_nr(g2);
+    const double f = __builtin_isinf(g2) ? 0.0 : div_nr(hq, K.c * sqrt_pos(g2));   // as the push
 #pragma unroll
     for (int i = 0; i < 3; ++i) t[i] = f * s.B[i];
     const double g = 2.0 * rcp_nr0(1.0 + dot3(t, t));
@@ -677,17 +680,18 @@ GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
     cross3(up, sv, x);
 #pragma unroll
     for (int i = 0; i < 3; ++i) un[i] = (um[i] + x[i]) + hq * s.E[i];
-    const Gam<double> gn = gamma_full2(un[0], un[1], un[2], K);
+    const double gn2 = 1.0 + dot3(un, un) * K.inv_c2;
+    const double ign = __builtin_isinf(gn2) ? 0.0 : rsqrt_nr(gn2);
     // reverse: x^{n+1} = x^n + dt un/Gamma
     double unb[3] = {ub[0], ub[1], ub[2]}, igb = 0.0;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-        unb[a] += dt * gn.inv * lam[a];
+        unb[a] += dt * ign * lam[a];
         igb += dt * un[a] * lam[a];
     }
-    const double gnb = -igb * (gn.inv * gn.inv);
+    const double gnb = -igb * (ign * ign);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) unb[i] += (gnb * K.inv_c2 * gn.inv) * un[i];
+    for (int i = 0; i < 3; ++i) unb[i] += (gnb * K.inv_c2 * ign) * un[i];
     SampleBar<D> sb;
     double umb[3], upb[3], svb[3], tb[3];
     // un = uq + hq E, uq = um + up x s
@@ -705,11 +709,11 @@ GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
     for (int i = 0; i < 3; ++i) tb[i] += g * svb[i] + (2.0 * t2b) * t[i];
     // t = f B, f = hq/(c Gamma)
     const double fb = dot3(tb, s.B);
-    const double gmb = -fb * f * gm.inv;
+    const double gmb = -fb * f * igm;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         sb.v[3 + i] = f * tb[i];
-        umb[i] += (gmb * K.inv_c2 * gm.inv) * um[i];
+        umb[i] += (gmb * K.inv_c2 * igm) * um[i];
         sb.v[i] = hq * (unb[i] + umb[i]);
     }
     // (x, u) of the step start; the previous position has no part in the step,

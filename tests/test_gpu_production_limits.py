@@ -83,3 +83,37 @@ def test_extreme_switch_limit_curved():
         run.close()
     assert (tr[0] == 0).any()
     assert np.array_equal(tr[0], tr[1])
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+def test_overflowing_momentum_backwards(dim):
+    """One step backwards in uniform fields: a particle whose u^2 overflows does not
+    move or turn, so its cotangents pass through, and no node of the field cotangents
+    is lost to it."""
+    from paper_2007_14401_amd import gcb, state
+    cfg, run = uniform(dim)
+    n, k = 130, 2 * dim + 3
+    rng = np.random.default_rng(2)
+    lam = rng.normal(size=(k, n))
+    dev = lambda a, t=torch.float64: torch.as_tensor(a, dtype=t, device="cuda:0")
+    try:
+        ens = cfg.particles(n=n)
+        ens.ux[::3] = 1e160
+        t = state.to_device(ens)
+        end, start = [dev(v) for v in lam], [dev(0 * v) for v in lam]
+        F = run.cfg.fields()[0]
+        d = [dev(0 * F, torch.float32) for _ in range(6)]
+        parts = gcb.particles(t) if dim == 2 else gcb.particles3(t)
+        back = gcb.gcb_push_backward if dim == 2 else gcb.gcb_push_backward_3d
+        prm = gcb.params(dt=cfg.dt, c=cfg.c, qm=cfg.qm, f_rho=cfg.f_rho, f_E=cfg.f_E)
+        back(run.ctx, parts, prm, 1, end, start, d[:3], d[3:])
+        torch.cuda.synchronize()
+        got = np.stack([v.cpu().numpy() for v in start])
+        nodes = np.stack([v.cpu().numpy() for v in d])
+    finally:
+        run.close()
+    assert np.isfinite(got).all() and np.isfinite(nodes).all()
+    want = lam[:, ::3].copy()
+    want[:dim] += want[dim:2 * dim]
+    want[dim:2 * dim] = 0.0
+    assert np.array_equal(got[:, ::3], want)
