@@ -305,7 +305,7 @@ int gcb_push_noalloc(gcb_ctx* ctx, gcb_particles* p, const gcb_params* prm,
    GCB_EUNSUPPORTED): per step its cotangents are no further from exact ones
    than correctly rounded operations without contraction give (root mean square
    1.5e-16 relative for Boris, 3.0e-16 for guiding-center particles); the node
-   sums are binary64 per batch of steps, binary32 across batches.  The forward
+   sums are binary64 until they are added to dE and dB.  The forward
    steps are recomputed internally: with params.sort_every > 0 by the tiled push in place
    (keep_order), else by the cache-served kernel; needs n_steps * n * 61 +
    n * 12 bytes of context scratch beside the cell sort's. */

@@ -1,12 +1,14 @@
 """Build libgcb.so (HIP for gfx950) in-tree with hipcc.
 
 Each translation unit is compiled separately (in parallel) and linked into
-paper_2007_14401_amd/libgcb.so.  The binary64 push and adjoint units are
-compiled with -ffp-contract=off so that their arithmetic is evaluated exactly
-as written (no fused multiply-add: the parity build, GCB_ARITH_EXACT); the
-contracted binary64 push (GCB_ARITH_FAST, the production build) is the same
-source compiled with -ffp-contract=fast; the mixed-precision units may
-contract and use the hardware's binary32 reciprocal and square root.
+paper_2007_14401_amd/libgcb.so.  The binary64 push units are compiled with
+-ffp-contract=off so that their arithmetic is evaluated exactly as written (no
+fused multiply-add: the parity build, GCB_ARITH_EXACT); the contracted binary64
+push (GCB_ARITH_FAST, the production build) is the same source compiled with
+-ffp-contract=fast; the reverse sweep's units fuse multiply-adds within an
+expression as it is written (-ffp-contract=on), so that its two kernels give a
+particle the same bits; the mixed-precision units may contract and use the
+hardware's binary32 reciprocal and square root.
 """
 from __future__ import annotations
 
@@ -35,8 +37,8 @@ UNITS = {
     "gcb_host.hip": ["-ffp-contract=off"],
     "gcb_push_f64.hip": ["-ffp-contract=off"],
     "gcb_push_f64_fast.hip": ["-ffp-contract=fast"],
-    "gcb_adjoint.hip": ["-ffp-contract=fast"],
-    "gcb_adjoint3.hip": ["-ffp-contract=fast"],
+    "gcb_adjoint.hip": ["-ffp-contract=on"],
+    "gcb_adjoint3.hip": ["-ffp-contract=on"],
     "gcb_push_mixed.hip": FAST_F32,
     "gcb_sort.hip": ["-ffp-contract=off"],
     "gcb_util.hip": ["-ffp-contract=off"],

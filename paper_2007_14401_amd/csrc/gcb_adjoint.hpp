@@ -44,12 +44,16 @@ struct Dim<2> {
     using Push = PushConst;
     using Const = Consts<double>;
     using Acc = TileAcc<double>;
+    using Direct = GlobalAcc<double>;
     using Smp = Sample<double>;
     GCB_HD static const PushConst& base(const Push& pc) { return pc; }
     GCB_HD static Const consts(const Push& pc) { return make_consts<double>(pc); }
     GCB_HD static Acc acc(const double* lds, const double* F, const Push& pc, const int o[2],
                           int W) {
         return Acc{lds, F, pc.nx, pc.ny, o[0], o[1], W, false};
+    }
+    GCB_HD static Direct direct(const double* F, const Push& pc) {
+        return Direct{F, pc.nx, pc.ny};
     }
     GCB_HD static double inv_d(const Push& pc, int a) { return a == 0 ? pc.inv_dx : pc.inv_dy; }
     GCB_HD static double box(const Push& pc, int a) { return a == 0 ? pc.Lx : pc.Ly; }
@@ -59,8 +63,12 @@ struct Dim<2> {
     GCB_HD static int nodes(const Push& pc, int a) { return a == 0 ? pc.nx : pc.ny; }
     GCB_HD static double stagger(const Push& pc, int k, int a) { return pc.stagger[k][a]; }
     GCB_HD static constexpr int set(int k) { return kYeeSet[k]; }
-    template <bool kYee>
-    GCB_HD static void gather(const Acc& acc, const Push& pc, const Const& K, const double X[2],
+    // set(k) in the three bits from 3 k
+    GCB_HD static constexpr unsigned packed_sets() {
+        return set(0) | set(1) << 3 | set(2) << 6 | set(3) << 9 | set(4) << 12 | set(5) << 15;
+    }
+    template <bool kYee, class A>
+    GCB_HD static void gather(const A& acc, const Push& pc, const Const& K, const double X[2],
                               Smp& s) {
         gcb::gather<double, true, kYee>(acc, pc, K, X[0], X[1], s);
     }
@@ -73,6 +81,7 @@ struct Dim<3> {
     using Push = PushConst3;
     using Const = Consts3<double>;
     using Acc = TileAcc3<double>;
+    using Direct = GlobalAcc3<double>;
     using Smp = Sample3<double>;
     GCB_HD static const PushConst& base(const Push& pc) { return pc.b; }
     GCB_HD static Const consts(const Push& pc) { return make_consts3<double>(pc); }
@@ -80,6 +89,9 @@ struct Dim<3> {
                           int W) {
         return Acc{lds, GlobalAcc3<double>{F, pc.b.nx, pc.b.ny, pc.nz}, o[0], o[1], o[2], W,
                    false};
+    }
+    GCB_HD static Direct direct(const double* F, const Push& pc) {
+        return Direct{F, pc.b.nx, pc.b.ny, pc.nz};
     }
     GCB_HD static double inv_d(const Push& pc, int a) {
         return a == 0 ? pc.b.inv_dx : a == 1 ? pc.b.inv_dy : pc.inv_dz;
@@ -97,8 +109,11 @@ struct Dim<3> {
         return a < 2 ? pc.b.stagger[k][a] : pc.sz[k];
     }
     GCB_HD static constexpr int set(int k) { return kYee3Set[k]; }
-    template <bool kYee>
-    GCB_HD static void gather(const Acc& acc, const Push& pc, const Const& K, const double X[3],
+    GCB_HD static constexpr unsigned packed_sets() {
+        return set(0) | set(1) << 3 | set(2) << 6 | set(3) << 9 | set(4) << 12 | set(5) << 15;
+    }
+    template <bool kYee, class A>
+    GCB_HD static void gather(const A& acc, const Push& pc, const Const& K, const double X[3],
                               Smp& s) {
         gcb::gather3<double, true, kYee>(acc, pc, K, X[0], X[1], X[2], s);
     }
@@ -216,6 +231,29 @@ GCB_HD void locate(const typename Dim<D>::Push& pc, const int o[D], int W,
     }
 }
 
+// the sample of cells c from the field array
+template <bool kYee>
+GCB_HD void from_grid(const GlobalAcc<double>& g, const int c[2][Point<2, kYee>::kSets],
+                      Point<2, kYee>& p) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        double f00, f10, f01, f11;
+        g.quad(k, c[0][p.entry(k, 0)], c[1][p.entry(k, 1)], f00, f10, f01, f11);
+        eval_point(k, f00, f10, f01, f11, p);
+    }
+}
+
+template <bool kYee>
+GCB_HD void from_grid(const GlobalAcc3<double>& g, const int c[3][Point<3, kYee>::kSets],
+                      Point<3, kYee>& p) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        double f[8];
+        g.oct<double>(k, c[0][p.entry(k, 0)], c[1][p.entry(k, 1)], c[2][p.entry(k, 2)], f);
+        eval_point(k, f, p);
+    }
+}
+
 template <bool kYee>
 GCB_HD void sample_at(const TileAcc<double>& acc, const PushConst& pc, const double X[2],
                       Point<2, kYee>& p) {
@@ -242,13 +280,7 @@ GCB_HD void sample_at(const TileAcc<double>& acc, const PushConst& pc, const dou
             eval_point(k, f00, f10, f01, f11, p);
         }
     } else {
-        const GlobalAcc<double> g{acc.F, acc.nx, acc.ny};
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            double f00, f10, f01, f11;
-            g.quad(k, c[0][p.entry(k, 0)], c[1][p.entry(k, 1)], f00, f10, f01, f11);
-            eval_point(k, f00, f10, f01, f11, p);
-        }
+        from_grid(GlobalAcc<double>{acc.F, acc.nx, acc.ny}, c, p);
     }
 }
 
@@ -268,14 +300,24 @@ GCB_HD void sample_at(const TileAcc3<double>& acc, const PushConst3& pc, const d
             eval_point(k, f, p);
         }
     } else {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            double f[8];
-            acc.g.oct<double>(k, c[0][p.entry(k, 0)], c[1][p.entry(k, 1)],
-                              c[2][p.entry(k, 2)], f);
-            eval_point(k, f, p);
-        }
+        from_grid(acc.g, c, p);
     }
+}
+
+template <bool kYee>
+GCB_HD void sample_at(const GlobalAcc<double>& acc, const PushConst& pc, const double X[2],
+                      Point<2, kYee>& p) {
+    int c[2][Point<2, kYee>::kSets];
+    place<2>(pc, X, c, p);
+    from_grid(acc, c, p);
+}
+
+template <bool kYee>
+GCB_HD void sample_at(const GlobalAcc3<double>& acc, const PushConst3& pc, const double X[3],
+                      Point<3, kYee>& p) {
+    int c[3][Point<3, kYee>::kSets];
+    place<3>(pc, X, c, p);
+    from_grid(acc, c, p);
 }
 
 // The point as the sample that the forward functions take (a runaway point's
@@ -648,8 +690,8 @@ GCB_HD void parallel_back(const LocalD& L, double upar, double mu, double qm, bo
 // steps.  st = (x, previous x, u) at the step start; lam holds the cotangents
 // of the step outputs on entry and of its inputs on return.
 
-template <int D, bool kYee, class Win>
-GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
+template <int D, bool kYee, class Acc, class Win>
+GCB_HD void boris_vjp(const Acc& acc, const Win& win,
                       const typename Dim<D>::Push& pc, const typename Dim<D>::Const& K,
                       const double st[2 * D + 3], double qm, double lam[2 * D + 3]) {
     Point<D, kYee> p;
@@ -733,8 +775,8 @@ GCB_HD void boris_vjp(const typename Dim<D>::Acc& acc, const Win& win,
 
 constexpr int kMaxAdjIter = 8;   // fixed-point iterations the adjoint supports
 
-template <int D, bool kYee, class Win>
-GCB_HD void gca_vjp(const typename Dim<D>::Acc& acc, const Win& win,
+template <int D, bool kYee, class Acc, class Win>
+GCB_HD void gca_vjp(const Acc& acc, const Win& win,
                     const typename Dim<D>::Push& pc, const typename Dim<D>::Const& K,
                     const double st[2 * D + 3], double qm, double lam[2 * D + 3]) {
     using Smp = typename Dim<D>::Smp;

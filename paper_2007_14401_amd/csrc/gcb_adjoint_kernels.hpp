@@ -34,12 +34,20 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "gcb_adjoint.hpp"
 #include "gcb_internal.h"
 #include "gcb_queues.hpp"
 
 namespace gcb {
 namespace adj {
+
+// *p += v for a value of the gradient grid, by the memory's own addition
+__device__ __forceinline__ void grid_add(double* p, double v) {
+    __builtin_amdgcn_global_atomic_fadd_f64(
+        (__attribute__((address_space(1))) double*)p, v);
+}
 
 // Node cotangents: W^D nodes of six components in LDS, a plane per component,
 // covering global nodes [o, o + W) per axis (periodic).
@@ -48,7 +56,7 @@ struct Window {
     static constexpr int W = kAdjWindow<D>;
     static constexpr int kPlane = D == 2 ? W * W : W * W * W;
     double* lds;
-    float* grad;   // node-interleaved grid
+    double* grad;   // node-interleaved grid
     int o[D], n[D];
 
     __device__ void node(int k, const int c[D], double v) const {
@@ -67,7 +75,7 @@ struct Window {
             size_t g = 0;
 #pragma unroll
             for (int a = D - 1; a >= 0; --a) g = g * n[a] + wrap_index(c[a], n[a]);
-            atomicAdd(grad + g * 6 + k, (float)v);
+            grid_add(grad + g * 6 + k, v);
         }
     }
 
@@ -119,6 +127,119 @@ __device__ __forceinline__ size_t grid_row(const Window<D>& w, int row) {
     return g * w.n[0] * 6;
 }
 
+// particle p through the steps [s_lo, s_hi) of a segment, last to first
+template <int D, bool kYee, class Acc, class Win>
+__device__ __forceinline__ void sweep_particle(
+    const Acc& acc, const Win& win, const typename Dim<D>::Push& pc,
+    const typename Dim<D>::Const& K, int64_t p, const double* __restrict__ rec,
+    const double* __restrict__ qm_arr, const uint8_t* __restrict__ S, double* lam, int64_t n,
+    int s_lo, int s_hi) {
+    constexpr int kL = 2 * D + 3;
+    const double qm = qm_arr ? qm_arr[p] : Dim<D>::base(pc).qm;
+    double l[kL];
+#pragma unroll
+    for (int c = 0; c < kL; ++c) l[c] = lam[c * n + p];
+    for (int s = s_hi - 1; s >= s_lo; --s) {
+        const double* r = rec + (size_t)s * kL * n + p;
+        double st[kL];
+#pragma unroll
+        for (int c = 0; c < kL; ++c) st[c] = r[c * n];
+        if (S[(size_t)s * n + p] == 0)
+            gca_vjp<D, kYee>(acc, win, pc, K, st, qm, l);
+        else
+            boris_vjp<D, kYee>(acc, win, pc, K, st, qm, l);
+    }
+#pragma unroll
+    for (int c = 0; c < kL; ++c) lam[c * n + p] = l[c];
+}
+
+// Node cotangents of a wavefront's lanes, each to its own place in the grid: the
+// lanes of a call put their values into LDS (kPoints of them at a time) and then
+// add them together, so that neighbouring lanes add to neighbouring components
+// and nodes of one point, and an atomic instruction reaches a few cache lines
+// instead of one per lane.  All six components of a point at a time: three by
+// three they reach twice the lines (256^3, 1e6 particles, 4 steps: 21.2 -> 15.8 ms).
+template <int D, bool kYee>
+struct LaneSums {
+    static constexpr int kC = 1 << D;
+    static constexpr int kV = 6 * kC;                 // values of a point
+    static constexpr int kStride = kV + 1;            // in LDS
+    static constexpr int kPoints = D == 2 ? 64 : 32;
+    static constexpr int kSets = Point<D, kYee>::kSets;
+    static constexpr size_t kBytes =
+        kPoints * (kStride * sizeof(double) + D * kSets * sizeof(int));
+    double* val;   // kPoints x kStride, of the wavefront's own
+    int* cell;     // kPoints x D x kSets
+    double* grad;
+    int n[D];
+
+    template <bool kY>
+    __device__ void add(const typename Dim<D>::Push& pc, const double X[D],
+                        const Point<D, kY>& p, const SampleBar<D>& sb) const {
+        static_assert(kY == kYee, "the lattice of the kernel");
+        // the lanes of this call, numbered
+        const unsigned long long here = __ballot(1);
+        const int lanes = __popcll(here);
+        const int rank = __popcll(here & ((1ull << (threadIdx.x & 63)) - 1ull));
+        for (int first = 0; first < lanes; first += kPoints) {
+            const int own = rank - first;
+            if ((unsigned)own < (unsigned)kPoints) {
+                Point<D, kYee> t;
+                int c[D][kSets];
+                place<D>(pc, X, c, t);
+#pragma unroll
+                for (int a = 0; a < D; ++a)
+#pragma unroll
+                    for (int s = 0; s < kSets; ++s)
+                        cell[(own * D + a) * kSets + s] = wrap_index(c[a][s], n[a]);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    double q[kC];
+                    nodes_back(p, sb, k, q);
+#pragma unroll
+                    for (int i = 0; i < kC; ++i) val[own * kStride + i * 6 + k] = q[i];
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int all = min(kPoints, lanes - first) * kV;
+#pragma unroll 4
+            for (int e = rank; e < all; e += lanes) {
+                const int pt = e / kV, u = e - pt * kV;
+                const int corner = u / 6, k = u - corner * 6;
+                const double v = val[pt * kStride + u];
+                size_t g = 0;
+#pragma unroll
+                for (int a = D - 1; a >= 0; --a) {
+                    const int s = kYee ? (Dim<D>::packed_sets() >> (3 * k + a)) & 1 : k;
+                    int m = cell[(pt * D + a) * kSets + s] + ((corner >> a) & 1);
+                    m = m == n[a] ? 0 : m;
+                    g = g * n[a] + m;
+                }
+                if (v != 0.0) grid_add(grad + g * 6 + k, v);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    }
+};
+
+// The wavefronts of a workgroup take the slices of 64 of its two queues (see
+// split_queues): nG of m entries in the first
+template <class Sweep>
+__device__ __forceinline__ void take_slices(int nG, int m, int* next_slice, Sweep&& sweep) {
+    const int lane = threadIdx.x & 63;
+    const int sG = (nG + 63) >> 6;
+    const int sAll = sG + ((m - nG + 63) >> 6);
+    for (;;) {
+        int sl = 0;
+        if (lane == 0) sl = atomicAdd(next_slice, 1);
+        sl = __builtin_amdgcn_readfirstlane(sl);
+        if (sl >= sAll) break;
+        const bool gslice = sl < sG;
+        const int q = gslice ? sl * 64 + lane : nG + (sl - sG) * 64 + lane;
+        if (q < (gslice ? nG : m)) sweep(q);
+    }
+}
+
 // One workgroup per chunk of a tile's particles (chunk c of the launch: tile
 // t with starts[t] <= c < starts[t+1], particles [c - starts[t]] * part of the
 // tile's), for the steps [s_lo, s_hi) of a segment, last to first.  Slot p of
@@ -131,23 +252,25 @@ k_adjoint_batch(const double* __restrict__ rec, const double* __restrict__ qm_ar
                 const int32_t* __restrict__ tile_start, const int32_t* __restrict__ starts,
                 int ntx, int nty, int ntiles, int tile, int part, double* lam, int64_t n,
                 int s_lo, int s_hi, const double* __restrict__ F, typename Dim<D>::Push pc,
-                float* grad) {
+                double* grad) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int wave_g[kAdjWG / 64];
     __shared__ int wave_b[kAdjWG / 64];
     __shared__ int next_slice;
-    constexpr int kL = 2 * D + 3;
     constexpr int W = Window<D>::W;
     constexpr int kAll = 6 * Window<D>::kPlane;
-    double* F_lds = reinterpret_cast<double*>(smem);
-    double* win_lds = F_lds + kAll;
-    uint16_t* queue = reinterpret_cast<uint16_t*>(win_lds + kAll);
 
     // consecutive chunks on the same XCD (workgroup b runs on XCD b % 8)
     const int total = starts[ntiles];
     const int per = (total + 7) / 8;
-    const int chunk = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-    if ((int)(blockIdx.x / 8) >= per || chunk >= total) return;
+    const int turn = (int)(blockIdx.x / 8);
+    if (turn >= per) return;
+    const int chunk = (int)(blockIdx.x % 8) * per + turn;
+    if (chunk >= total) return;
+    double* F_lds = reinterpret_cast<double*>(smem);
+    double* win_lds = F_lds + kAll;
+    uint16_t* queue = reinterpret_cast<uint16_t*>(win_lds + kAll);
+
     int t0 = 0, t1 = ntiles;   // starts[t0] <= chunk < starts[t1]
     while (t1 - t0 > 1) {
         const int m = (t0 + t1) >> 1;
@@ -207,66 +330,120 @@ k_adjoint_batch(const double* __restrict__ rec, const double* __restrict__ qm_ar
     const int nG = split_queues<kAdjWG>(m, queue, wave_g, wave_b,
                                         [&](int q) { return Slast[perm[p0 + q]] == 0; });
     __syncthreads();
-
     const typename Dim<D>::Const K = Dim<D>::consts(pc);
-    const int lane = threadIdx.x & 63;
-    const int sG = (nG + 63) >> 6;
-    const int sAll = sG + ((m - nG + 63) >> 6);
-    for (;;) {
-        int sl = 0;
-        if (lane == 0) sl = atomicAdd(&next_slice, 1);
-        sl = __builtin_amdgcn_readfirstlane(sl);
-        if (sl >= sAll) break;
-        const bool gslice = sl < sG;
-        const int q = gslice ? sl * 64 + lane : nG + (sl - sG) * 64 + lane;
-        if (q < (gslice ? nG : m)) {
-            const int64_t p = perm[p0 + queue[q]];
-            const double qm = qm_arr ? qm_arr[p] : Dim<D>::base(pc).qm;
-            double l[kL];
-#pragma unroll
-            for (int c = 0; c < kL; ++c) l[c] = lam[c * n + p];
-            for (int s = s_hi - 1; s >= s_lo; --s) {
-                const double* r = rec + (size_t)s * kL * n + p;
-                double st[kL];
-#pragma unroll
-                for (int c = 0; c < kL; ++c) st[c] = r[c * n];
-                if (S[(size_t)s * n + p] == 0)
-                    gca_vjp<D, kYee>(acc, win, pc, K, st, qm, l);
-                else
-                    boris_vjp<D, kYee>(acc, win, pc, K, st, qm, l);
-            }
-#pragma unroll
-            for (int c = 0; c < kL; ++c) lam[c * n + p] = l[c];
-        }
-    }
+    take_slices(nG, m, &next_slice, [&](int q) {
+        sweep_particle<D, kYee>(acc, win, pc, K, perm[p0 + queue[q]], rec, qm_arr, S, lam, n, s_lo,
+                                s_hi);
+    });
     __syncthreads();
     // the window to the grid, the values of a row of nodes by neighbouring lanes
     for (int row = threadIdx.x >> 6; row < kRows; row += kAdjWG / 64) {
-        float* dst = grad + grid_row(win, row);
+        double* dst = grad + grid_row(win, row);
         for (int e = threadIdx.x & 63; e < 6 * W; e += 64) {
             const int c = e / 6, k = e - 6 * c;
             const double v = win_lds[(k * kRows + row) * W + c];
-            if (v != 0.0) atomicAdd(dst + wrap_index(win.o[0] + c, win.n[0]) * 6 + k, (float)v);
+            if (v != 0.0) grid_add(dst + wrap_index(win.o[0] + c, win.n[0]) * 6 + k, v);
         }
     }
+}
+
+// The same for the particles of tiles with few of them (loose[t]: such particles
+// in the tiles before t), `part` per workgroup in the order of the sort: a
+// window of LDS and a workgroup would serve a few lanes there, so these gather
+// from the grid and add to it.  Bound by those additions once the device is full
+// (5e10 per second), by the latency of a step below.  A particle's bits are those
+// of the other kernel: the same source, with multiply-adds fused as it is written
+// (-ffp-contract=on).
+//   3D, 256^3, 1e5 particles, 4 steps: 19.9 ms with a window per tile, 2.0 here;
+//   2D, 4096^2, 1e5, 8 steps: 7.8 and 1.4 ms.
+template <int D, bool kYee>
+__global__ __launch_bounds__(kLooseWG) __attribute__((amdgpu_waves_per_eu(2))) void
+k_adjoint_loose(const double* __restrict__ rec, const double* __restrict__ qm_arr,
+                const uint8_t* __restrict__ S, const uint32_t* __restrict__ perm,
+                const int32_t* __restrict__ tile_start, const int32_t* __restrict__ loose,
+                int ntiles, int part, double* lam, int64_t n, int s_lo, int s_hi,
+                const double* __restrict__ F, typename Dim<D>::Push pc, double* grad) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int wave_g[kLooseWG / 64];
+    __shared__ int wave_b[kLooseWG / 64];
+    __shared__ int next_slice;
+    __shared__ uint32_t id[kLoosePart];
+    __shared__ uint16_t queue[kLoosePart];
+    // consecutive chunks on the same XCD, as above
+    const int total = loose[ntiles];
+    const int per = ((total + part - 1) / part + 7) / 8;
+    const int turn = (int)(blockIdx.x / 8);
+    if (turn >= per) return;
+    const int64_t at0 = ((int64_t)(blockIdx.x % 8) * per + turn) * part;
+    if (at0 >= total) return;
+    const int first = (int)at0;
+    const int m = min(part, total - first);
+
+    LaneSums<D, kYee> sums;
+    unsigned char* own = smem + (threadIdx.x >> 6) * LaneSums<D, kYee>::kBytes;
+    sums.val = reinterpret_cast<double*>(own);
+    sums.cell = reinterpret_cast<int*>(sums.val + LaneSums<D, kYee>::kPoints * LaneSums<D, kYee>::kStride);
+    sums.grad = grad;
+#pragma unroll
+    for (int a = 0; a < D; ++a) sums.n[a] = Dim<D>::nodes(pc, a);
+    const typename Dim<D>::Direct acc = Dim<D>::direct(F, pc);
+
+    if (threadIdx.x == 0) next_slice = 0;
+    const uint8_t* Slast = S + (size_t)(s_hi - 1) * n;
+    const int nG = split_queues<kLooseWG>(m, queue, wave_g, wave_b, [&](int q) {
+        const int at = first + q;
+        int t0 = 0, t1 = ntiles;   // loose[t0] <= at < loose[t1]
+        while (t1 - t0 > 1) {
+            const int h = (t0 + t1) >> 1;
+            if (loose[h] <= at) t0 = h; else t1 = h;
+        }
+        const uint32_t p = perm[tile_start[t0] + (at - loose[t0])];
+        id[q] = p;
+        return Slast[p] == 0;
+    });
+    __syncthreads();
+    const typename Dim<D>::Const K = Dim<D>::consts(pc);
+    take_slices(nG, m, &next_slice, [&](int q) {
+        sweep_particle<D, kYee>(acc, sums, pc, K, id[queue[q]], rec, qm_arr, S, lam, n, s_lo,
+                                s_hi);
+    });
 }
 
 template <int D, bool kYee>
 hipError_t launch_batch(const AdjointLaunch& L, const typename Dim<D>::Push& pc,
                         hipStream_t stream) {
-    auto kfn = k_adjoint_batch<D, kYee>;
-    constexpr size_t lds = adj_lds_bytes<D>();
-    hipError_t e = hipFuncSetAttribute((const void*)kfn,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    // at most one partly filled chunk per tile beside the full ones; the
+    hipError_t e = hipSuccess;
+    // of the chunks at most one partly filled per tile beside the full ones; the
     // kernel deals them out in eight runs
-    const int64_t most = L.ntiles + L.n / L.part;
-    hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * ((most + 7) / 8))), dim3(kAdjWG), lds, stream,
-                       L.states, L.qm, L.strace, L.perm, L.tile_start, L.chunk_starts, L.ntx,
-                       L.nty, L.ntiles, kAdjTile<D>, L.part, L.lam, L.n, L.s_lo, L.s_hi,
-                       L.fields, pc, L.grad_fields);
-    return hipGetLastError();
+    const int64_t most = std::min<int64_t>(L.ntiles, L.n / L.few) + L.n / L.part;
+    if (most > 0) {
+        auto kfn = k_adjoint_batch<D, kYee>;
+        constexpr size_t lds = adj_lds_bytes<D>();
+        e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * ((most + 7) / 8))), dim3(kAdjWG), lds,
+                           stream, L.states, L.qm, L.strace, L.perm, L.tile_start,
+                           L.chunk_starts, L.ntx, L.nty, L.ntiles, kAdjTile<D>, L.part, L.lam,
+                           L.n, L.s_lo, L.s_hi, L.fields, pc, L.grad_fields);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (L.few > 1) {   // (else no tile has fewer)
+        auto kfn = k_adjoint_loose<D, kYee>;
+        constexpr size_t lds = (kLooseWG / 64) * LaneSums<D, kYee>::kBytes;
+        static_assert(lds + 8 * kLoosePart <= 80 * 1024, "two workgroups per compute unit");
+        e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds);
+        if (e != hipSuccess) return e;
+        const int part = std::min(L.part, kLoosePart);
+        const int64_t parts = (L.n + part - 1) / part;
+        hipLaunchKernelGGL(kfn, dim3((unsigned)(8 * ((parts + 7) / 8))), dim3(kLooseWG), lds,
+                           stream, L.states, L.qm, L.strace, L.perm, L.tile_start,
+                           L.loose_starts, L.ntiles, part, L.lam, L.n, L.s_lo, L.s_hi, L.fields,
+                           pc, L.grad_fields);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace adj

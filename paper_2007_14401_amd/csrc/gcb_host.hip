@@ -466,6 +466,39 @@ int adjoint_part(int64_t n) {
     return (int)std::max<int64_t>(64, std::min<int64_t>(part, kAdjPart));
 }
 
+// Particles below which a tile gets no workgroup of its own in the reverse sweep
+// (1: every tile has one).  A workgroup with its window costs the same for one
+// particle as for a wavefront of them, 0.35 us of the device in 3D (4 steps) and
+// 0.5 us in 2D (8 steps); a particle of k_adjoint_loose 16 and 8 ns, for its
+// additions to the grid.  By the mean per tile, so that a call has all its tiles
+// on one side of it, but for crowded tiles of an empty box: the two kernels run
+// one after the other.  Whole backward calls, with windows / without:
+// 3D, 256^3: 12.6 per tile 54.4 / 39.1 ms, 25 56.8 / 53.4, 31 57.5 / 60.7;
+// 2D, 4096^2: 6.1 per tile 12.3 / 6.2 ms, 30.5 13.1 / 11.7, 43 13.3 / 14.4.
+// Where every tile has a compute unit soon the window's shorter step counts
+// (64^3, 1331 tiles, 3e3 particles: 0.87 / 0.94 ms).
+template <int D>
+int adjoint_few(int64_t n, int64_t ntiles) {
+    constexpr int kMean = D == 2 ? 36 : 28;
+    return std::min(n, ntiles) <= 2048 || n >= kMean * ntiles ? 1 : 64;
+}
+
+// Tables of the reverse sweep's chunks, in one buffer
+struct ChunkTables {
+    uint64_t* sums;
+    int32_t *starts, *loose;
+};
+
+int chunk_tables(gcb_ctx* ctx, int ntiles, ChunkTables& t) {
+    const size_t ns = (size_t)chunk_sums_elems(ntiles), nt = (size_t)ntiles + 1;
+    const int rc = ensure(ctx, ctx->adj_chunks, ns * 8 + 2 * nt * 4);
+    if (rc) return rc;
+    t.sums = static_cast<uint64_t*>(ctx->adj_chunks.ptr);
+    t.starts = reinterpret_cast<int32_t*>(t.sums + ns);
+    t.loose = t.starts + nt;
+    return GCB_OK;
+}
+
 // Halo of the LDS window in nodes: the drift bound c dt per step over the
 // steps between sorts, plus one node for the stencil.  Formed in binary64;
 // 0 when it exceeds kMaxHalo (no window that large fits in LDS, and the int
@@ -1004,7 +1037,7 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
     if ((rc = ensure(ctx, ctx->adj_trace, (size_t)n_steps * n))) return rc;
     if ((rc = ensure(ctx, ctx->adj_lam, 7 * nd))) return rc;
     if ((rc = ensure(ctx, ctx->adj_work, 7 * nd + (size_t)n))) return rc;
-    if ((rc = ensure(ctx, ctx->adj_grad, nodes * 6 * sizeof(float)))) return rc;
+    if ((rc = ensure(ctx, ctx->adj_grad, nodes * 6 * sizeof(double)))) return rc;
     // The segment runs on its particles in the tile order of their start
     // positions (the reverse sweep's tiles): the state, q/m and the adjoint
     // are permuted on the way in and the adjoint back on the way out.  Each
@@ -1027,7 +1060,7 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
     double* states = static_cast<double*>(ctx->adj_states.ptr);
     uint8_t* trace = static_cast<uint8_t*>(ctx->adj_trace.ptr);
     double* lam = static_cast<double*>(ctx->adj_lam.ptr);
-    float* grad = static_cast<float*>(ctx->adj_grad.ptr);
+    double* grad = static_cast<double*>(ctx->adj_grad.ptr);
     const double* src[7] = {start->x, start->y, start->xp, start->yp,
                             static_cast<const double*>(start->ux),
                             static_cast<const double*>(start->uy),
@@ -1085,7 +1118,7 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
     }
     // reverse sweep
     if (n > 0) GCB_HIP(move_arrays(lam_end, lams, 7, perm, n, false, stream));
-    GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(float), stream));
+    GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(double), stream));
     // steps in reverse order, in batches [s_lo, s_hi), the particles sorted by
     // their positions halfway
     if (ordered) {
@@ -1093,7 +1126,8 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
         const int ntiles = og.ntx * og.nty;
         SortBuffers ssb{};
         if ((rc = prepare_sort(ctx, n, ntiles, ssb))) return rc;
-        if ((rc = ensure(ctx, ctx->adj_chunks, (size_t)(ntiles + 1) * 4))) return rc;
+        ChunkTables ct;
+        if ((rc = chunk_tables(ctx, ntiles, ct))) return rc;
         AdjointLaunch A;
         A.yee = ctx->yee;
         A.fields = static_cast<const double*>(ctx->fields.ptr);
@@ -1107,7 +1141,9 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
         A.nty = og.nty;
         A.ntiles = ntiles;
         A.part = adjoint_part(n);
-        A.chunk_starts = static_cast<int32_t*>(ctx->adj_chunks.ptr);
+        A.few = adjoint_few<2>(n, ntiles);
+        A.chunk_starts = ct.starts;
+        A.loose_starts = ct.loose;
         A.lam = lam;
         A.grad_fields = grad;
         for (int32_t s_hi = n_steps; s_hi > 0; s_hi -= batch) {
@@ -1116,8 +1152,8 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
             const double* at = states + (size_t)((A.s_lo + s_hi) / 2) * 7 * n;
             GCB_HIP(launch_cell_sort(at, at + n, n, 1.0 / ctx->dx, 1.0 / ctx->dy, og, ssb,
                                      stream));
-            GCB_HIP(launch_chunk_starts(A.tile_start, ntiles, A.part,
-                                        static_cast<int32_t*>(ctx->adj_chunks.ptr), stream));
+            GCB_HIP(launch_chunk_starts(A.tile_start, ntiles, A.part, A.few, ct.starts,
+                                        ct.loose, ct.sums, stream));
             GCB_HIP(launch_adjoint_batch(A, pc, stream));
         }
     }
@@ -1431,7 +1467,7 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
     if ((rc = ensure(ctx, ctx->adj_trace, (size_t)n_steps * n))) return rc;
     if ((rc = ensure(ctx, ctx->adj_lam, kS * nd))) return rc;
     if ((rc = ensure(ctx, ctx->adj_work, kS * nd + (size_t)n))) return rc;
-    if ((rc = ensure(ctx, ctx->adj_grad, nodes * 6 * sizeof(float)))) return rc;
+    if ((rc = ensure(ctx, ctx->adj_grad, nodes * 6 * sizeof(double)))) return rc;
     // the segment's particles in the tile order of their start positions, as
     // in the 2D backward (cubic tiles)
     TileGeom3 og{};
@@ -1452,7 +1488,7 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
     double* states = static_cast<double*>(ctx->adj_states.ptr);
     uint8_t* trace = static_cast<uint8_t*>(ctx->adj_trace.ptr);
     double* lam = static_cast<double*>(ctx->adj_lam.ptr);
-    float* grad = static_cast<float*>(ctx->adj_grad.ptr);
+    double* grad = static_cast<double*>(ctx->adj_grad.ptr);
     const double* src[kS] = {start->x,  start->y,  start->z,
                              start->xp, start->yp, start->zp,
                              static_cast<const double*>(start->ux),
@@ -1534,7 +1570,7 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
     }
     // reverse sweep
     if (n > 0) GCB_HIP(move_arrays(lam_end, lams, kS, perm, n, false, stream));
-    GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(float), stream));
+    GCB_HIP(hipMemsetAsync(grad, 0, nodes * 6 * sizeof(double), stream));
     if (ordered) {
         const double inv_min =
             std::max(1.0 / ctx->d3[0], std::max(1.0 / ctx->d3[1], 1.0 / ctx->d3[2]));
@@ -1542,7 +1578,8 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
         const int ntiles = og.ntx * og.nty * og.ntz;
         SortBuffers ssb{};
         if ((rc = prepare_sort(ctx, n, ntiles, ssb))) return rc;
-        if ((rc = ensure(ctx, ctx->adj_chunks, (size_t)(ntiles + 1) * 4))) return rc;
+        ChunkTables ct;
+        if ((rc = chunk_tables(ctx, ntiles, ct))) return rc;
         AdjointLaunch A;
         A.yee = ctx->yee3;
         A.fields = static_cast<const double*>(ctx->fields3.ptr);
@@ -1556,7 +1593,9 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
         A.nty = og.nty;
         A.ntiles = ntiles;
         A.part = adjoint_part(n);
-        A.chunk_starts = static_cast<int32_t*>(ctx->adj_chunks.ptr);
+        A.few = adjoint_few<3>(n, ntiles);
+        A.chunk_starts = ct.starts;
+        A.loose_starts = ct.loose;
         A.lam = lam;
         A.grad_fields = grad;
         for (int32_t s_hi = n_steps; s_hi > 0; s_hi -= batch) {
@@ -1565,8 +1604,8 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
             const double* at = states + (size_t)((A.s_lo + s_hi) / 2) * kS * n;
             GCB_HIP(launch_cell_sort3(at, at + n, at + 2 * n, n, 1.0 / ctx->d3[0],
                                       1.0 / ctx->d3[1], 1.0 / ctx->d3[2], og, ssb, stream));
-            GCB_HIP(launch_chunk_starts(A.tile_start, ntiles, A.part,
-                                        static_cast<int32_t*>(ctx->adj_chunks.ptr), stream));
+            GCB_HIP(launch_chunk_starts(A.tile_start, ntiles, A.part, A.few, ct.starts,
+                                        ct.loose, ct.sums, stream));
             GCB_HIP(launch_adjoint3_batch(A, pc, stream));
         }
     }

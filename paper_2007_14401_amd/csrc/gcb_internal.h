@@ -196,6 +196,9 @@ template <int D>
 constexpr int kAdjWindow = D == 2 ? 40 : 11;
 template <int D>
 constexpr int kAdjTile = D == 2 ? 32 : 6;
+// Threads and most particles of a workgroup that takes those of tiles with few.
+constexpr int kLooseWG = 256;
+constexpr int kLoosePart = 1024;
 template <int D>
 constexpr size_t adj_lds_bytes() {
     return (size_t)6 * kAdjWindow<D> * kAdjWindow<D> * (D == 3 ? kAdjWindow<D> : 1) *
@@ -216,20 +219,26 @@ struct AdjointLaunch {
     const int32_t* tile_start;    // its tiles (ntx x nty (x ntz), kAdjTile cells)
     int ntx, nty, ntiles;
     int part;                     // particles per chunk, at most kAdjPart
+    int few;                      // particles below which a tile gets no chunk
     const int32_t* chunk_starts;  // launch_chunk_starts
+    const int32_t* loose_starts;
     double* lam;                  // 7 or 9 arrays of n: cotangents, in place
     int s_lo, s_hi;
-    float* grad_fields;           // node-interleaved gradient accumulators
+    double* grad_fields;          // node-interleaved gradient accumulators
 };
 
-// starts[t] (ntiles + 1): chunks of `part` particles in the tiles before t
-hipError_t launch_chunk_starts(const int32_t* tile_start, int ntiles, int part, int32_t* starts,
+// starts[t], loose[t] (ntiles + 1 each): in the tiles before t, the chunks of
+// `part` particles of those with at least `few`, the particles of the others
+// (sums: chunk_sums_elems of scratch)
+int64_t chunk_sums_elems(int ntiles);
+hipError_t launch_chunk_starts(const int32_t* tile_start, int ntiles, int part, int few,
+                               int32_t* starts, int32_t* loose, uint64_t* sums,
                                hipStream_t stream);
 hipError_t launch_adjoint_batch(const AdjointLaunch& L, const PushConst& pc, hipStream_t stream);
 hipError_t launch_adjoint3_batch(const AdjointLaunch& L, const PushConst3& pc,
                                  hipStream_t stream);
 
-hipError_t launch_deinterleave_add(const float* grad_fields, int nx, int ny,
+hipError_t launch_deinterleave_add(const double* grad_fields, int nx, int ny,
                                    float* const out[6], hipStream_t stream);
 
 // curved-spacetime push (gcb_gr.hip)

@@ -25,12 +25,12 @@ struct SixOut {
     float* c[6];
 };
 
-__global__ __launch_bounds__(kWG) void k_deinterleave_add(const float* __restrict__ g,
+__global__ __launch_bounds__(kWG) void k_deinterleave_add(const double* __restrict__ g,
                                                           int64_t nodes, SixOut out) {
     const int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x;
     if (i >= nodes) return;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) out.c[k][i] += g[i * 6 + k];
+    for (int k = 0; k < 6; ++k) out.c[k][i] += (float)g[i * 6 + k];
 }
 
 template <typename U>
@@ -223,7 +223,7 @@ hipError_t launch_interleave_fields(const double* const comps[6], int nx, int ny
     return hipGetLastError();
 }
 
-hipError_t launch_deinterleave_add(const float* grad_fields, int nx, int ny,
+hipError_t launch_deinterleave_add(const double* grad_fields, int nx, int ny,
                                    float* const out[6], hipStream_t stream) {
     SixOut o;
     for (int k = 0; k < 6; ++k) o.c[k] = out[k];

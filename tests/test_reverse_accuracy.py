@@ -69,7 +69,7 @@ extern "C" void step(const in64* F_, int nx, int ny, const in64* par, const in64
 
 @pytest.fixture(scope="module")
 def libs(tmp_path_factory):
-    return (compile_host(str(tmp_path_factory.mktemp("v64")), SOURCE, "-ffp-contract=fast"),
+    return (compile_host(str(tmp_path_factory.mktemp("v64")), SOURCE, "-ffp-contract=on"),
             compile_host(str(tmp_path_factory.mktemp("v80")), SOURCE, "-ffp-contract=off",
                          "-DEXTENDED"))
 
