@@ -12,13 +12,17 @@
 //                  exclusive scan, 3 kernels)
 //   k_bucket_sort  a workgroup per bucket: counting sort by the low bits, which
 //                  also gives tile_start (with 256 tiles or fewer the scatter
-//                  does that, and is the last step)
+//                  does that, and is the last step); of larger buckets, which
+//                  particles gathered in a few tiles make, the counts of their
+//                  parts
+//   k_bucket_parts those parts, a workgroup each (nothing to do for it costs
+//                  1.5 us; not launched where no bucket can be larger)
 // Launches and their gaps are most of a sort of 1e5 particles, and the passes
-// over the keys of one of 1e6: two or three kernels where an LSD radix sort of
+// over the keys of one of 1e6: two to four kernels where an LSD radix sort of
 // two digits has twelve (keys; histogram, scan, scatter of each digit; tile
-// bounds).  1e6 particles, 2704 tiles: 92 -> 35 us.  A bucket that holds far
-// more particles than the others is sorted by one workgroup, as its tiles are
-// pushed by one each.
+// bounds).  1e6 particles, 2704 tiles: 93 -> 45 us; all of them in one tile 145
+// -> 76, half of them 91 -> 66 (1.95 and 0.94 ms with one workgroup per bucket,
+// which sorts 16384 particles in some 50 us).
 // Otherwise LSD radix sort, 8 bits per pass, and k_tile_bounds: with 256 buckets
 // of many particles each the bucket sort has too few wavefronts (1e7 particles,
 // 1024 (r, theta) tiles: 12.66 ms of a push with it, 12.44 without).
@@ -356,33 +360,19 @@ __global__ __launch_bounds__(kWaves * 64) void k_scatter(
     }
 }
 
-// Counting sort of one bucket (the particles of the 2^low tiles from
-// blockIdx.x << low) by the low bits, and the starts of its tiles.
 constexpr int kBucketWG = 1024;
-__global__ __launch_bounds__(kBucketWG) void k_bucket_sort(
-    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ idx, int64_t n, int low,
-    int ntiles, int32_t* tile_start, uint32_t* idx_out) {
+constexpr int kBucketMost = 16384;   // particles of a bucket that one workgroup sorts
+constexpr int kPart = 8192;          // those of a larger one that a workgroup takes
+
+// The particles [s, e) of a bucket to their places by the low bits of their keys:
+// base[d] the next place of digit d (LDS, of 256).
+__device__ __forceinline__ void place_by_low(const uint32_t* __restrict__ keys,
+                                             const uint32_t* __restrict__ idx, int64_t s,
+                                             int64_t e, int low, uint32_t* base,
+                                             uint32_t (*wcount)[256], uint32_t* idx_out) {
     constexpr int kWaves = kBucketWG / 64, kChunk = kBucketWG * kGroups;
-    __shared__ uint32_t wcount[kWaves][256];
-    __shared__ uint32_t base[256];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const uint32_t mask = (1u << low) - 1u;
-    const int t0 = (int)blockIdx.x << low;
-    const int64_t s = tile_start[t0];
-    const int64_t e = t0 + (1 << low) < ntiles ? tile_start[t0 + (1 << low)] : n;
-    if (threadIdx.x < 256) base[threadIdx.x] = 0;
-    __syncthreads();
-    for (int64_t p = s + threadIdx.x; p < e; p += kBucketWG)
-        atomicAdd(&base[keys[p] & mask], 1u);
-    __syncthreads();
-    if (wave == 0) scan_256(base);
-    __syncthreads();
-    if (threadIdx.x < 256) {
-        const int d = threadIdx.x;
-        base[d] += (uint32_t)s;
-        if (d > 0 && d < (1 << low) && t0 + d < ntiles) tile_start[t0 + d] = (int32_t)base[d];
-    }
     for (int64_t c0 = s; c0 < e; c0 += kChunk) {
         __syncthreads();
         for (int d = threadIdx.x; d < 256 * kWaves; d += kBucketWG) (&wcount[0][0])[d] = 0;
@@ -390,7 +380,7 @@ __global__ __launch_bounds__(kBucketWG) void k_bucket_sort(
         const int64_t w0 = c0 + wave * (kGroups * 64);
         uint32_t rank[kGroups];
         uint32_t dig[kGroups];
-        wave_ranks(keys, w0, e, 0, mask, low, wcount[wave], rank, dig);
+        wave_ranks(keys, w0, e, 0, (1u << low) - 1u, low, wcount[wave], rank, dig);
         __syncthreads();
         if (threadIdx.x < 256) {
             const int d = threadIdx.x;
@@ -410,6 +400,135 @@ __global__ __launch_bounds__(kBucketWG) void k_bucket_sort(
             if (p < e) idx_out[wcount[wave][dig[gi]] + rank[gi]] = idx[p];
         }
     }
+}
+
+// counts of the low bits of the keys of [s, e), in LDS (256)
+__device__ __forceinline__ void count_low(const uint32_t* __restrict__ keys, int64_t s, int64_t e,
+                                          int low, uint32_t* count) {
+    if (threadIdx.x < 256) count[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t p = s + threadIdx.x; p < e; p += kBucketWG)
+        atomicAdd(&count[keys[p] & ((1u << low) - 1u)], 1u);
+    __syncthreads();
+}
+
+// the starts of a bucket's tiles but the first, from t0 + 1 on
+__device__ __forceinline__ void note_starts(const uint32_t* base, int low, int t0, int ntiles,
+                                            int32_t* tile_start) {
+    const int d = threadIdx.x;
+    if (d > 0 && d < (1 << low) && t0 + d < ntiles) tile_start[t0 + d] = (int32_t)base[d];
+}
+
+// A part of a bucket of more than kBucketMost particles: the i-th over all such
+// buckets.  `first` is the number of the bucket's first part, `parts` how many
+// it has (0: there are not so many parts).  Called by the whole workgroup.
+struct BucketPart {
+    int t0, first, parts;
+    int64_t s, e;   // the part's particles
+    int64_t s0;     // the bucket's first
+
+    __device__ void find(int i, const int32_t* tile_start, int64_t n, int low, int ntiles,
+                         uint32_t* before /* LDS, 257 */, uint32_t* total) {
+        const int buckets = ((ntiles - 1) >> low) + 1;
+        const int b = threadIdx.x;
+        auto start = [&](int k) -> int64_t { return k < buckets ? tile_start[k << low] : n; };
+        if (b < 256) {
+            const int64_t m = b < buckets ? start(b + 1) - start(b) : 0;
+            before[b] = m > kBucketMost ? (uint32_t)((m + kPart - 1) / kPart) : 0u;
+            if (b == 255) before[256] = before[255];
+        }
+        __syncthreads();
+        if (b < 64) scan_256(before);
+        __syncthreads();
+        if (b == 0) before[256] += before[255];
+        __syncthreads();
+        *total = before[256];
+        parts = 0;
+        if (i >= (int)before[256]) return;
+        int lo = 0, hi = 256;   // before[lo] <= i < before[hi]
+        while (hi - lo > 1) {
+            const int h = (lo + hi) >> 1;
+            if ((int)before[h] <= i) lo = h; else hi = h;
+        }
+        first = (int)before[lo];
+        parts = (int)before[lo + 1] - first;
+        t0 = lo << low;
+        s0 = start(lo);
+        s = s0 + (int64_t)(i - first) * kPart;
+        e = min(s + kPart, start(lo + 1));
+    }
+};
+
+// Counting sort of one bucket (the particles of the 2^low tiles from
+// blockIdx.x << low) by the low bits, and the starts of its tiles.  Larger buckets
+// (particles gathered in few tiles) are left to k_bucket_parts; the workgroups
+// after the buckets' count their parts' low bits for it (part_hist) and how many
+// parts there are (*nparts).
+__global__ __launch_bounds__(kBucketWG) void k_bucket_sort(
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ idx, int64_t n, int low,
+    int ntiles, int32_t* tile_start, uint32_t* idx_out, uint32_t* part_hist, uint32_t* nparts) {
+    __shared__ uint32_t wcount[kBucketWG / 64][256];
+    __shared__ uint32_t base[257];
+    const int buckets = ((ntiles - 1) >> low) + 1;
+    if ((int)blockIdx.x >= buckets) {
+        BucketPart part;
+        uint32_t total;
+        const int i = (int)blockIdx.x - buckets;
+        part.find(i, tile_start, n, low, ntiles, base, &total);
+        if (i == 0 && threadIdx.x == 0) *nparts = total;
+        if (part.parts == 0) return;
+        __syncthreads();
+        count_low(keys, part.s, part.e, low, base);
+        if (threadIdx.x < 256) part_hist[(int64_t)i * 256 + threadIdx.x] = base[threadIdx.x];
+        return;
+    }
+    const int t0 = (int)blockIdx.x << low;
+    const int64_t s = tile_start[t0];
+    const int64_t e = t0 + (1 << low) < ntiles ? tile_start[t0 + (1 << low)] : n;
+    if (e - s > kBucketMost) return;
+    count_low(keys, s, e, low, base);
+    if (threadIdx.x < 64) scan_256(base);
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        base[threadIdx.x] += (uint32_t)s;
+        note_starts(base, low, t0, ntiles, tile_start);
+    }
+    place_by_low(keys, idx, s, e, low, base, wcount, idx_out);
+}
+
+// The parts of the buckets that k_bucket_sort leaves, a workgroup each: the counts
+// of the bucket's parts give it its places.
+__global__ __launch_bounds__(kBucketWG) void k_bucket_parts(
+    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ idx, int64_t n, int low,
+    int ntiles, int32_t* tile_start, uint32_t* idx_out, const uint32_t* __restrict__ part_hist,
+    const uint32_t* __restrict__ nparts) {
+    if (blockIdx.x >= *nparts) return;
+    __shared__ uint32_t wcount[kBucketWG / 64][256];
+    __shared__ uint32_t base[257];
+    BucketPart part;
+    uint32_t total;
+    const int i = (int)blockIdx.x;
+    part.find(i, tile_start, n, low, ntiles, base, &total);
+    __syncthreads();
+    const int d = threadIdx.x;
+    uint32_t before = 0, all = 0;
+    if (d < 256) {
+        for (int k = 0; k < part.parts; ++k) {
+            const uint32_t c = part_hist[(int64_t)(part.first + k) * 256 + d];
+            before += part.first + k < i ? c : 0u;
+            all += c;
+        }
+        base[d] = all;
+    }
+    __syncthreads();
+    if (d < 64) scan_256(base);
+    __syncthreads();
+    if (d < 256) {
+        base[d] += (uint32_t)part.s0;
+        if (i == part.first) note_starts(base, low, part.t0, ntiles, tile_start);
+        base[d] += before;
+    }
+    place_by_low(keys, idx, part.s, part.e, low, base, wcount, idx_out);
 }
 
 hipError_t scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* sums,
@@ -478,8 +597,13 @@ hipError_t cell_sort(const Key& key, int64_t n, int ntiles, const SortBuffers& b
                 : first_pass<false>(key, n, low, b.keys, kout, iout, ntiles, true, b, stream);
         if (e != hipSuccess || !low) return e;
         const int buckets = ((ntiles - 1) >> low) + 1;
-        hipLaunchKernelGGL(k_bucket_sort, dim3(buckets), dim3(kBucketWG), 0, stream, kout, iout,
-                           n, low, ntiles, b.tile_start, b.idx);
+        // parts of large buckets: full ones and a rest of each
+        const int parts = n > kBucketMost ? (int)(n / kPart + n / kBucketMost) : 0;
+        hipLaunchKernelGGL(k_bucket_sort, dim3(buckets + parts), dim3(kBucketWG), 0, stream,
+                           kout, iout, n, low, ntiles, b.tile_start, b.idx, b.hist, b.scan_tmp);
+        if (parts)
+            hipLaunchKernelGGL(k_bucket_parts, dim3(parts), dim3(kBucketWG), 0, stream, kout,
+                               iout, n, low, ntiles, b.tile_start, b.idx, b.hist, b.scan_tmp);
         return hipGetLastError();
     }
     // LSD, the last pass into b.idx
