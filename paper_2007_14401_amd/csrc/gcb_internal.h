@@ -149,15 +149,21 @@ int64_t kinetic_partial_elems(int64_t n);
 hipError_t launch_count_flagged(const uint8_t* status, int64_t n,
                                 unsigned long long* out, hipStream_t stream);
 
-// zero `words` 8-byte words at p (8-byte aligned) with a kernel
-// copies of whole arrays, all in one launch (no overlaps)
+// Copies of whole arrays, all in one launch (no overlaps).  A list that is given
+// more than it holds is refused by the launch.
 struct CopyList {
-    void* dst[12];
-    const void* src[12];
-    int64_t bytes[12];
+    static constexpr int kMax = 12;   // the 3D state with q/m and ids
+    void* dst[kMax];
+    const void* src[kMax];
+    int64_t bytes[kMax];
     int n = 0;
+    bool over = false;
     void add(void* d, const void* s, int64_t b) {
         if (!s || b <= 0) return;
+        if (n == kMax) {
+            over = true;
+            return;
+        }
         dst[n] = d;
         src[n] = s;
         bytes[n++] = b;
@@ -165,16 +171,19 @@ struct CopyList {
 };
 hipError_t launch_copy_arrays(const CopyList& L, hipStream_t stream);
 
-hipError_t launch_zero_words(void* p, int64_t words, hipStream_t stream);
-
-// the library's binary64 sin and cos of n values (device arrays)
 // dst[s] = src[perm[s]] (inverse: dst[perm[s]] = src[s]) for n binary64 values
+// of each array of a list
 struct PermuteList {
     static constexpr int kMax = 10;
     const double* src[kMax];
     double* dst[kMax];
     int n = 0;
+    bool over = false;
     void add(const double* s, double* d) {
+        if (n == kMax) {
+            over = true;
+            return;
+        }
         src[n] = s;
         dst[n++] = d;
     }
@@ -182,6 +191,10 @@ struct PermuteList {
 hipError_t launch_permute(const PermuteList& L, const uint32_t* perm, int64_t n, bool inverse,
                           hipStream_t stream);
 
+// zero `words` 8-byte words at p (8-byte aligned) with a kernel
+hipError_t launch_zero_words(void* p, int64_t words, hipStream_t stream);
+
+// the library's binary64 sin and cos of n values (device arrays)
 hipError_t launch_sincos(const double* x, double* s, double* c, int64_t n,
                          hipStream_t stream);
 

@@ -172,6 +172,7 @@ __global__ __launch_bounds__(kWG) void k_permute(PermuteList L,
 
 hipError_t launch_permute(const PermuteList& L, const uint32_t* perm, int64_t n, bool inverse,
                           hipStream_t stream) {
+    if (L.over) return hipErrorInvalidValue;
     if (n == 0 || L.n == 0) return hipSuccess;
     const unsigned blocks = (unsigned)((n + kWG - 1) / kWG);
     if (inverse)
@@ -190,6 +191,7 @@ hipError_t launch_sincos(const double* x, double* s, double* c, int64_t n,
 }
 
 hipError_t launch_copy_arrays(const CopyList& L, hipStream_t stream) {
+    if (L.over) return hipErrorInvalidValue;
     int64_t most = 0;
     for (int a = 0; a < L.n; ++a) most = L.bytes[a] > most ? L.bytes[a] : most;
     if (most <= 0) return hipSuccess;
