@@ -65,9 +65,10 @@ extern "C" {
                                bit for bit (the parity build of the kernels) */
 #define GCB_ARITH_FAST  1   /* the production build: multiply-adds fused where the
                                compiler forms them (one rounding instead of two), and
-                               a square root that only serves as a divisor taken as a
-                               refined hardware reciprocal square root, quotients by a
-                               shared value as products with its reciprocal; a step
+                               square roots, quotients and reciprocals from refined
+                               hardware estimates, quotients by a shared value as
+                               products with its reciprocal, interpolations nested, the
+                               curvature drift from one directional derivative; a step
                                differs from GCB_ARITH_EXACT by a few units in the last
                                place (relative 1e-12 asserted per step, switch decisions
                                identical); over many steps the difference grows as the
@@ -307,8 +308,11 @@ int gcb_push_noalloc(gcb_ctx* ctx, gcb_particles* p, const gcb_params* prm,
    1.5e-16 relative for Boris, 3.0e-16 for guiding-center particles); the node
    sums are binary64 until they are added to dE and dB.  The forward
    steps are recomputed internally: with params.sort_every > 0 by the tiled push in place
-   (keep_order), else by the cache-served kernel; needs n_steps * n * 61 +
-   n * 12 bytes of context scratch beside the cell sort's. */
+   (keep_order), else by the cache-served kernel.  Context scratch, kept and
+   grown as needed: n_steps * n * 57 bytes of start states and decisions,
+   n * 125 (the state and the cotangents in tile order, their order), 48 per
+   grid node, 8 per tile of 32^2 cells, and the cell sort's (16.3 per particle,
+   4 per tile). */
 int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start,
                       const gcb_params* prm, int32_t n_steps,
                       const double* const lam_end[7], double* const lam_start[7],
@@ -465,8 +469,8 @@ int gcb_push_3d(gcb_ctx* ctx, gcb_particles3* p, const gcb_params* prm,
    stated there, and the forward steps
    are recomputed internally: with params.sort_every > 0 and a tile window
    that fits in LDS by the tiled push in place (keep_order), else by the
-   cache-served kernel; needs n_steps * n * 77 + n * 12 bytes of context
-   scratch beside the cell sort's. */
+   cache-served kernel.  Context scratch as in 2D: n_steps * n * 73 bytes, n * 157,
+   48 per grid node, 8 per tile of 6^3 cells, and the cell sort's. */
 int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_params* prm,
                          int32_t n_steps, const double* const lam_end[9],
                          double* const lam_start[9], float* const dE[3], float* const dB[3],

@@ -8,19 +8,21 @@
 // LDS: the fields, and the sums of the node cotangents, which are added to the
 // gradient grid once at the end.  The window reaches as far as a particle can
 // drift in the batch; what falls outside all the same goes to the grid directly.
+// Particles of nearly empty tiles have a kernel without windows (k_adjoint_loose).
 //
 // Node sums in binary64, because the LDS adds those at full speed and binary32
 // ones lane by lane: a wavefront's ds_add_f32 holds the LDS for 194 cycles
 // wherever its addresses lie, ds_add_f64 for 12 (consecutive) to 22 (random).
 // With binary32 sums the 2D sweep below took 20.5 ms instead of 6.3 (its tiles of
 // 30 then).
-// Device-scope atomics, some 2e10 per second, are slower again: hence the window.
+// Device-scope atomics, some 2e10 per second with an address per lane, are slower
+// again: hence the window.
 //
 // Bound by the LDS in 2D (65 % busy: at K = 4 a guiding-center step has six points
 // of 24 adds and eleven gathers of 16 loads; VALU 51 %) with two wavefronts per
 // SIMD to hide its latency: 256 registers and the window leave room for no
-// more.  In 3D fewer particles fit a window's tile (225 at one per cell) than
-// fill the wavefronts: LDS 41 %, VALU 30 %.
+// more.  In 3D a window's tile has 216 cells, whose particles need not fill the
+// wavefronts (225 of them at 3e5 on 64^3: LDS 41 %, VALU 30 %).
 //   2D, 1e6 particles, 1024^2, 32 steps, K = 4: 5.9 ms, the whole backward 35.1
 //   -> 10.3 ms, 9.7 with the sorts of today (before: a launch per step and
 //   regime with global gathers, records of the cotangents to memory, and their

@@ -53,8 +53,8 @@ constexpr bool kMixed = std::is_same<R, float>::value;
 //     b x (V.grad)b = b x (V.grad)B / B, because (V.grad)b is (V.grad)B / B
 //     less its part along b, for V = (u_par^2/Gamma) b + u_par v_E
 //     (v_curv_dir); likewise A and C, as v_E is perpendicular to b.
-// The step is bound by the issue of its binary64 arithmetic (VALU busy in two
-// thirds of the SIMD cycles, memory at a sixth), so time follows the count of
+// The step is bound by the issue of its binary64 arithmetic (VALU busy in three
+// quarters of the SIMD cycles, memory at a sixth), so time follows the count of
 // operations.
 #ifndef GCB_FAST_ARITH
 #define GCB_FAST_ARITH 0
@@ -1154,14 +1154,14 @@ GCB_HD double nan_max(double a, double b) {
 // The end of a guiding-center step that the next step of the same particle
 // takes up: the sample and the local quantities at R^{n+1/2}, which is the
 // next step's R^{n-1/2} (the midpoint of the same two positions) whenever the
-// two come out as the same numbers -- always, but for a particle that crossed
-// the edge of the box.  The same numbers in, the same numbers out: the parity
-// arithmetic keeps its bits.  One gather and one set of local quantities in six
+// two come out as the same numbers -- wherever the difference of the positions is
+// exact: not across the edge of the box, and not always next to coordinate 0.
+// The same numbers in, the same numbers out: the parity arithmetic keeps its bits.  One gather and one set of local quantities in six
 // are left out.  Binary64 forms only: in the mixed one the compiler's choice of
 // fused operations, and so the side of fp_tol that a residual falls on, hangs
 // on where the values were computed.
-// Measured (16.8M particles, 4096^2, production arithmetic, 100 steps):
-// 11.66 -> 10.77 ms; 3D, 2M on 128^3, 9.11 -> 8.66 ms.
+// Measured, production arithmetic: 1e7 particles, 4096^2, 20 steps, 11.66 ->
+// 10.77 ms; 3D, 1e7 on 128^3, 8 steps, 9.11 -> 8.66 ms.
 template <typename R, class S>
 struct Midpoint {
     S s;
