@@ -1068,7 +1068,11 @@ int gcb_push_backward(gcb_ctx* ctx, const gcb_particles* start, const gcb_params
     Timer t(ctx, stream, GCB_TIMER_BACKWARD);
     if (ordered) {
         SortBuffers ssb{};
-        if ((rc = prepare_sort(ctx, n, og.ntx * og.nty, ssb))) return rc;
+        // room for the recomputation's tiles as well: to grow the buffers between
+        // the two sorts waits for the first (2 to 5 ms of a new context's call)
+        const TileGeom pg = make_geom(ctx, prm);
+        const int tiles = std::max(og.ntx * og.nty, prm->sort_every > 0 ? pg.ntx * pg.nty : 0);
+        if ((rc = prepare_sort(ctx, n, tiles, ssb))) return rc;
         GCB_HIP(launch_cell_sort(start->x, start->y, n, 1.0 / ctx->dx, 1.0 / ctx->dy, og, ssb,
                                  stream));
         // the sort's buffers serve the recomputation's sorts too: keep the
@@ -1497,7 +1501,10 @@ int gcb_push_backward_3d(gcb_ctx* ctx, const gcb_particles3* start, const gcb_pa
     Timer t(ctx, stream, GCB_TIMER_BACKWARD);
     if (ordered) {
         SortBuffers ssb{};
-        if ((rc = prepare_sort(ctx, n, og.ntx * og.nty * og.ntz, ssb))) return rc;
+        const TileGeom3 pg = make_geom3(ctx, prm);   // room for its tiles, as in 2D
+        const int tiles = std::max(og.ntx * og.nty * og.ntz,
+                                   prm->sort_every > 0 ? pg.ntx * pg.nty * pg.ntz : 0);
+        if ((rc = prepare_sort(ctx, n, tiles, ssb))) return rc;
         GCB_HIP(launch_cell_sort3(start->x, start->y, start->z, n, 1.0 / ctx->d3[0],
                                   1.0 / ctx->d3[1], 1.0 / ctx->d3[2], og, ssb, stream));
         GCB_HIP(hipMemcpyAsync(perm, ssb.idx, (size_t)n * 4, hipMemcpyDeviceToDevice, stream));
