@@ -18,11 +18,11 @@
 // Device-scope atomics, some 2e10 per second with an address per lane, are slower
 // again: hence the window.
 //
-// Bound by the LDS in 2D (65 % busy: at K = 4 a guiding-center step has six points
-// of 24 adds and eleven gathers of 16 loads; VALU 51 %) with two wavefronts per
+// Bound by the LDS in 2D (72 % busy: at K = 4 a guiding-center step has six points
+// of 24 adds and eleven gathers of 16 loads; VALU 56 %) with two wavefronts per
 // SIMD to hide its latency: 256 registers and the window leave room for no
 // more.  In 3D a window's tile has 216 cells, whose particles need not fill the
-// wavefronts (225 of them at 3e5 on 64^3: LDS 41 %, VALU 30 %).
+// wavefronts (225 of them at 3e5 on 64^3: LDS 43 %, VALU 30 %).
 //   2D, 1e6 particles, 1024^2, 32 steps, K = 4: 5.9 ms, the whole backward 35.1
 //   -> 10.3 ms, 9.7 with the sorts of today (before: a launch per step and
 //   regime with global gathers, records of the cotangents to memory, and their

@@ -853,7 +853,7 @@ GCB_HD int coupled_step(const T* __restrict__ F, const double* __restrict__ dl_t
 // metric and, on the guiding-center branch, the fields and the local quantities
 // already: only the derivatives are evaluated there.  The same values at the
 // same point, a sample, a metric and a set of local quantities in five left out
-// at K = 4.  The VALU issues in 83 % of the cycles, so instructions count:
+// at K = 4.  The VALU issues in 73 % of the cycles, so instructions count:
 // production form, 1e7 particles, 512^2, 16 steps: 12.46 -> 11.10 ms, and 10.74
 // with the midpoints' sines from the step start's (sincos_near); parity form,
 // 2e6: 4.63 -> 4.36 ms (with two wavefronts per SIMD, see there).  Carrying

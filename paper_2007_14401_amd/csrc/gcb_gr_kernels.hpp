@@ -26,8 +26,8 @@ namespace gcb {
 namespace GCB_GR_KERN_NS {
 
 constexpr int kGrWG = 256;
-// waves per SIMD the register allocation must allow (the kernel is bound by
-// the issue of its binary64 arithmetic; three waves hide its latencies)
+// waves per SIMD the register allocation must allow: the precision form's; the
+// binary64 units, which spill at three, set two
 #ifndef GCB_GR_MIN_WAVES
 #define GCB_GR_MIN_WAVES 3
 #endif
